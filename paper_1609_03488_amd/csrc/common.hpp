@@ -219,7 +219,8 @@ constexpr int VEC_TILE_MIN = 1024; // smallest tile length the autotuner tries (
 constexpr int VEC_NT = 256;        // threads per vector-kernel block
 constexpr int CONV_TILE_F32 = 512;   // outputs per convolution tile (64 lanes x 8)
 constexpr int CONV_TILE_F64 = 256;   // (64 lanes x 4)
-constexpr int CONV_KC_MAX_F32 = 2048;  // taps staged per pass (LDS: (512 + 2*2048 + 16) * 4 B)
+constexpr int CONV_KC_MAX = 2048;      // taps per pass of a convolution launch (LDS: its window)
+constexpr int CONV_KC_MAX_F32 = 2048;  // taps staged per pass by k_fused
 constexpr int CONV_KC_MAX_F64 = 1024;
 constexpr int CONV_R_F32 = 8;        // taps are padded to a multiple of this
 constexpr int CONV_R_F64 = 4;

@@ -142,7 +142,7 @@ __global__ __launch_bounds__(CM_NT) void k_conv_mfma(Tables tb, ConvLaunch cl, i
         for (int v = 0; v < 4; ++v) {
             const int64_t oi = o0 + v;
             if (oi < n_out)
-                o[oi] = (float)(owned_init<float>(d, tb.ids, adj, out, in, base, sigma, g0 + oi) +
+                o[oi] = (float)(owned_init<float>(d, tb.ids, adj, in, base, sigma, g0 + oi) +
                                 s * (double)(acc0[v] + acc1[v]));
         }
     } else {

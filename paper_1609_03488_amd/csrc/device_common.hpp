@@ -283,12 +283,10 @@ DEVI void st4(gptr<T> p, const Chunks& c, int j, const v4<T>& v) {
 // correlation form:  out[o] += s * sum_t w[t] * in[o + off + t]  with
 //   A x : w = reversed taps, off = -(k-1), in = x (zero outside [0, n_in));
 //   A^T y: w = taps,          off = 0,      in = y.
-// One wave computes a tile of CONV_NT * R consecutive outputs; each lane keeps
-// R outputs in registers and slides a 2R-wide register window over an LDS copy
-// of the tile's input window (TILE + kc - 1 values, staged with batched
-// loads); the taps of the chunk sit in LDS and are read as broadcasts.  The
-// LDS size follows the kernel length (dynamic shared memory), so kernels up to
-// CONV_KC_MAX taps need a single staging pass.
+// Each lane keeps R outputs in registers and slides a register window over an
+// LDS copy of the tile's input window, staged with batched loads.  Two forms, both
+// summing in tap order: k_conv (one wave, taps by scalar loads) and conv_sums (a
+// tile of R outputs per thread of a workgroup, taps staged in LDS, for k_fused).
 constexpr int CONV_NT = 64;
 template <typename T> struct ConvCfg;
 template <> struct ConvCfg<float> { static constexpr int R = 8; };
@@ -366,22 +364,37 @@ DEVI CheckOut check_outcome(gptr<const double> sc, double tau, double kap, doubl
     return o;
 }
 
-// The part of an apply's output element g (index in the output vector) that
-// does not come from convolution or dense blocks: base[g] (base >= 0) plus the
-// identity blocks of the instance that cover g.
-template <typename T>
-DEVI double owned_init(const InstDesc& d, const IdBlock* ids, int adj, int out, int in, int base,
-                       double sigma, int64_t g) {
-    (void)out;
+// The part of an apply's output elements g .. g + no - 1 (no <= R; indices in the
+// output vector) that does not come from convolution or dense blocks: base[g]
+// (base >= 0) plus the identity blocks of the instance that cover g.
+template <typename T, int R>
+DEVI void owned_init_n(const InstDesc& d, const IdBlock* ids, int adj, int in, int base, double sigma,
+                       int64_t g, int no, double (&v)[R]) {
     gptr<const T> src = adj ? yvec<T>(d, in) : xvec<T>(d, in);
-    double v = base >= 0 ? (double)(adj ? xvec<T>(d, base) : yvec<T>(d, base))[g] : 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        v[r] = (base >= 0 && r < no) ? (double)(adj ? xvec<T>(d, base) : yvec<T>(d, base))[g + r] : 0.0;
     for (int b = d.id0; b < d.id1; ++b) {
         const IdBlock ib = ids[b];
         const int64_t r0 = adj ? ib.col0 : ib.row0;
         const int64_t c0 = adj ? ib.row0 : ib.col0;
-        if (g >= r0 && g < r0 + ib.len) v += sigma * ib.scale * (double)src[g - r0 + c0];
+        T x[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const bool hit = r < no && g + r >= r0 && g + r < r0 + ib.len;
+            x[r] = hit ? src[g + r - r0 + c0] : T(0);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (r < no && g + r >= r0 && g + r < r0 + ib.len) v[r] += sigma * ib.scale * (double)x[r];
     }
-    return v;
+}
+
+template <typename T>
+DEVI double owned_init(const InstDesc& d, const IdBlock* ids, int adj, int in, int base, double sigma, int64_t g) {
+    double v[1];
+    owned_init_n<T, 1>(d, ids, adj, in, base, sigma, g, 1, v);
+    return v[0];
 }
 
 // Initialisation of an apply's output tile: base plus identity blocks, for the
@@ -616,48 +629,5 @@ DEVI void conv_sums(const ConvBlock& cb, int adj, PC src, int64_t ot, int KC, un
         }
     }
 }
-
-// One tile of NT * R consecutive outputs (from `ot`) of a convolution block
-// (adj = 0: A, out is Y; adj = 1: A^T, out is X), out += sigma * scale * (...),
-// or, when ids is given and the block owns its output range, out = the
-// element's base and identity-block terms + sigma * scale * (...).
-// smem: (NT * R + 2 * KC + 2R) elements of T.  Called by every thread of the
-// workgroup; starts and ends with a workgroup barrier.
-template <typename T, int NT>
-DEVI void conv_tile(const InstDesc& d, const ConvBlock& cb, int adj, int out, int in, double sigma,
-                    int64_t ot, int KC, unsigned char* smem, const IdBlock* ids = nullptr,
-                    int base = -1) {
-    constexpr int R = ConvCfg<T>::R;
-    const int64_t n_out = adj ? cb.n_in : cb.n_in + cb.k - 1;
-    gptr<T> o = adj ? xvec<T>(d, out) + cb.col0 : yvec<T>(d, out) + cb.row0;
-    gptr<const T> src = adj ? yvec<T>(d, in) + cb.row0 : xvec<T>(d, in) + cb.col0;
-    const int tid = threadIdx.x;
-    T acc[R];
-    conv_sums<T, NT>(cb, adj, src, ot, KC, smem, acc);
-    const double s = sigma * cb.scale;
-    if (ids && (cb.own >> adj) & 1) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t oi = ot + (int64_t)tid * R + r;
-            if (oi < n_out) o[oi] = (T)(owned_init<T>(d, ids, adj, out, in, base, sigma,
-                                                      (adj ? cb.col0 : cb.row0) + oi) +
-                                        s * (double)acc[r]);
-        }
-    } else {
-        T ov[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t oi = ot + (int64_t)tid * R + r;
-            ov[r] = oi < n_out ? o[oi] : T(0);
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t oi = ot + (int64_t)tid * R + r;
-            if (oi < n_out) o[oi] = (T)((double)ov[r] + s * (double)acc[r]);
-        }
-    }
-    __syncthreads();
-}
-
 
 }  // namespace cgs

@@ -702,7 +702,7 @@ int Engine::build(const std::vector<InstRec>& r) {
     const int64_t kcmax = precision == CGS_FP64 ? CONV_KC_MAX_F64 : CONV_KC_MAX_F32;
     auto slot_kc = [&](const std::vector<ConvTile>& v) {
         int64_t kc = conv_r(precision);
-        for (const ConvTile& t : v) kc = std::max(kc, std::min(kcmax, im.cblk[t.blk].kpad));
+        for (const ConvTile& t : v) kc = std::max(kc, std::min<int64_t>(CONV_KC_MAX, im.cblk[t.blk].kpad));
         return (int)kc;
     };
     // the FFT engine can take a slot when every block in it has spectra

@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <utility>
 #include <vector>
 
 #include "cgs.h"
@@ -39,27 +40,178 @@ __global__ __launch_bounds__(VEC_NT) void k_apply_init(Tables tb, int adj, int o
     init_tile<T>(tb, d, tl, adj, out, in, base, sigma);
 }
 
-template <typename T>
-__global__ __launch_bounds__(CONV_NT) void k_conv(Tables tb, ConvLaunch cl, int adj, int out, int in,
+// Direct convolution: one wave sums 64 R outputs, lane l the R ones from R l, over
+// all taps in tap order (the order, and so the result, depends on neither R nor
+// the form of the loop).  Two forms, chosen by the launch's tile count (conv_sub):
+//  * R = ConvCfg::R, many tiles: each step of 2 R taps reads its window values and
+//    taps from LDS; the other waves of the SIMD cover the reads.
+//  * R half of that (NARROW), few tiles: the launch is one wave's chain over the taps
+//    (n = 3000, k = 1365 in FP64: 18 waves on the chip at R = 4, 25.2 us).  The
+//    window values of the next 16 taps are read while the current ones are summed,
+//    and the taps, which as broadcast reads cost as much LDS time as the window,
+//    travel in a register, 16 to a row of lanes, and reach the row's lanes through
+//    DPP broadcasts: 17.4 us, bound by the latency of the dependent FP64 sums
+//    (about 22 cycles a tap).
+constexpr int CONV_U = 16;   // taps per step of the narrow form
+
+// the row's lane N value in every lane of the row of 16 (the builtin's value has
+// its operands' width, 64 bits for a double's, whatever type the front end states)
+template <int N>
+DEVI double row_bcast(double v) {
+    const long x = __builtin_bit_cast(long, v);
+    const long y = __builtin_amdgcn_update_dpp(x, x, 0x150 + N, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, y);
+}
+template <int N>
+DEVI float row_bcast(float v) {
+    const int x = __builtin_bit_cast(int, v);
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(x, x, 0x150 + N, 0xf, 0xf, true));
+}
+// acc[r] += tap t * x[r + t], t = 0..15 in order: x[0..R) in c, the rest in v, tap t
+// in lane t of each row of tw; c becomes the R values the next 16 taps start with
+template <typename T, int R, int... N>
+DEVI void conv_row(T (&acc)[R], T (&c)[R], const T (&v)[CONV_U], T tw, std::integer_sequence<int, N...>) {
+    auto one = [&](T tv, int t) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            acc[r] = fma(tv, r + t < R ? c[(r + t) % R] : v[(r + t - R + CONV_U) % CONV_U], acc[r]);
+    };
+    (one(row_bcast<N>(tw), N), ...);
+#pragma unroll
+    for (int j = 0; j < R; ++j) c[j] = v[CONV_U - R + j];
+}
+
+__host__ __device__ constexpr int conv_init_parts(int sub) { return sub > 1 ? 8 : 2; }
+template <typename T, int R>
+__global__ __launch_bounds__(CONV_NT) void k_conv(Tables tb, ConvLaunch cl, int sub, int adj, int out, int in,
                                                   int base, double sigma, int gate) {
     extern __shared__ __align__(16) unsigned char conv_smem[];
-    if ((int)blockIdx.x >= cl.ntiles) {   // initialisation tiles riding on the launch
-        const VecTile it = cl.init[blockIdx.x - cl.ntiles];
+    if ((int)blockIdx.x >= cl.ntiles * sub) {
+        // initialisation tiles riding on the launch, in parts: a whole tile on one
+        // wave is a chain of 12.5 us, longer than most launches of few tiles
+        const int w = (int)blockIdx.x - cl.ntiles * sub, np = conv_init_parts(sub), len = VEC_TILE / np;
+        VecTile it = cl.init[w / np];
+        const int p0 = (w % np) * len;
+        if (p0 >= it.len) return;
+        it.start += p0;
+        it.len = it.len - p0 < len ? it.len - p0 : len;
         const InstDesc di = tb.inst[it.inst];
         if (gate_ok(scal(di), gate)) init_tile<T>(tb, di, it, adj, out, in, base, sigma);
         return;
     }
-    const ConvTile tl = cl.tiles[blockIdx.x];
+    const int tix = (int)blockIdx.x / sub;
+    const ConvTile tl = cl.tiles[tix];
     const InstDesc d = tb.inst[tl.inst];
-    if (!gate_ok(scal(d), gate)) return;
     const ConvBlock cb = cl.blocks[tl.blk];
-    conv_tile<T, CONV_NT>(d, cb, adj, out, in, sigma, tl.start, cl.kc, conv_smem, tb.ids, base);
-}
-
-size_t conv_smem_bytes(int prec, int kc) {
-    const int R = prec == 0 ? CONV_R_F64 : CONV_R_F32;
-    const int tile = prec == 0 ? CONV_TILE_F64 : CONV_TILE_F32;
-    return (size_t)(tile + 2 * kc + 2 * R) * (prec == 0 ? 8 : 4);
+    if (!gate_ok(scal(d), gate)) return;
+    constexpr int TILE = CONV_NT * R, U = CONV_U;
+    constexpr bool NARROW = R < ConvCfg<T>::R;
+    T* taps = reinterpret_cast<T*>(conv_smem);   // kc entries
+    T* win = taps + cl.kc;                       // TILE + kc entries
+    const int lane = threadIdx.x, li = lane * R;
+    const int64_t ot = tl.start + (int64_t)((int)blockIdx.x - tix * sub) * TILE;
+    const int64_t n_out = adj ? cb.n_in : cb.n_in + cb.k - 1;
+    if (ot >= n_out) return;
+    const int64_t n_in = adj ? cb.n_in + cb.k - 1 : cb.n_in;
+    const int64_t off = adj ? 0 : -(cb.k - 1), g0 = adj ? cb.col0 : cb.row0;
+    gptr<T> o = adj ? xvec<T>(d, out) + cb.col0 : yvec<T>(d, out) + cb.row0;
+    gptr<const T> src = adj ? yvec<T>(d, in) + cb.row0 : xvec<T>(d, in) + cb.col0;
+    gptr<const T> w = (gptr<const T>)(adj ? cb.w_adj : cb.w_fwd);
+    const bool own = (cb.own >> adj) & 1;
+    const int no = n_out - ot - li < R ? (int)(n_out - ot - li) : R;   // the lane's outputs (<= 0: none)
+    double ov[R];   // what they hold besides the sums
+    T acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = T(0);
+    for (int64_t t0 = 0; t0 < cb.kpad; t0 += cl.kc) {
+        const int kc = (int)((cb.kpad - t0) < cl.kc ? (cb.kpad - t0) : cl.kc);
+        const int nwin = TILE + kc;
+        // the window's positions [qlo, qhi) lie inside the block's inputs
+        const int64_t i0 = ot + off + t0;
+        const int qlo = i0 < 0 ? (int)-i0 : 0;
+        const int qhi = n_in - i0 < nwin ? (int)(n_in - i0) : nwin;
+        gptr<const T> sw = src + i0;
+        if (t0) __syncthreads();
+        constexpr int NB = 16;   // window loads in flight per lane
+        for (int b0 = 0; b0 < nwin; b0 += NB * CONV_NT) {
+            T v[NB], tv[NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const int i = b0 + j * CONV_NT + lane;
+                v[j] = (i >= qlo && i < qhi) ? sw[i] : T(0);
+                tv[j] = i < kc ? w[t0 + i] : T(0);
+            }
+            if (t0 == 0 && b0 == 0) {   // (while the window's loads are in flight)
+                if (own) {
+                    owned_init_n<T, R>(d, tb.ids, adj, in, base, sigma, g0 + ot + li, no, ov);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) ov[r] = r < no ? (double)o[ot + li + r] : 0.0;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const int i = b0 + j * CONV_NT + lane;
+                if (i < nwin) win[i] = v[j];
+                if (i < kc) taps[i] = tv[j];
+            }
+        }
+        __syncthreads();
+        int tt = 0;
+        if constexpr (NARROW) {
+            // steps of U taps in two register buffers (the barriers keep the
+            // compiler from sinking the next step's reads to where they are
+            // used); tap tt + (lane % 16) in every row of 16 lanes
+            T c[R], xa[U], xb[U], ta = T(0), te = T(0);
+            auto fetch = [&](int u, T (&v)[U], T& tv) {
+#pragma unroll
+                for (int j = 0; j < U / Vec16<T>::W; ++j) {
+                    using V = typename Vec16<T>::type;
+                    const V q = *reinterpret_cast<const V*>(win + li + u * U + R + j * Vec16<T>::W);
+                    vec_get<T>(q, v + j * Vec16<T>::W);
+                }
+                tv = taps[u * U + (lane & 15)];
+            };
+            constexpr auto seq = std::make_integer_sequence<int, U>{};
+#pragma unroll
+            for (int j = 0; j < R; ++j) c[j] = win[li + j];
+            const int nu = kc / U;
+            if (nu > 0) fetch(0, xa, ta);
+            for (int u = 0; u + 1 < nu; u += 2) {
+                fetch(u + 1, xb, te);
+                __builtin_amdgcn_sched_barrier(0);
+                conv_row<T, R>(acc, c, xa, ta, seq);
+                fetch(u + 2 < nu ? u + 2 : u, xa, ta);
+                __builtin_amdgcn_sched_barrier(0);
+                conv_row<T, R>(acc, c, xb, te, seq);
+            }
+            if (nu & 1) conv_row<T, R>(acc, c, xa, ta, seq);
+            tt = nu * U;
+        } else {
+            T a[R], b[R], tw[R];
+            lds_vec<T, R>(a, win + li);
+            for (; tt + 2 * R <= kc; tt += 2 * R) {
+                lds_vec<T, R>(b, win + li + tt + R);
+                lds_vec<T, R>(tw, taps + tt);
+                conv_step<T, R>(acc, a, b, tw);
+                lds_vec<T, R>(a, win + li + tt + 2 * R);
+                lds_vec<T, R>(tw, taps + tt + R);
+                conv_step<T, R>(acc, b, a, tw);
+            }
+        }
+        for (; tt < kc; tt += 4) {   // (kc is a multiple of 4)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const T tv = taps[tt + t];
+#pragma unroll
+                for (int r = 0; r < R; ++r) acc[r] = fma(tv, win[li + tt + t + r], acc[r]);
+            }
+        }
+    }
+    const double s = sigma * cb.scale;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (r < no) o[ot + li + r] = (T)(ov[r] + s * (double)acc[r]);
 }
 
 // ---------------------------------------------------------------- operator: dense block
@@ -994,13 +1146,27 @@ void launch_apply_init(int prec, const Tables& t, int adj, int out, int in, int 
     CGS_DISPATCH(prec, k_apply_init, adj ? t.nx_tiles : t.ny_tiles, VEC_NT, st, t, adj, out, in,
                  base, sigma, gate);
 }
+// Workgroups per tile of the tile tables: two, in the narrow form of k_conv, up to
+// 512 tiles, where the chip has at most two waves per SIMD in the other form and a
+// wave's own chain bounds the launch (FP64, k = 257: 118 tiles 9.1 -> 7.0 us).
+static int conv_sub(int tiles) { return tiles <= 512 ? 2 : 1; }
+
 void launch_conv(int prec, const Tables& t, const ConvLaunch& c, int adj, int out, int in, int base,
                  double sigma, int gate, hipStream_t st) {
-    const int grid = c.ntiles + c.ninit;
+    const int sub = conv_sub(c.ntiles);
+    const int grid = c.ntiles * sub + c.ninit * conv_init_parts(sub);
     if (grid <= 0) return;
-    const size_t lds = conv_smem_bytes(prec, c.kc);
-    if (prec == 0) k_conv<double><<<grid, CONV_NT, lds, st>>>(t, c, adj, out, in, base, sigma, gate);
-    else k_conv<float><<<grid, CONV_NT, lds, st>>>(t, c, adj, out, in, base, sigma, gate);
+    // taps and window (at the larger R)
+    const size_t lds = (size_t)(2 * c.kc + (prec == 0 ? CONV_TILE_F64 : CONV_TILE_F32)) * (prec == 0 ? 8 : 4);
+#define CGS_CONV(T, R) k_conv<T, R><<<grid, CONV_NT, lds, st>>>(t, c, sub, adj, out, in, base, sigma, gate)
+    if (prec == 0) {
+        if (sub == 2) CGS_CONV(double, 2);
+        else CGS_CONV(double, 4);
+    } else {
+        if (sub == 2) CGS_CONV(float, 4);
+        else CGS_CONV(float, 8);
+    }
+#undef CGS_CONV
 }
 void launch_gemv(int prec, const Tables& t, const DenseLaunch& d, int adj, int out, int in,
                  double sigma, int gate, hipStream_t st) {

@@ -45,8 +45,6 @@ struct ConvLaunch {
     // the A launch's initialisation workgroups would write (0: none)
     int idrows;
 };
-// dynamic LDS bytes of the convolution kernel for a staging pass of kc taps
-size_t conv_smem_bytes(int prec, int kc);
 struct DenseLaunch {
     const DenseTile* tiles;
     const DenseBlock* blocks;
