@@ -15,17 +15,20 @@
 // stages of radix 8, 8, 8 and 4 (Govindaraju et al., "High performance
 // discrete Fourier transforms on graphics processors", SC 2008); each thread
 // keeps the 8 values of its butterflies in registers; the twiddles come from a
-// table of the 2048 roots of unity (sincospi) that each workgroup builds in LDS
-// first.  One workgroup per two output blocks (2B outputs).
+// table of roots of unity (sincospi) that each workgroup copies to LDS first.  One workgroup per two output blocks (2B outputs).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstdint>
+#include <mutex>
 
+#include "cgs.h"
 #include "kernels.hpp"
 #include "device_common.hpp"
 
 namespace cgs {
+
+int fail(int code, const char* fmt, ...);
 
 namespace {
 
@@ -85,17 +88,35 @@ DEVI int tw_index(int e) {   // entry -> m
     if (e < TW512) return (((e - TW64) / 64 + 1) * ((e - TW64) % 64) * (FFT_L / 512)) & (FFT_L - 1);
     return (((e - TW512) / 512 + 1) * ((e - TW512) % 512)) & (FFT_L - 1);
 }
-// filled by every workgroup (8 values per thread)
-DEVI void fill_twiddles(cf* tw) {
-#pragma unroll
-    for (int r = 0; r < (TW_N + FT - 1) / FT; ++r) {
-        const int e = threadIdx.x + FT * r;
-        if (e >= TW_N) break;
+// The table's values, in device memory (one copy per GPU, written once per GPU by
+// fft_prepare).  A workgroup copies them to LDS beside its window loads; computing
+// them (eight sincospi per thread) took about 0.6 us of every launch.
+__device__ float2 g_twiddles[TW_N];
+__global__ __launch_bounds__(FT) void k_twiddles() {
+    for (int e = threadIdx.x; e < TW_N; e += FT) {
         float s, c;
         sincospif(-2.0f * (float)tw_index(e) / (float)FFT_L, &s, &c);
-        tw[e] = {c, s};
+        g_twiddles[e] = make_float2(c, s);
     }
 }
+constexpr int TW_PER = (TW_N + FT - 1) / FT;
+struct TwRegs {
+    float2 v[TW_PER];
+    DEVI void load() {
+#pragma unroll
+        for (int r = 0; r < TW_PER; ++r) {
+            const int e = threadIdx.x + FT * r;
+            v[r] = g_twiddles[e < TW_N ? e : 0];
+        }
+    }
+    DEVI void store(cf* tw) const {
+#pragma unroll
+        for (int r = 0; r < TW_PER; ++r) {
+            const int e = threadIdx.x + FT * r;
+            if (e < TW_N) tw[e] = {v[r].x, v[r].y};
+        }
+    }
+};
 // v[r] *= factor (r - 1) of the stage table `t` (stride n), r = 1 .. R-1
 template <int R>
 DEVI void twiddle(cf* v, const cf* t, int n) {
@@ -139,6 +160,83 @@ DEVI void fft2048(cf* v, cf* lds, const cf* tw) {
     __syncthreads();
 }
 
+// The identity blocks that reach a workgroup's outputs, in table order: outputs at
+// offsets [lo, hi) from its first one (output vector position gw) take the input
+// at off + offset.  One lane per block reads the table while the window's loads
+// are in flight; walked where they are used, the blocks' records were dependent
+// memory round trips (six blocks: 16.7 us per right-hand side launch, two: 11.8).
+struct IdRec {
+    int lo, hi;   // (lo >= hi: none)
+    int64_t off;
+    double scale;
+};
+DEVI IdRec id_rec(const IdBlock& ib, int adj, int64_t gw, int nout) {
+    const int64_t r0 = adj ? ib.col0 : ib.row0, c0 = adj ? ib.row0 : ib.col0;
+    const int64_t rl = r0 - gw, rh = r0 + ib.len - gw;   // the block's outputs, clamped to [0, nout)
+    IdRec r;
+    r.lo = rl < 0 ? 0 : rl > nout ? nout : (int)rl;
+    r.hi = rh > nout ? nout : rh < 0 ? 0 : (int)rh;
+    r.off = c0 - r0 + gw;
+    r.scale = ib.scale;
+    return r;
+}
+struct IdList {
+    static constexpr int N = 64;
+    IdRec rec[N];   // those of the instance's first N blocks with outputs here
+    int n, more;    // how many, and the blocks past the first N
+    DEVI IdRec at(const Tables& tb, const InstDesc& d, int adj, int64_t gw, int nout, int b) const {
+        return b < n ? rec[b] : id_rec(tb.ids[d.id0 + N + (b - n)], adj, gw, nout);
+    }
+};
+// (by the first wave; a barrier follows before the list is read)
+DEVI void id_list(const Tables& tb, const InstDesc& d, int adj, int64_t gw, int nout, IdList& l) {
+    const int lane = threadIdx.x, nb = d.id1 - d.id0;
+    IdRec r{0, 0, 0, 0.0};
+    if (lane < nb) r = id_rec(tb.ids[d.id0 + lane], adj, gw, nout);
+    const bool hit = r.lo < r.hi;
+    const unsigned long long m = __ballot(hit);
+    if (hit) l.rec[__popcll(m & ((1ull << lane) - 1))] = r;
+    if (lane == 0) {
+        l.n = __popcll(m);
+        l.more = nb > IdList::N ? nb - IdList::N : 0;
+    }
+}
+
+// Four consecutive elements at any element alignment
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+// the identity block's inputs for outputs o .. o + 3 (0 where it has none)
+DEVI f32x4 id_load(gptr<const float> iw, int o, const IdRec& ib) {
+    f32x4 l = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (o >= ib.lo && o + 4 <= ib.hi) {
+        const f32x4u q = *(gptr<const f32x4u>)(iw + o);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) l[e] = q[e];
+    } else if (o < ib.hi && o + 4 > ib.lo) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (o + e >= ib.lo && o + e < ib.hi) l[e] = iw[o + e];
+    }
+    return l;
+}
+// stores v[e] at p[e] for the outputs o + e in [lo, hi); out4: p 16-byte aligned
+template <typename V>
+DEVI void out4_as(gptr<float> p, int o, int lo, int hi, const f32x4& v) {
+    if (o >= lo && o + 4 <= hi) {
+        *(gptr<V>)p = v;
+    } else if (o < hi && o + 4 > lo) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (o + e >= lo && o + e < hi) p[e] = v[e];
+    }
+}
+DEVI void out4(gptr<float> p, int o, int lo, int hi, const f32x4& v) { out4_as<f32x4>(p, o, lo, hi, v); }
+DEVI void out4u(gptr<float> p, int o, int lo, int hi, const f32x4& v) { out4_as<f32x4u>(p, o, lo, hi, v); }
+
+// Partial sums of a CG step folded into an A^T launch:
+//   fold 1: ||r||^2, ||h||^2;  fold 2: <p, q>, ||r||^2, <r, q>, ||q||^2
+struct Fold4 {
+    double a, b, c, d;
+};
 // The workgroup's partials of a folded CG step (every thread calls this).
 DEVI void fold_partials(double* part, const Fold4& f, double* red) {
     double v[4] = {f.a, f.b, f.c, f.d};
@@ -156,7 +254,9 @@ __global__ __launch_bounds__(FT) void k_conv_spectrum(const float* w, int k, flo
     __shared__ cf lds[LDS_L];
     __shared__ cf tw[TW_N];
     const int t = threadIdx.x;
-    fill_twiddles(tw);
+    TwRegs twr;
+    twr.load();
+    twr.store(tw);
     cf v[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
@@ -170,12 +270,36 @@ __global__ __launch_bounds__(FT) void k_conv_spectrum(const float* w, int k, flo
         for (int r = 0; r < 4; ++r) spec[t + FT * h + 512 * r] = make_float2(v[4 * h + r].x, -v[4 * h + r].y);
 }
 
+DEVI void conv_windows(cf (&v)[8], cf* lds, const cf* tw, const void* spec) {
+    const int t = threadIdx.x;
+    fft2048(v, lds, tw);
+    // product with conj(DFT(w)), conjugated: the inverse is a forward transform.
+    // The thread holds X[t + 256 (h + 2 r)] in v[4 h + r], which is exactly
+    // the set x[t + 256 r'] the next transform's first stage takes from it:
+    // the products only change register, v'[r'] = p[4 (r' % 2) + r' / 2]
+    // (no exchange through LDS; the transform ended with a barrier).
+    gptr<const float> sp = (gptr<const float>)spec;   // interleaved (re, im)
+    cf pr[8];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = t + FT * h + 512 * r;
+            const cf p = cmul(v[4 * h + r], cf{sp[2 * j], sp[2 * j + 1]});
+            pr[h + 2 * r] = {p.x, -p.y};
+        }
+#pragma unroll
+    for (int r = 0; r < 8; ++r) v[r] = pr[r];
+    fft2048(v, lds, tw);
+}
+
 template <int FOLD>
 __global__ __launch_bounds__(FT) void k_conv_fft(Tables tb, ConvLaunch cl, int adj, int out, int in, int base,
                                                  double sigma, int gate) {
     __shared__ cf lds[LDS_L];
     __shared__ cf tw[TW_N];
     __shared__ double red[4 * (FT / 64)];
+    __shared__ IdList ids;
     Fold4 f{0.0, 0.0, 0.0, 0.0};
     int bid = (int)blockIdx.x;
     if (FOLD == 0 && cl.pair) {
@@ -198,248 +322,205 @@ __global__ __launch_bounds__(FT) void k_conv_fft(Tables tb, ConvLaunch cl, int a
             base = cl.base2;
         }
     }
-    if (bid >= cl.nftiles) {   // initialisation tiles riding on the launch
-        const VecTile it = cl.init[bid - cl.nftiles];
-        const InstDesc di = tb.inst[it.inst];
-        if (!gate_ok(scal(di), gate)) return;
-        init_tile<float, false>(tb, di, it, adj, out, in, base, sigma, FOLD, cl.fr, cl.fp, cl.fq, f,
-                                FOLD == 1 ? cl.idrows : 0);
-        if (FOLD) fold_partials(cl.part, f, red);
-        return;
-    }
-    const ConvTile tl = cl.ftiles[bid];
-    const InstDesc d = tb.inst[tl.inst];
-    const ConvBlock cb = cl.blocks[tl.blk];   // (loaded beside the instance, ahead of the gate)
-    if (!gate_ok(scal(d), gate)) return;
-    if (FOLD == 2 && (int)blockIdx.x == d.cp0 && threadIdx.x == 0) scal(d)[SC_CGRUN] = (double)cl.fit;
-    int64_t n_out, n_in, off;
-    gptr<float> o;
-    gptr<const float> src;
-    const float2* spec;
-    if (!adj) {
-        n_out = cb.n_in + cb.k - 1;
-        n_in = cb.n_in;
-        off = -(cb.k - 1);
-        spec = (const float2*)cb.s_fwd;
-        o = yvec<float>(d, out) + cb.row0;
-        src = xvec<float>(d, in) + cb.col0;
-    } else {
-        n_out = cb.n_in;
-        n_in = cb.n_in + cb.k - 1;
-        off = 0;
-        spec = (const float2*)cb.s_adj;
-        o = xvec<float>(d, out) + cb.col0;
-        src = yvec<float>(d, in) + cb.row0;
-    }
+    // Workgroups past the transforms write the output elements that no convolution
+    // owns (base and identity blocks alone): an initialisation tile goes through
+    // the same epilogue with no sums.  Element by element, each behind the last
+    // one's loads, such a tile was the longest chain of most launches.
     const int t = threadIdx.x;
-    const int B = FFT_L - (int)cb.k + 1;   // outputs per window
-    const int64_t oa = tl.start;
-    // the pair's inputs as 32-bit offsets q = p (window a) and B + p (window b)
-    // from input position oa + off; valid offsets [qlo, qhi)
-    const int64_t i0 = oa + off;
-    const int qlo = i0 < 0 ? (int)-i0 : 0;
-    const int qhi = n_in - i0 < FFT_L + B ? (int)(n_in - i0) : FFT_L + B;
-    gptr<const float> sw = src + i0;
+    const bool init = bid >= cl.nftiles;
+    const VecTile it = init ? cl.init[bid - cl.nftiles] : VecTile{};
+    const ConvTile tl = init ? ConvTile{it.inst, 0, 0} : cl.ftiles[bid];
+    const InstDesc d = tb.inst[tl.inst];
+    ConvBlock cb{};
+    if (!init) cb = cl.blocks[tl.blk];   // (loaded beside the instance, ahead of the gate)
+    if (!gate_ok(scal(d), gate)) return;
+    if (FOLD == 2 && (int)blockIdx.x == d.cp0 && t == 0) scal(d)[SC_CGRUN] = (double)cl.fit;
+    const int64_t g0 = adj ? cb.col0 : cb.row0, oa = tl.start;
+    const int B = init ? 0 : FFT_L - (int)cb.k + 1;   // outputs per window
+    // the workgroup's outputs: nlim of them from position gw of the output vector
+    const int64_t gw = init ? it.start : g0 + oa;
+    int nlim = it.len;
     cf v[8];
+    if (!init) {
+        const int64_t n_out = adj ? cb.n_in : cb.n_in + cb.k - 1;
+        const int64_t n_in = adj ? cb.n_in + cb.k - 1 : cb.n_in;
+        nlim = n_out - oa < 2 * (int64_t)B ? (int)(n_out - oa) : 2 * B;
+        gptr<const float> src = adj ? yvec<float>(d, in) + cb.row0 : xvec<float>(d, in) + cb.col0;
+        // the pair's inputs as 32-bit offsets q = p (window a) and B + p (window b)
+        // from input position i0; valid offsets [qlo, qhi)
+        const int64_t i0 = adj ? oa : oa - (cb.k - 1);
+        const int qlo = i0 < 0 ? (int)-i0 : 0;
+        const int qhi = n_in - i0 < FFT_L + B ? (int)(n_in - i0) : FFT_L + B;
+        gptr<const float> sw = src + i0;
+        TwRegs twr;
+        twr.load();
+        // (no load behind a branch: at the block's ends positions are clamped to
+        // valid ones, and what was loaded there is dropped)
+        float wa[8], wb[8];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const int p = t + FT * r;
-        v[r] = {(p >= qlo && p < qhi) ? sw[p] : 0.0f, (B + p >= qlo && B + p < qhi) ? sw[B + p] : 0.0f};
-    }
-    fill_twiddles(tw);
-    fft2048(v, lds, tw);
-    // product with conj(DFT(w)), conjugated: the inverse is a forward transform.
-    // The thread holds X[t + 256 (h + 2 r)] in v[4 h + r], which is exactly
-    // the set x[t + 256 r'] the next transform's first stage takes from it:
-    // the products only change register, v'[r'] = p[4 (r' % 2) + r' / 2]
-    // (no exchange through LDS; the transform ended with a barrier).
-    gptr<const float> sp = (gptr<const float>)spec;   // interleaved (re, im)
-    cf pr[8];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = t + FT * h + 512 * r;
-            const cf p = cmul(v[4 * h + r], cf{sp[2 * j], sp[2 * j + 1]});
-            pr[h + 2 * r] = {p.x, -p.y};
+        for (int r = 0; r < 8; ++r) {
+            const int p = t + FT * r;
+            wa[r] = sw[min(max(p, qlo), qhi - 1)];
+            wb[r] = sw[min(max(B + p, qlo), qhi - 1)];
         }
+        if (t < 64) id_list(tb, d, adj, gw, nlim, ids);   // (while the window's loads are in flight)
 #pragma unroll
-    for (int r = 0; r < 8; ++r) v[r] = pr[r];
-    fft2048(v, lds, tw);
-    // conj(result) / L: real part = window a, imaginary part = window b.
-    // Epilogue: every load of the thread's outputs (base, identity blocks,
-    // folded operands) is issued before its first store; element by element
-    // each load would wait for the previous element's stores, since they may
-    // alias as far as the compiler knows.  The additions keep the order of the
-    // element-wise form: (base + identity terms) + sum, then the fold.
-    const double s = sigma * cb.scale / (double)FFT_L;
-    const bool own = (cb.own >> adj) & 1;
-    const int64_t g0 = adj ? cb.col0 : cb.row0;
-    bool id_hit = false;     // an identity block adds to the workgroup's outputs
-    for (int b = d.id0; b < d.id1; ++b) {
-        const IdBlock ib = tb.ids[b];
-        const int64_t r0 = adj ? ib.col0 : ib.row0;
-        id_hit = id_hit || (ib.len > 0 && r0 < g0 + oa + 2 * (int64_t)B && r0 + ib.len > g0 + oa);
+        for (int r = 0; r < 8; ++r) {
+            const int p = t + FT * r;
+            v[r] = {(p >= qlo && p < qhi) ? wa[r] : 0.0f, (B + p >= qlo && B + p < qhi) ? wb[r] : 0.0f};
+        }
+        twr.store(tw);
+        conv_windows(v, lds, tw, adj ? cb.s_adj : cb.s_fwd);
+    } else if (t < 64) {
+        id_list(tb, d, adj, gw, nlim, ids);
     }
-    // Output positions as 32-bit offsets from the pair's first output oa
-    // (window a: j, window b: B + j); offsets below nlim exist.  The block's
-    // outputs start at g0 in the output vector.
-    const int nlim = n_out - oa < 2 * (int64_t)B ? (int)(n_out - oa) : 2 * B;
-    gptr<float> ow = o + oa;
-    if (FOLD == 0 && own && base < 0 && !id_hit) {
-        // nothing to load: the outputs are the sums alone
+    // conj(result) / L: real part = window a, imaginary part = window b.  Output o
+    // (window a: o = j, window b: o = B + j) has position gw + o in the output
+    // vector.  They pass through LDS so that a thread's
+    // epilogue elements are whole aligned 16-byte chunks of the vectors (LDS entry
+    // al + o, the chunk grid's offset al): in the transform's order, 256 apart,
+    // every vector cost 16 four-byte accesses a thread, and the epilogue took half
+    // of a right-hand side launch (14 of 28 thousand cycles).
+    const double s = init ? 0.0 : sigma * cb.scale / (double)FFT_L;
+    const bool own = init || ((cb.own >> adj) & 1);
+    const int al = (int)(gw & 3);
+    float* res = reinterpret_cast<float*>(lds);
+    static_assert(2 * LDS_L >= 2 * FFT_L + 4, "outputs in the transform's LDS");
+    if (!init) {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int j = t + FT * h + 512 * r;
-                if (j >= B) continue;
-                if (j < nlim) ow[j] = (float)(0.0 + s * (double)v[4 * h + r].x);
-                if (B + j < nlim) ow[B + j] = (float)(0.0 + s * -(double)v[4 * h + r].y);
+                if (j < B) {
+                    res[al + j] = v[4 * h + r].x;
+                    res[al + B + j] = -v[4 * h + r].y;
+                }
             }
-        return;
     }
-    constexpr int NE = 16;   // two windows x 8 values
-    // (-1: no output)
-    int li[NE];
-    double res[NE];
+    __syncthreads();
+    const int nid = own ? ids.n + ids.more : 0;   // identity blocks to look at
+    gptr<float> xo = (adj ? xvec<float>(d, out) : yvec<float>(d, out)) + (gw - al);
+    const int kb = own ? base : out;   // what the sums are added to (-1: nothing)
+    gptr<const float> xb = kb >= 0 ? (adj ? xvec<float>(d, kb) : yvec<float>(d, kb)) + (gw - al) : nullptr;
+    gptr<const float> isrc = adj ? yvec<float>(d, in) : xvec<float>(d, in);
+    const int nchunk = (al + nlim + 3) / 4;
+    constexpr int NQ = 4;   // chunks of a thread whose loads are issued together
+    for (int c0 = t; c0 < nchunk; c0 += FT * NQ) {
+        // every load is at a position inside its (padded) vector: chunks past
+        // the last one load the first
+        int o0[NQ];   // the chunk's first output (may be < 0)
+        f32x4 bl[NQ], sv[NQ], kv[NQ], rv[NQ];
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int e = 4 * h + r;
-            const int j = t + FT * h + 512 * r;
-            li[2 * e] = (j < B && j < nlim) ? j : -1;
-            li[2 * e + 1] = (j < B && B + j < nlim) ? B + j : -1;
-            res[2 * e] = (double)v[e].x;
-            res[2 * e + 1] = -(double)v[e].y;
+        for (int q = 0; q < NQ; ++q) {
+            const int c = c0 + FT * q;
+            const int k4 = 4 * (c < nchunk ? c : 0);
+            o0[q] = c < nchunk ? 4 * c - al : nlim;
+            sv[q] = init ? f32x4{0.0f, 0.0f, 0.0f, 0.0f} : *reinterpret_cast<const f32x4*>(res + k4);
+            if (xb != nullptr) bl[q] = *(gptr<const f32x4>)(xb + k4);
+            if (FOLD == 1) kv[q] = *(gptr<const f32x4>)(xvec<float>(d, cl.fq) + (gw - al) + k4);
+            if (FOLD == 2) {
+                kv[q] = cl.fp == kb ? bl[q] : *(gptr<const f32x4>)(xvec<float>(d, cl.fp) + (gw - al) + k4);
+                rv[q] = cl.fr == cl.fp ? kv[q] : *(gptr<const f32x4>)(xvec<float>(d, cl.fr) + (gw - al) + k4);
+            }
         }
-    if (!own) {
-        double old[NE];
+        double bv[NQ][4];   // base + identity blocks, in table order
 #pragma unroll
-        for (int e = 0; e < NE; ++e) old[e] = (double)ow[li[e] >= 0 ? li[e] : 0];
+        for (int q = 0; q < NQ; ++q)
 #pragma unroll
-        for (int e = 0; e < NE; ++e)
-            if (li[e] >= 0) ow[li[e]] = (float)(old[e] + s * res[e]);
-        return;
-    }
-    const int64_t gw = g0 + oa;   // output vector position of offset 0
-    // base + identity blocks of the owned range
-    double bv[NE];
-    float bl[NE];   // the base values as loaded (FOLD 2: the base is p)
-    {
-        // (loads are unconditional, at the pair's first output where the
-        // thread has no output, so that none sits behind a branch)
-        if (base >= 0) {
-            gptr<const float> bp = (adj ? xvec<float>(d, base) : yvec<float>(d, base)) + gw;
-#pragma unroll
-            for (int e = 0; e < NE; ++e) bl[e] = bp[li[e] >= 0 ? li[e] : 0];
-#pragma unroll
-            for (int e = 0; e < NE; ++e) bv[e] = li[e] >= 0 ? (double)bl[e] : 0.0;
-        } else {
-#pragma unroll
-            for (int e = 0; e < NE; ++e) bv[e] = 0.0;
-        }
-        gptr<const float> isrc = adj ? yvec<float>(d, in) : xvec<float>(d, in);
-        for (int b = d.id0; b < d.id1; ++b) {
-            const IdBlock ib = tb.ids[b];
-            const int64_t r0 = adj ? ib.col0 : ib.row0;
-            // blocks that miss the workgroup's outputs [oa, oa + 2B) issue no load
-            if (ib.len <= 0 || r0 >= gw + 2 * (int64_t)B || r0 + ib.len <= gw) continue;
-            const int64_t c0 = adj ? ib.row0 : ib.col0;
+            for (int e = 0; e < 4; ++e) bv[q][e] = xb != nullptr ? (double)bl[q][e] : 0.0;
+        for (int b = 0; b < nid; ++b) {
+            const IdRec ib = ids.at(tb, d, adj, gw, nlim, b);
+            if (ib.lo >= ib.hi) continue;
             const double w = sigma * ib.scale;
-            // the block's rows as offsets, clamped to [0, 2B]
-            const int64_t rl = r0 - gw, rh = r0 + ib.len - gw;
-            const int lo = rl < 0 ? 0 : (int)rl;
-            const int hi = rh > 2 * (int64_t)B ? 2 * B : (int)rh;
-            gptr<const float> iw = isrc + (c0 - r0 + gw);
-            float l[NE];
+            gptr<const float> iw = isrc + ib.off;
+            f32x4 l[NQ];
 #pragma unroll
-            for (int e = 0; e < NE; ++e) {
-                const bool in_r = li[e] >= lo && li[e] < hi;
-                l[e] = in_r ? iw[li[e]] : isrc[c0];
+            for (int q = 0; q < NQ; ++q) l[q] = id_load(iw, o0[q], ib);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (o0[q] + e >= ib.lo && o0[q] + e < ib.hi) bv[q][e] += w * (double)l[q][e];
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            f32x4 val;
+            double g[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                val[e] = (float)(bv[q][e] + s * (double)sv[q][e]);
+                g[e] = (o0[q] + e >= 0 && o0[q] + e < nlim) ? 1.0 : 0.0;   // the output exists
             }
+            const int k4 = o0[q] + al;
+            if (FOLD == 1) {
+                // h = value; r = h - K z (and p = r when fp >= 0) written instead of h
+                f32x4 rr;
 #pragma unroll
-            for (int e = 0; e < NE; ++e)
-                if (li[e] >= lo && li[e] < hi) bv[e] += w * (double)l[e];
+                for (int e = 0; e < 4; ++e) {
+                    const double hd = (double)val[e];
+                    rr[e] = (float)(hd - (double)kv[q][e]);
+                    if (g[e] != 0.0) {
+                        f.a += (double)rr[e] * (double)rr[e];
+                        f.b += hd * hd;
+                    }
+                }
+                out4(xvec<float>(d, cl.fr) + (gw - al) + k4, o0[q], 0, nlim, rr);
+                if (cl.fp >= 0) out4(xvec<float>(d, cl.fp) + (gw - al) + k4, o0[q], 0, nlim, rr);
+                sv[q] = rr;
+            } else {
+                out4(xo + k4, o0[q], 0, nlim, val);
+                if (FOLD == 2) {
+                    // q = value; partials <p, q>, ||r||^2, <r, q>, ||q||^2.  p is the
+                    // launch's base (q = p + A^T A p), already loaded; r is p's vector
+                    // in a step's first iteration (p = r)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const double pd = (double)kv[q][e], rd = (double)rv[q][e], qd = (double)val[e];
+                        if (g[e] == 0.0) continue;
+                        f.a = fma(pd, qd, f.a);
+                        f.b = fma(rd, rd, f.b);
+                        f.c = fma(rd, qd, f.c);
+                        f.d = fma(qd, qd, f.d);
+                    }
+                }
+            }
         }
-    }
-    if (FOLD == 0) {
-#pragma unroll
-        for (int e = 0; e < NE; ++e)
-            if (li[e] >= 0) ow[li[e]] = (float)(bv[e] + s * res[e]);
-        return;
-    }
-    // (a folded launch owns every X element)
-    if (FOLD == 1) {
-        // h = value; r = h - K z (and p = r when fp >= 0) written instead of h
-        gptr<const float> kz = xvec<float>(d, cl.fq) + gw;
-        float kv[NE];
-#pragma unroll
-        for (int e = 0; e < NE; ++e) kv[e] = kz[li[e] >= 0 ? li[e] : 0];
-        gptr<float> rv = xvec<float>(d, cl.fr) + gw;
-        gptr<float> pv = xvec<float>(d, cl.fp >= 0 ? cl.fp : cl.fr) + gw;   // (fp < 0: p is not written)
-        float rrv[NE];
-#pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            rrv[e] = 0.0f;
-            if (li[e] < 0) continue;
-            const float hv = (float)(bv[e] + s * res[e]);
-            const double hd = (double)hv;
-            const float rr = (float)(hd - (double)kv[e]);
-            rrv[e] = rr;
-            rv[li[e]] = rr;
-            if (cl.fp >= 0) pv[li[e]] = rr;
-            f.a += (double)rr * (double)rr;
-            f.b += hd * hd;
-        }
-        if (cl.idrows) {
+        if (FOLD == 1 && cl.idrows) {
             // A p's identity rows for p = r: A's block maps X column col0 + i
             // to Y row row0 + i (ConvLaunch::idrows)
             gptr<float> yt = yvec<float>(d, cl.idrows - 1);
-            for (int b = d.id0; b < d.id1; ++b) {
-                const IdBlock ib = tb.ids[b];
-                const int64_t rl = ib.col0 - gw, rh = ib.col0 + ib.len - gw;
-                if (ib.len <= 0 || rh <= 0 || rl >= 2 * (int64_t)B) continue;
-                const int lo = rl < 0 ? 0 : (int)rl;
-                const int hi = rh > 2 * (int64_t)B ? 2 * B : (int)rh;
-                gptr<float> yw = yt + (ib.row0 - ib.col0 + gw);
+            for (int b = 0; b < nid; ++b) {
+                const IdRec ib = ids.at(tb, d, adj, gw, nlim, b);
+                gptr<float> yw = yt + ib.off;
 #pragma unroll
-                for (int e = 0; e < NE; ++e)
-                    if (li[e] >= lo && li[e] < hi) yw[li[e]] = (float)(0.0 + ib.scale * (double)rrv[e]);
+                for (int q = 0; q < NQ; ++q) {
+                    f32x4 y;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) y[e] = (float)(0.0 + ib.scale * (double)sv[q][e]);
+                    out4u(yw + o0[q], o0[q], ib.lo, ib.hi, y);
+                }
             }
-        }
-    } else {
-        // q = value; partials <p, q>, ||r||^2, <r, q>, ||q||^2.  p is the
-        // launch's base (q = p + A^T A p), already loaded; r is p's vector in
-        // a step's first iteration (p = r)
-        const bool p_base = base == cl.fp, r_p = cl.fr == cl.fp;
-        gptr<const float> pp = xvec<float>(d, cl.fp) + gw;
-        gptr<const float> rp = xvec<float>(d, cl.fr) + gw;
-        float pvv[NE], rvv[NE];
-#pragma unroll
-        for (int e = 0; e < NE; ++e) pvv[e] = p_base ? bl[e] : pp[li[e] >= 0 ? li[e] : 0];
-        if (r_p) {
-#pragma unroll
-            for (int e = 0; e < NE; ++e) rvv[e] = pvv[e];
-        } else {
-#pragma unroll
-            for (int e = 0; e < NE; ++e) rvv[e] = rp[li[e] >= 0 ? li[e] : 0];
-        }
-        gptr<float> qo = xvec<float>(d, out) + gw;
-#pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            if (li[e] < 0) continue;
-            const float q = (float)(bv[e] + s * res[e]);
-            qo[li[e]] = q;
-            const double pd = (double)pvv[e], rd = (double)rvv[e], qd = (double)q;
-            f.a = fma(pd, qd, f.a);
-            f.b = fma(rd, rd, f.b);
-            f.c = fma(rd, qd, f.c);
-            f.d = fma(qd, qd, f.d);
         }
     }
     if (FOLD) fold_partials(cl.part, f, red);
+}
+
+int fft_prepare(hipStream_t st) {
+    static std::mutex mu;
+    static bool done[64] = {};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return fail(CGS_EHIP, "hipGetDevice failed: %s", hipGetErrorString(e));
+    if (dev < 0 || dev >= 64) return fail(CGS_EINVAL, "device %d out of range", dev);
+    std::lock_guard<std::mutex> lock(mu);
+    if (done[dev]) return CGS_OK;
+    k_twiddles<<<1, FT, 0, st>>>();
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return fail(CGS_EHIP, "twiddle table failed: %s", hipGetErrorString(e));
+    done[dev] = true;
+    return CGS_OK;
 }
 
 void launch_conv_spectrum(const void* w, int64_t k, void* spec, hipStream_t st) {

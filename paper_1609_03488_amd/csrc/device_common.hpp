@@ -398,62 +398,21 @@ DEVI double owned_init(const InstDesc& d, const IdBlock* ids, int adj, int in, i
 }
 
 // Initialisation of an apply's output tile: base plus identity blocks, for the
-// elements that no owning convolution writes (the tile's ends are trimmed
-// against owned ranges; an owned range inside the tile is skipped element by
-// element).  Convolution and dense blocks that do not own their range then
-// accumulate into these values.
-// Four partial sums of a CG step folded into an A^T launch.
-struct Fold4 {
-    double a, b, c, d;
-};
-
-// The CG work folded into an A^T launch for X element g whose apply output is
-// v (the arithmetic of k_cg_init and k_cg_dot):
-//   mode 1: h = v; r = h - x_fq (and p = r when fp >= 0) written (not h); a += r^2, b += h^2
-//   mode 2: q = v is written to `out`; a += p q, b += r^2, c += r q, d += q^2
+// tile's elements.  Convolution and dense blocks that do not own their range then
+// accumulate into these values; one that does writes its whole range itself, so
+// with trim the elements of owned ranges are left out (the tile's ends are trimmed
+// against them; an owned range inside the tile is skipped element by element).
+// Initialisation tiles riding on a convolution launch come without them.
 template <typename T>
-DEVI void fold_elem(const Tables& tb, const InstDesc& d, int mode, int fr, int fp, int fq, int out,
-                    int64_t g, double v, Fold4& f, int idrows) {
-    if (mode == 1) {
-        const T h = (T)v;
-        const double hd = (double)h;
-        const T r = (T)(hd - (double)xvec<T>(d, fq)[g]);
-        xvec<T>(d, fr)[g] = r;
-        if (fp >= 0) xvec<T>(d, fp)[g] = r;
-        f.a += (double)r * (double)r;
-        f.b += hd * hd;
-        if (idrows) {
-            // A p's identity rows for p = r (ConvLaunch::idrows)
-            for (int b = d.id0; b < d.id1; ++b) {
-                const IdBlock ib = tb.ids[b];
-                if (g >= ib.col0 && g < ib.col0 + ib.len)
-                    yvec<T>(d, idrows - 1)[ib.row0 + g - ib.col0] = (T)(0.0 + ib.scale * (double)r);
-            }
-        }
-    } else {
-        const T q = (T)v;
-        xvec<T>(d, out)[g] = q;
-        const double pd = (double)xvec<T>(d, fp)[g], rd = (double)xvec<T>(d, fr)[g], qd = (double)q;
-        f.a = fma(pd, qd, f.a);
-        f.b = fma(rd, rd, f.b);
-        f.c = fma(rd, qd, f.c);
-        f.d = fma(qd, qd, f.d);
-    }
-}
-
-// BATCH: loads of several elements in flight (a kernel of its own); without
-// it the element loop, for initialisation tiles riding on long kernels, where
-// the batched loop's code and registers would cost the kernel's main path.
-template <typename T, bool BATCH = true>
 DEVI void init_tile(const Tables& tb, const InstDesc& d, const VecTile& tl, int adj, int out, int in,
-                    int base, double sigma, int fold, int fr, int fp, int fq, Fold4& f, int idrows = 0) {
+                    int base, double sigma, bool trim) {
     gptr<T> o = adj ? xvec<T>(d, out) : yvec<T>(d, out);
     gptr<const T> src = adj ? yvec<T>(d, in) : xvec<T>(d, in);
     gptr<const T> bs = base >= 0 ? (adj ? xvec<T>(d, base) : yvec<T>(d, base)) : nullptr;
     int64_t lo = tl.start, hi = tl.start + tl.len;
     int64_t olo[4], ohi[4];
     int nown = 0;
-    for (int b = d.cb0; b < d.cb1 && nown < 4; ++b) {
+    for (int b = d.cb0; trim && b < d.cb1 && nown < 4; ++b) {
         const ConvBlock cb = tb.cblk[b];
         if (!((cb.own >> adj) & 1)) continue;
         olo[nown] = adj ? cb.col0 : cb.row0;
@@ -475,7 +434,7 @@ DEVI void init_tile(const Tables& tb, const InstDesc& d, const VecTile& tl, int 
     double bw[IB];
     int nb = 0;
     bool many = false;
-    for (int b = d.id0; BATCH && b < d.id1; ++b) {
+    for (int b = d.id0; b < d.id1; ++b) {
         const IdBlock ib = tb.ids[b];
         const int64_t r0 = adj ? ib.col0 : ib.row0;
         if (ib.len <= 0 || r0 >= hi || r0 + ib.len <= lo) continue;
@@ -489,7 +448,7 @@ DEVI void init_tile(const Tables& tb, const InstDesc& d, const VecTile& tl, int 
         bw[nb] = sigma * ib.scale;
         ++nb;
     }
-    if (many || !BATCH) {
+    if (many) {
         for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
             bool owned = false;
             for (int j = 0; j < nown; ++j) owned = owned || (i >= olo[j] && i < ohi[j]);
@@ -501,8 +460,7 @@ DEVI void init_tile(const Tables& tb, const InstDesc& d, const VecTile& tl, int 
                 const int64_t c0 = adj ? ib.row0 : ib.col0;
                 if (i >= r0 && i < r0 + ib.len) v += sigma * ib.scale * (double)src[i - r0 + c0];
             }
-            if (fold) fold_elem<T>(tb, d, fold, fr, fp, fq, out, i, v, f, idrows);
-            else o[i] = (T)v;
+            o[i] = (T)v;
         }
         return;
     }
@@ -535,16 +493,9 @@ DEVI void init_tile(const Tables& tb, const InstDesc& d, const VecTile& tl, int 
 #pragma unroll
             for (int j = 0; j < IB; ++j)
                 if (j < nb && i >= br0[j] && i < bhi[j]) v += bw[j] * (double)sv[j][u];
-            if (fold) fold_elem<T>(tb, d, fold, fr, fp, fq, out, i, v, f, idrows);
-            else o[i] = (T)v;
+            o[i] = (T)v;
         }
     }
-}
-template <typename T>
-DEVI void init_tile(const Tables& tb, const InstDesc& d, const VecTile& tl, int adj, int out, int in,
-                    int base, double sigma) {
-    Fold4 f{0.0, 0.0, 0.0, 0.0};
-    init_tile<T>(tb, d, tl, adj, out, in, base, sigma, 0, 0, 0, 0, f);
 }
 
 // z_y = w_y + A z in working precision, with w_y = u_y + v_s formed as the

@@ -293,6 +293,7 @@ int op_upload(const cgs_op& op, int precision, char* dst, const Staging& stg, hi
             launch_cast(prec, stg.dev + kpad, p, kpad, st);
             p += align256(kpad * sz);
             if (prec == 1 && k <= FFT_KMAX) {   // spectra for the FFT engine
+                CGS_TRY(fft_prepare(st));
                 cb.s_fwd = p;
                 launch_conv_spectrum(cb.w_fwd, k, p, st);
                 p += align256((size_t)FFT_L * 8);
@@ -484,15 +485,22 @@ size_t image_table_bytes(const TableImage& im) {
     for (const auto& v : im.fadj) t += vbytes(v);
     for (const auto& v : im.dfwd) t += vbytes(v);
     for (const auto& v : im.dadj) t += vbytes(v);
-    t += vbytes(im.xt) + vbytes(im.yt);   // initialisation tiles folded into convolution launches
+    // initialisation tiles folded into convolution launches: the tiles outside
+    // owned ranges, and one more piece for a range inside a tile
+    t += vbytes(im.xt) + vbytes(im.yt) + 2 * vbytes(im.cblk);
     return t + 256;
 }
 
+// most workgroups of a folded A^T launch: transforms and initialisation tiles
+static size_t folded_wgs(const TableImage& im) {
+    return (im.fadj.empty() ? 0 : im.fadj[0].size()) + im.xt.size() + im.cblk.size();
+}
+
 size_t image_work_bytes(const TableImage& im) {
-    const size_t nfa = im.fadj.empty() ? 0 : im.fadj[0].size();
+    const size_t nfa = folded_wgs(im);
     return align256(4 * im.xt.size() * 8) + align256(4 * im.yt.size() * 8) +
            align256(2 * im.seg.size() * 8) + align256(im.seg.size() * 4) +
-           2 * align256(4 * (nfa + im.xt.size()) * 8) + align256(4 * (im.xt.size() + im.yt.size()) * 8) +
+           2 * align256(4 * nfa * 8) + align256(4 * (im.xt.size() + im.yt.size()) * 8) +
            align256(im.inst.size() * NSC * 8) + 256;
 }
 
@@ -596,14 +604,25 @@ int Engine::build(const std::vector<InstRec>& r) {
         if (!all) continue;
         for (const VecTile& t : adj ? im.xt : im.yt) {
             const InstDesc& d = im.inst[t.inst];
-            bool covered = false;
-            for (int b = d.cb0; b < d.cb1 && !covered; ++b) {
+            // the pieces of the tile outside every owned range
+            std::vector<std::pair<int64_t, int64_t>> own;
+            for (int b = d.cb0; b < d.cb1; ++b) {
                 const ConvBlock& cb = im.cblk[b];
                 const int64_t lo = adj ? cb.col0 : cb.row0;
-                const int64_t hi = lo + (adj ? cb.n_in : cb.n_in + cb.k - 1);
-                covered = lo <= t.start && t.start + t.len <= hi;
+                own.emplace_back(lo, lo + (adj ? cb.n_in : cb.n_in + cb.k - 1));
             }
-            if (!covered) init_tiles[adj].push_back(t);
+            std::sort(own.begin(), own.end());
+            int64_t pos = t.start;
+            const int64_t end = t.start + t.len;
+            auto piece = [&](int64_t to) {
+                if (to > pos) init_tiles[adj].push_back(VecTile{t.inst, t.seg, pos, (int32_t)(to - pos), 0});
+            };
+            for (const auto& r : own) {
+                if (r.second <= pos || r.first >= end) continue;
+                piece(r.first);
+                pos = std::max(pos, r.second);
+            }
+            piece(end);
         }
         fold_init[adj] = 1;
     }
@@ -744,8 +763,8 @@ int Engine::build(const std::vector<InstRec>& r) {
     T.ypart = (double*)w; w += align256(4 * im.yt.size() * 8);
     T.seg_val = (double*)w; w += align256(2 * im.seg.size() * 8);
     T.seg_cnt = (int*)w; w += align256(im.seg.size() * 4);
-    T.cpart = (double*)w; w += align256(4 * ((im.fadj.empty() ? 0 : im.fadj[0].size()) + im.xt.size()) * 8);
-    T.spart = (double*)w; w += align256(4 * ((im.fadj.empty() ? 0 : im.fadj[0].size()) + im.xt.size()) * 8);
+    T.cpart = (double*)w; w += align256(4 * folded_wgs(im) * 8);
+    T.spart = (double*)w; w += align256(4 * folded_wgs(im) * 8);
     T.tpart = (double*)w; w += align256(4 * (im.xt.size() + im.yt.size()) * 8);
     gather_dev = (double*)w;
     if (!im.seg.empty()) CGS_HIP(hipMemsetAsync(T.seg_cnt, 0, im.seg.size() * 4, stream));

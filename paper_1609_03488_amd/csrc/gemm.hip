@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void k_gemm_pack(Tables tb, int ninst, int adj
         const int t = (int)blockIdx.x - npack;
         const VecTile tl = adj ? tb.xt[t] : tb.yt[t];
         const InstDesc d = tb.inst[tl.inst];
-        if (gate_ok(scal(d), gate)) init_tile<float>(tb, d, tl, adj, out, in, base, sigma);
+        if (gate_ok(scal(d), gate)) init_tile<float>(tb, d, tl, adj, out, in, base, sigma, true);
         return;
     }
     const int b = (int)blockIdx.x / kblocks;

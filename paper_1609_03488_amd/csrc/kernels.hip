@@ -37,7 +37,7 @@ __global__ __launch_bounds__(VEC_NT) void k_apply_init(Tables tb, int adj, int o
     const VecTile tl = adj ? tb.xt[blockIdx.x] : tb.yt[blockIdx.x];
     const InstDesc d = tb.inst[tl.inst];
     if (!gate_ok(scal(d), gate)) return;
-    init_tile<T>(tb, d, tl, adj, out, in, base, sigma);
+    init_tile<T>(tb, d, tl, adj, out, in, base, sigma, true);
 }
 
 // Direct convolution: one wave sums 64 R outputs, lane l the R ones from R l, over
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(CONV_NT) void k_conv(Tables tb, ConvLaunch cl, int 
         it.start += p0;
         it.len = it.len - p0 < len ? it.len - p0 : len;
         const InstDesc di = tb.inst[it.inst];
-        if (gate_ok(scal(di), gate)) init_tile<T>(tb, di, it, adj, out, in, base, sigma);
+        if (gate_ok(scal(di), gate)) init_tile<T>(tb, di, it, adj, out, in, base, sigma, false);
         return;
     }
     const int tix = (int)blockIdx.x / sub;

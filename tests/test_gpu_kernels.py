@@ -42,3 +42,51 @@ def test_direct_convolution_edges(n, k, prec):
     assert np.all(err <= (k + 4) * u * 0.75 * np.convolve(a, np.abs(x)))
     err = np.abs(s.apply(y, transpose=True) - np.correlate(y, at, "valid"))
     assert np.all(err <= (k + 4) * u * 0.75 * np.correlate(np.abs(y), a, "valid"))
+
+
+def _fft_bound(taps, src):
+    """Normwise rounding of the FFT convolution: 12 log2(L) u ||w||_1 sqrt(2) times the
+    largest 2-norm of a window of L = 2048 inputs (two windows share a transform)."""
+    sq = np.concatenate([[0.0], np.cumsum(src * src)])
+    win = np.sqrt(np.max(sq[2048:] - sq[:-2048])) if src.size >= 2048 else np.sqrt(sq[-1])
+    return 12 * 11 * 2.0 ** -24 * np.abs(taps).sum() * np.sqrt(2) * win
+
+
+# the convolution's rows and columns start off the 4-element grid and lie inside vector
+# tiles; identity blocks ahead of, across and past them, several to an output, and (70)
+# more blocks than a workgroup's list of 64; one window pair, its ragged end, several
+@pytest.mark.parametrize("n,k,r0,c0,nid", [(40, 5, 0, 0, 1), (1000, 129, 3, 5, 3), (4061, 34, 1, 2, 3),
+                                           (9000, 1536, 7, 1, 70), (5003, 2, 2, 3, 70)])
+@pytest.mark.parametrize("engine", [0, 2], ids=["direct", "fft"])
+def test_convolution_with_identity_blocks(n, k, r0, c0, nid, engine):
+    """A x and A^T y against NumPy; identity terms and the sum rounded in FP64, so the
+    FP32 error is the convolution's plus (nid + 4) u of the terms."""
+    print("[case] convolution + identity blocks", n, k, r0, c0, nid, engine, flush=True)
+    rng = np.random.default_rng(n * k)
+    taps = rng.standard_normal(k)
+    rows, cols = r0 + n + k - 1 + 9, c0 + n + 6
+    op = P.Operator(rows, cols).add_conv(r0, c0, taps, n, -0.5)
+    ids = [(0, 0, min(rows, cols), 0.25)]
+    for j in range(1, nid):
+        ln = int(rng.integers(1, cols // 2))
+        ids.append((int(rng.integers(0, rows - ln)), int(rng.integers(0, cols - ln)), ln, float(rng.standard_normal())))
+    for b in ids:
+        op.add_identity(*b)
+    s = P.Solver(op, rows, [], P.Settings.make(precision=P.FP32, normalize=0, conv_mfma=engine))
+    u = 2.0 ** -24
+    for adj in (False, True):
+        v = rng.standard_normal(rows if adj else cols).astype(np.float32).astype(np.float64)
+        ref, mag = np.zeros(cols if adj else rows), np.zeros(cols if adj else rows)
+        bound = np.zeros_like(ref)
+        src = v[r0:r0 + n + k - 1] if adj else v[c0:c0 + n]
+        lo, m = (c0, n) if adj else (r0, n + k - 1)
+        conv = (lambda a, w: np.correlate(a, w, "valid")) if adj else np.convolve
+        ref[lo:lo + m] = -0.5 * conv(src, taps)
+        mag[lo:lo + m] = 0.5 * conv(np.abs(src), np.abs(taps))
+        bound[lo:lo + m] = 0.5 * _fft_bound(taps, src) if engine == 2 else k * u * mag[lo:lo + m]
+        for a0, b0, ln, sc in ids:
+            o, i = (b0, a0) if adj else (a0, b0)
+            ref[o:o + ln] += sc * v[i:i + ln]
+            mag[o:o + ln] += abs(sc) * np.abs(v[i:i + ln])
+        err = np.abs(s.apply(v, transpose=adj) - ref)
+        assert np.all(err <= bound + (nid + 4) * u * mag)
