@@ -957,6 +957,7 @@ int cgs_server_create(int64_t max_slots, const cgs_settings* st, void* workspace
     e.stream = (hipStream_t)stream;
     e.st.cg_adaptive = 0;     // results must not depend on the other requests in the mix
     e.st.intervals_per_sync = 1;   // requests arrive and leave at every check
+    e.per_interval = 1;
     e.cg_launch = st->cg_max_iters;
     // tables and reduction scratch: a fixed slice of the workspace
     const size_t tab = cgs::align256(std::max<size_t>(size_t(1) << 20, ws_bytes / 64));

@@ -110,7 +110,8 @@ struct InstDesc {
     int32_t id0, id1;    // identity-block range
     int32_t cb0, cb1;    // convolution-block range (Tables::cblk)
     int32_t db0, db1;    // dense-block range (Tables::dblk)
-    int32_t fused;       // 1: whole ADMM steps run in one workgroup (k_fused)
+    int32_t fused;       // not 0: whole ADMM steps run in one workgroup (k_fused), in its
+                         // general form (1) or its register form (FUSED_REG + variant)
     int32_t pad_;
     // partials of CG steps folded into the A^T convolution launch (Tables::cpart
     // and Tables::spart indices): the instance's transform workgroups [cp0, cp1) and

@@ -48,9 +48,38 @@ DEVI bool gate_ok(gptr<const double> sc, int gate) {
     }
 }
 
+// Lane exchanges of a double on the vector ALU, 32 bits at a time (a shuffle would go
+// through LDS, about 100 cycles each): the value a DPP control brings ...
+template <int C>
+DEVI double dpp_move(double v) {
+    const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
+    const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)x, (int)(unsigned)x, C, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(x >> 32), (int)(x >> 32), C, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+// ... and v plus the value of the lane 32 (H = 32) or 16 (H = 16) away
+template <int H>
+DEVI double swap_add(double v) {
+    const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
+    const unsigned xl = (unsigned)x, xh = (unsigned)(x >> 32);
+    const auto lo = H == 32 ? __builtin_amdgcn_permlane32_swap(xl, xl, false, false)
+                            : __builtin_amdgcn_permlane16_swap(xl, xl, false, false);
+    const auto hi = H == 32 ? __builtin_amdgcn_permlane32_swap(xh, xh, false, false)
+                            : __builtin_amdgcn_permlane16_swap(xh, xh, false, false);
+    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+
+// Sum over the wave, in every lane: pairs 32, 16, 8, 4, 2 and 1 lanes apart in turn.
+// (After each step the value repeats with that period, so a rotation by 4 within a row
+// of 16 lanes brings the pair 4 apart.)
 DEVI double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = swap_add<32>(v);
+    v = swap_add<16>(v);
+    v += dpp_move<0x128>(v);   // row_ror 8
+    v += dpp_move<0x124>(v);   // row_ror 4
+    v += dpp_move<0x4e>(v);    // quad_perm 2, 3, 0, 1
+    v += dpp_move<0xb1>(v);    // quad_perm 1, 0, 3, 2
     return v;
 }
 

@@ -572,6 +572,34 @@ int Engine::init_host_buffers(size_t tab_bytes, int max_inst, int64_t stg_double
     return CGS_OK;
 }
 
+// Variant of the register form of the fused steps (kRegVariants) for an instance, or -1
+// where it takes the general form: one convolution block, no dense block, at most one
+// second-order cone, at most two identity blocks to a row or column, and a size whose
+// outputs, elements and LDS fit.  From the instance's own size only.
+static int fused_reg_variant(const TableImage& im, const InstDesc& d, int prec, int64_t lds) {
+    if (d.cb1 - d.cb0 != 1 || d.db1 != d.db0 || d.sg1 - d.sg0 > 1 || d.id1 - d.id0 > FUSED_REG_IDS) return -1;
+    for (int side = 0; side < 2; ++side) {   // (+1 at a block's start, -1 at its end)
+        std::vector<std::pair<int64_t, int>> ev;
+        for (int b = d.id0; b < d.id1; ++b) {
+            const int64_t lo = side ? im.ids[b].col0 : im.ids[b].row0;
+            ev.emplace_back(lo, 1);
+            ev.emplace_back(lo + im.ids[b].len, -1);
+        }
+        std::sort(ev.begin(), ev.end());
+        int depth = 0;
+        for (const auto& e : ev)
+            if ((depth += e.second) > 2) return -1;
+    }
+    const ConvBlock& cb = im.cblk[d.cb0];
+    const int64_t nt = FUSED_THREADS;
+    for (int v = 0; v < (prec == 0 ? kNumRegVariants - 1 : kNumRegVariants); ++v) {
+        const RegVariant& rv = kRegVariants[v];
+        if (cb.n_in + cb.k - 1 > nt * rv.r || d.n > nt * rv.nx || d.m > nt * rv.ny) continue;
+        return fused_reg_bytes(prec, d.n, d.m, cb, rv.r, false) <= lds ? v : -1;
+    }
+    return -1;
+}
+
 int Engine::build(const std::vector<InstRec>& r) {
     recs = r;
     rounds_since_build = 0;
@@ -587,10 +615,21 @@ int Engine::build(const std::vector<InstRec>& r) {
         d.fused = (st.fused_max > 0 && !use_gemm && d.n + d.m <= lim && dense <= FUSED_DENSE_MAX) ? 1 : 0;
         (d.fused ? n_fused : n_multi) += 1;
     }
-    fused_res = 0;
-    for (const InstDesc& d : im.inst)
-        if (d.fused) fused_res = std::max(fused_res, fused_resident_bytes(prec, d.n, d.m));
-    if (n_fused) fused_prepare();
+    fused_res = fused_reg = 0;
+    fused_general = 0;
+    const int64_t lds = n_fused ? fused_prepare() : 0;
+    for (InstDesc& d : im.inst) {
+        if (!d.fused) continue;
+        const int v = fused_reg_variant(im, d, prec, lds);
+        if (v >= 0) {
+            d.fused = FUSED_REG + v;
+            fused_reg = std::max(fused_reg, std::min(lds, fused_reg_bytes(prec, d.n, d.m, im.cblk[d.cb0],
+                                                                          kRegVariants[v].r, true)));
+        } else {
+            fused_general = 1;
+            fused_res = std::max(fused_res, fused_resident_bytes(prec, d.n, d.m));
+        }
+    }
     // When every convolution owns its output range in a direction, the output
     // initialisation rides on the first convolution launch as extra
     // workgroups (one launch fewer per apply); tiles wholly inside an owned
@@ -949,6 +988,7 @@ void Engine::refresh() {
         // arithmetic (a result must not depend on when the host refreshes)
         FusedArgs fa{};
         fa.refresh = 1;
+        fa.general = 1;   // (in the general form: the two forms' products are the same)
         fa.kc = fused_kc;
         launch_fused(prec, T, fa, stream);
     }
@@ -963,6 +1003,7 @@ void Engine::fused_steps(int nsteps, int check) {
     FusedArgs fa{};
     fa.nsteps = nsteps;
     fa.check = check;
+    fa.check_every = st.check_every;
     fa.alpha = st.alpha;
     fa.eps = st.eps;
     fa.zeta = st.cg_tol;
@@ -972,7 +1013,16 @@ void Engine::fused_steps(int nsteps, int check) {
     fa.max_iters = st.max_iters;
     fa.kc = fused_kc;
     fa.res_want = fused_res;
+    fa.general = fused_general;
+    fa.reg_want = fused_reg;
     launch_fused(prec, T, fa, stream);
+}
+
+// nsteps steps of the fused instances with a test after every check_every of them: one
+// launch where all take the register form, else one per interval
+void Engine::fused_round(int nsteps) {
+    const int per = fused_general ? st.check_every : nsteps;
+    for (int done = 0; done < nsteps; done += per) fused_steps(std::min(per, nsteps - done), 1);
 }
 
 void Engine::steps_with_checks(int nsteps) {
@@ -999,15 +1049,13 @@ int Engine::round(int nsteps, bool multi_only) {
         CGS_HIP(hipStreamWaitEvent(side, ev_fork, 0));
         hipStream_t main_stream = stream;
         stream = side;
-        for (int done = 0; done < nsteps; done += st.check_every)
-            fused_steps(std::min(st.check_every, nsteps - done), 1);
+        fused_round(nsteps);
         stream = main_stream;
         CGS_HIP(hipGetLastError());
         CGS_HIP(hipEventRecord(ev_join, side));
         forked = true;
     } else if (n_fused) {
-        for (int done = 0; done < nsteps; done += st.check_every)
-            fused_steps(std::min(st.check_every, nsteps - done), 1);
+        fused_round(nsteps);
     }
     if (!n_multi) {
         CGS_HIP(hipGetLastError());

@@ -199,7 +199,9 @@ class Engine {
     int n_fused = 0, n_multi = 0;
     int lone = 0;                // a solver with a single instance (fused_lone_max applies)
     int fused_kc = 8;
-    int64_t fused_res = 0;        // LDS bytes of the largest fused instance's resident vectors
+    int64_t fused_res = 0;        // LDS bytes of the largest general fused instance's resident vectors
+    int64_t fused_reg = 0;        // LDS bytes of the largest fused instance of the register form
+    int fused_general = 0;        // some fused instance takes the general form
     // batched BF16 MFMA path for dense blocks shared by every instance
     int use_gemm = 0;
     int gemm_corr = 0;           // 1: add the refinement products (hi x lo)
@@ -252,8 +254,18 @@ class Engine {
     double setup_tol() const { return precision == CGS_FP64 ? std::min(st.setup_tol, 1e-10) : st.setup_tol; }
     void admm_step();
     void fused_steps(int nsteps, int check);
-    // steps of a round: intervals_per_sync check intervals
-    int round_steps() const { return st.check_every * std::max(1, st.intervals_per_sync); }
+    void fused_round(int nsteps);
+    // steps of a round: intervals_per_sync check intervals, or FUSED_INTERVALS where every
+    // instance takes the fused register form: its launch tests and stops inside, and the
+    // host has no decision to take between intervals
+    static constexpr int FUSED_INTERVALS = 16;
+    int round_steps() const {
+        const int iv = n_multi == 0 && !fused_general && fused_reg > 0 && !per_interval
+                           ? std::max(FUSED_INTERVALS, st.intervals_per_sync)
+                           : std::max(1, st.intervals_per_sync);
+        return st.check_every * iv;
+    }
+    int per_interval = 0;   // a server: the host reads every instance's scalars at every check
     // nsteps ADMM steps with the termination test after every check_every of them
     void steps_with_checks(int nsteps);
     void check(int gate = G_CHECK);

@@ -20,7 +20,7 @@
 
 namespace cgs {
 
-constexpr int FNT = 512;   // threads per instance workgroup
+constexpr int FNT = FUSED_THREADS;   // threads per instance workgroup
 constexpr int FU = 2;      // elements per thread whose loads are issued together
 
 // Workgroup sum in a fixed order; every thread receives the result.
@@ -221,13 +221,479 @@ DEVI void f_apply(const Tables& tb, const InstDesc& d, int adj, T* o, const T* s
     }
 }
 
+// The scalars a fused launch leaves (one thread calls these)
+DEVI void record_check(gptr<double> sc, const CheckOut& co) {
+    sc[SC_CUX] = co.cux;
+    sc[SC_BUY] = co.buy;
+    sc[SC_RP] = co.rp;
+    sc[SC_RD] = co.rd;
+    sc[SC_GAP] = co.gap;
+    sc[SC_CX] = co.cx;
+    sc[SC_BY] = co.by;
+}
+DEVI void record_state(gptr<double> sc, const FusedArgs& fa, double tau, double kap, double ut, double iter,
+                       double cgtot, double cgmax, double status) {
+    sc[SC_TAU] = tau;
+    sc[SC_KAPPA] = kap;
+    sc[SC_UT] = ut;
+    sc[SC_ITER] = iter;
+    sc[SC_CGTOT] = cgtot;
+    if (fa.check) {
+        sc[SC_CGMAXLAST] = cgmax;
+        sc[SC_CGMAX] = 0.0;
+    } else {
+        sc[SC_CGMAX] = cgmax;
+    }
+    if (status != 0.0) {
+        sc[SC_STATUS] = status;
+        sc[SC_ACTIVE] = 0.0;
+    }
+}
+
+// ---------------------------------------------------------------- register form
+// The whole-step kernel for the common small instance: one convolution block, no
+// dense block, at most one second-order cone, at most two identity blocks to a row
+// or column (InstDesc::fused = FUSED_REG + variant; the host checks, fused_reg_variant).
+// The general form below is a chain of short passes over vectors in LDS, two barriers
+// and a memory round trip each: 13 barriers per CG iteration, window and taps staged
+// for every product, the blocks' records read again.  Here thread t owns the elements
+// t + FNT j of every vector, as in the general form's passes, and keeps the CG state
+// (z, r, p, K z, A z) of them in registers.  LDS holds only what a product reads across
+// threads: its input, with zeros around it in place of a staged window, and the
+// convolution's sums, which pass to the elements' owners there.  The identity blocks
+// that reach an element are looked up once per launch; the taps are uniform scalar
+// loads.  Six barriers per CG iteration.  A launch may span several check intervals:
+// the test ends an instance inside it.  Arithmetic and order of every sum are those of
+// the general form: identical results.
+
+template <typename T> using cptr = const __attribute__((address_space(4))) T*;
+
+// N sums over the workgroup, each in the order of bsum, with one barrier; sh: two
+// buffers of 6 * FNT / 64, used in turn (a buffer is written again only after the next
+// sum's barrier)
+template <int N>
+DEVI void rsum(double (&s)[N], double* sh, int& turn) {
+    constexpr int NWV = FNT / 64;
+    double* b = sh + turn * 6 * NWV;
+    turn ^= 1;
+    const int w = threadIdx.x >> 6;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const double t = wave_sum(s[j]);
+        if ((threadIdx.x & 63) == 0) b[j * NWV + w] = t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        double r = 0.0;
+#pragma unroll
+        for (int i = 0; i < NWV; ++i) r += b[j * NWV + i];
+        s[j] = r;
+    }
+}
+
+// acc[r] = sum over kpad taps, in order, of w[t] in[r + t] (in: LDS, the thread's first
+// output); eight taps a step, the next step's values and taps fetched ahead of the
+// current one's sums
+template <typename T, int R>
+DEVI void reg_conv(T (&acc)[R], const T* in, cptr<T> w, int kpad) {
+    constexpr int U = 8;
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = T(0);
+    T c[R], xa[U], xb[U], ta[U], te[U];
+    auto fetch = [&](int t, T (&v)[U], T (&tv)[U]) {
+#pragma unroll
+        for (int j = 0; j < U; ++j) v[j] = in[t + R + j];
+#pragma unroll
+        for (int j = 0; j < U; ++j) tv[j] = w[t + j];
+    };
+    auto step = [&](const T (&v)[U], const T (&tv)[U]) {
+#pragma unroll
+        for (int t = 0; t < U; ++t)
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[r] = fma(tv[t], r + t < R ? c[(r + t) % R] : v[(r + t - R + U) % U], acc[r]);
+        T n[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) n[j] = U + j < R ? c[(U + j) % R] : v[(U - R + j + U) % U];
+#pragma unroll
+        for (int j = 0; j < R; ++j) c[j] = n[j];
+    };
+#pragma unroll
+    for (int j = 0; j < R; ++j) c[j] = in[j];
+    const int nu = kpad / U;
+    if (nu > 0) fetch(0, xa, ta);
+    for (int u = 0; u + 1 < nu; u += 2) {
+        fetch((u + 1) * U, xb, te);
+        __builtin_amdgcn_sched_barrier(0);
+        step(xa, ta);
+        fetch((u + 2 < nu ? u + 2 : u) * U, xa, ta);
+        __builtin_amdgcn_sched_barrier(0);
+        step(xb, te);
+    }
+    if (nu & 1) step(xa, ta);
+    for (int t = nu * U; t < kpad; t += 4) {   // (kpad is a multiple of 4)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const T tv = w[t + j];
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[r] = fma(tv, in[t + j + r], acc[r]);
+        }
+    }
+}
+
+// LDS elements: the input of A with k - 1 zeros ahead of it, the input of A^T, both
+// followed by zeros up to where the last wave's outputs read; the convolution's sums;
+// the other columns and rows
+struct RegLds {
+    int xi, yi, cs, xo, yo, total;   // offsets, elements
+};
+__host__ __device__ inline RegLds reg_lds(int n, int m, int n_in, int k, int kpad, int R) {
+    RegLds l;
+    const int no = n_in + k - 1, slack = 64 * R + kpad + 16;
+    l.xi = 0;
+    l.yi = no + slack;
+    l.cs = l.yi + no + slack;
+    l.xo = l.cs + no;
+    l.yo = l.xo + n - n_in;
+    l.total = (l.yo + m - no + 3) & ~3;
+    return l;
+}
+
+// R: convolution outputs per thread; NX, NY: a thread's most elements of an X / Y vector
+template <typename T, int R, int NX, int NY>
+DEVI void fused_reg(const Tables& tb, const FusedArgs& fa, const InstDesc& d, T* lds, double* sh, double* idw) {
+    gptr<double> sc = scal(d);
+    const int tid = threadIdx.x;
+    const ConvBlock& cbr = tb.cblk[d.cb0];
+    const int n = (int)d.n, m = (int)d.m, n_in = (int)cbr.n_in, k = (int)cbr.k, kpad = (int)cbr.kpad;
+    const int col0 = (int)cbr.col0, row0 = (int)cbr.row0, no = n_in + k - 1;
+    const double cscale = cbr.scale;
+    cptr<T> wf = (cptr<T>)cbr.w_fwd, wa = (cptr<T>)cbr.w_adj;
+    const RegLds L = reg_lds(n, m, n_in, k, kpad, R);
+    const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~63) * R;   // the wave's first output
+    // f(slot, index) for the thread's elements.  The thread's number is opaque to the
+    // compiler each time: it would otherwise keep every element's addresses in
+    // registers for the whole launch (and spill).
+    auto opaque_tid = [&]() {
+        int t = tid;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    auto each_x = [&](auto f) {
+        const int t = opaque_tid();
+#pragma unroll
+        for (int q = 0; q < NX; ++q)
+            if (q * FNT < n && t + q * FNT < n) f(q, t + q * FNT);
+    };
+    auto each_y = [&](auto f) {
+        const int t = opaque_tid();
+#pragma unroll
+        for (int q = 0; q < NY; ++q)
+            if (q * FNT < m && t + q * FNT < m) f(q, t + q * FNT);
+    };
+    // LDS offset of an element of a product's input
+    auto x_at = [&](int c) { return c >= col0 && c < col0 + n_in ? L.xi + k - 1 + c - col0 : L.xo + (c < col0 ? c : c - n_in); };
+    auto y_at = [&](int r) { return r >= row0 && r < row0 + no ? L.yi + r - row0 : L.yo + (r < row0 ? r : r - no); };
+
+    for (int i = tid; i < L.total; i += FNT) lds[i] = T(0);
+    // the identity blocks that reach an element, in table order: LDS offset of the
+    // input and block, one word each (-1: none)
+    int xh[NX][2], yh[NY][2];
+#pragma unroll
+    for (int s = 0; s < NX; ++s) xh[s][0] = xh[s][1] = -1;
+#pragma unroll
+    for (int s = 0; s < NY; ++s) yh[s][0] = yh[s][1] = -1;
+    for (int b = d.id0; b < d.id1; ++b) {
+        const IdBlock ib = tb.ids[b];
+        const int r0 = (int)ib.row0, c0 = (int)ib.col0, ln = (int)ib.len, j = b - d.id0;
+        if (tid == 0) idw[j] = ib.scale;
+        each_x([&](int s, int i) {
+            if (i < c0 || i >= c0 + ln) return;
+            const int h = y_at(i - c0 + r0) | (j << 24);
+            if (xh[s][0] < 0) xh[s][0] = h;
+            else xh[s][1] = h;
+        });
+        each_y([&](int s, int i) {
+            if (i < r0 || i >= r0 + ln) return;
+            const int h = x_at(i - r0 + c0) | (j << 24);
+            if (yh[s][0] < 0) yh[s][0] = h;
+            else yh[s][1] = h;
+        });
+    }
+    auto id_add = [&](const int (&h)[2], double sigma, double v) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+            if (h[e] >= 0) v += sigma * idw[h[e] >> 24] * (double)lds[h[e] & 0xffffff];
+        return v;
+    };
+    // the step's vectors, in LDS where they fit (in this order), else in the region
+    T* vec[7];
+    constexpr int kinds[7] = {NXV + YU, NXV + YV, XU, NXV + YG, XG, NXV + YB, XC};
+    int resident = 0;
+    {
+        int64_t at = L.total;
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+            const int v = kinds[j];
+            const int64_t len = ((v < NXV ? n : m) + 3) & ~3;
+            vec[j] = v < NXV ? (T*)xvec<T>(d, v) : (T*)yvec<T>(d, v - NXV);
+            if ((at + len) * (int64_t)sizeof(T) <= fa.lds_reg) {
+                const T* g = vec[j];
+                T* to = lds + at;
+                vec[j] = to;
+                at += len;
+                resident |= 1 << j;
+                if (v < NXV) each_x([&](int, int i) { to[i] = g[i]; });
+                else each_y([&](int, int i) { to[i] = g[i]; });
+            }
+        }
+    }
+    T *uy = vec[0], *vs = vec[1], *ux = vec[2];
+    const T *gy = vec[3], *gx = vec[4], *by = vec[5], *cx = vec[6];
+    T z[NX], kz[NX], rx[NX], px[NX], az[NY], ty[NY];
+    each_x([&](int s, int i) {
+        z[s] = xvec<T>(d, XZ)[i];
+        kz[s] = xvec<T>(d, XK)[i];
+    });
+    each_y([&](int s, int i) { az[s] = yvec<T>(d, YA)[i]; });
+    double tau = sc[SC_TAU], kap = sc[SC_KAPPA], ut = sc[SC_UT];
+    const double eta = sc[SC_ETA], al = fa.alpha;
+    double iter = sc[SC_ITER], cgtot = sc[SC_CGTOT], cgmax = sc[SC_CGMAX];
+    int turn = 0;
+    const bool soc = d.sg1 > d.sg0;
+    const int s0 = soc ? (int)tb.seg[d.sg0].start : m;   // (the cone takes the rows from s0 on)
+    const int l = (int)d.l;
+    __syncthreads();
+
+    // the sums of A (adj = 0) or A^T over the product's input in LDS, into L.cs
+    auto sums = [&](int adj) {
+        const int nout = adj ? n_in : no;
+        if (wave0 < nout) {
+            T acc[R];
+            reg_conv<T, R>(acc, lds + (adj ? L.yi : L.xi) + tid * R, adj ? wa : wf, kpad);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (tid * R + r < nout) lds[L.cs + tid * R + r] = acc[r];
+        }
+        __syncthreads();
+    };
+    // out[s] = identity terms + convolution, for the thread's rows
+    auto apply_a = [&](T (&out)[NY]) {
+        sums(0);
+        each_y([&](int s, int i) {
+            T o = (T)id_add(yh[s], 1.0, 0.0);
+            if (i >= row0 && i < row0 + no) o = (T)((double)o + cscale * (double)lds[L.cs + i - row0]);
+            out[s] = o;
+        });
+    };
+    // out[s] = base(s, i) + sigma (identity terms + convolution), for the thread's columns
+    auto apply_at = [&](T (&out)[NX], double sigma, auto base) {
+        sums(1);
+        const double cs = sigma * cscale;
+        each_x([&](int s, int i) {
+            T o = (T)id_add(xh[s], sigma, base(s, i));
+            if (i >= col0 && i < col0 + n_in) o = (T)((double)o + cs * (double)lds[L.cs + i - col0]);
+            out[s] = o;
+        });
+    };
+
+    double status = 0.0;
+    for (int step = 0; step < fa.nsteps; ++step) {
+        // w_y = u_y + v_s; h = u_x - A^T w_y; r = h - K z, p = r
+        each_y([&](int, int i) { lds[y_at(i)] = (T)((double)uy[i] + (double)vs[i]); });
+        __syncthreads();
+        T q[NX];
+        apply_at(q, -1.0, [&](int, int i) { return (double)ux[i]; });
+        double s2[2] = {0.0, 0.0};   // ||r||^2, ||h||^2
+        each_x([&](int s, int i) {
+            const double hi = (double)q[s];
+            const T ri = (T)(hi - (double)kz[s]);
+            rx[s] = px[s] = ri;
+            lds[x_at(i)] = ri;
+            s2[0] = fma((double)ri, (double)ri, s2[0]);
+            s2[1] = fma(hi, hi, s2[1]);
+        });
+        rsum<2>(s2, sh, turn);
+        double rr = s2[0];
+        double rel = fa.zeta > 0.0 ? fa.zeta / pow(iter + 1.0, fa.rate) : 0.0;
+        rel = rel > fa.floor_ ? rel : fa.floor_;
+        const double tol = sqrt(s2[1]) * rel;
+        int cgit = 0;
+        bool act = fa.cg_max > 0 && std::isfinite(rr) && sqrt(rr) > tol;
+        while (act) {
+            apply_a(ty);   // A p
+            each_y([&](int s, int i) { lds[y_at(i)] = ty[s]; });
+            __syncthreads();
+            apply_at(q, 1.0, [&](int s, int) { return (double)px[s]; });   // q = p + A^T A p
+            double pq[1] = {0.0};
+            each_x([&](int s, int) { pq[0] = fma((double)px[s], (double)q[s], pq[0]); });
+            rsum<1>(pq, sh, turn);
+            const double a = rr / pq[0];
+            if (!(pq[0] > 0.0 && std::isfinite(a))) break;
+            double rn[1] = {0.0};
+            each_x([&](int s, int) {
+                const double qi = (double)q[s];
+                z[s] = (T)fma(a, (double)px[s], (double)z[s]);
+                const T ri = (T)fma(-a, qi, (double)rx[s]);
+                rx[s] = ri;
+                kz[s] = (T)fma(a, qi, (double)kz[s]);
+                rn[0] = fma((double)ri, (double)ri, rn[0]);
+            });
+            each_y([&](int s, int) { az[s] = (T)fma(a, (double)ty[s], (double)az[s]); });
+            rsum<1>(rn, sh, turn);
+            const double be = rr > 0.0 ? rn[0] / rr : 0.0;
+            rr = rn[0];
+            ++cgit;
+            cgtot += 1.0;
+            act = std::isfinite(rr) && sqrt(rr) > tol && cgit < fa.cg_max;
+            if (act) {
+                each_x([&](int s, int i) {
+                    px[s] = (T)fma(be, (double)px[s], (double)rx[s]);
+                    lds[x_at(i)] = px[s];
+                });
+                __syncthreads();
+            }
+        }
+        if (cgit > cgmax) cgmax = cgit;
+        // z_y = w_y + A z; u~_tau = (tau + kappa + c^T z_x + b^T z_y) / eta
+        double s3[2] = {0.0, 0.0};
+        each_x([&](int s, int i) { s3[0] = fma((double)cx[i], (double)z[s], s3[0]); });
+        each_y([&](int s, int i) {
+            ty[s] = z_y<T>(uy[i], vs[i], az[s]);
+            s3[1] = fma((double)by[i], (double)ty[s], s3[1]);
+        });
+        rsum<2>(s3, sh, turn);
+        ut = (tau + kap + s3[0] + s3[1]) / eta;
+        const double ubar = al * ut + (1.0 - al) * tau;
+        const double tnew = ubar - kap > 0.0 ? ubar - kap : 0.0;
+        kap = kap - ubar + tnew;
+        tau = tnew;
+        iter += 1.0;
+        // u_bar_y - v_s; the cone's head and tail norm (the general form sums the tail
+        // from its first entry on, thread (y - s0 - 1) % FNT: the partials change lanes)
+        auto pv_of = [&](int s, int i) {
+            const double ut_y = (double)ty[s] - ut * (double)gy[i];
+            const double ub = al * ut_y + (1.0 - al) * (double)uy[i];
+            return ub - (double)vs[i];
+        };
+        double nz = 0.0, aa = 0.0;
+        int mode = 0;
+        if (soc) {
+            double s4[1] = {0.0};
+            each_y([&](int s, int i) {
+                if (i < s0) return;
+                const double pv = pv_of(s, i);
+                if (i == s0) sh[2 * 6 * (FNT / 64)] = pv;
+                else s4[0] = fma(pv, pv, s4[0]);
+            });
+            sh[2 * 6 * (FNT / 64) + 1 + ((tid - s0 - 1) & (FNT - 1))] = s4[0];
+            __syncthreads();
+            const double t = sh[2 * 6 * (FNT / 64)];
+            s4[0] = sh[2 * 6 * (FNT / 64) + 1 + tid];
+            rsum<1>(s4, sh, turn);
+            nz = sqrt(s4[0]);
+            if (nz <= t) mode = 0;
+            else if (nz <= -t) mode = 1;
+            else {
+                mode = 2;
+                aa = 0.5 * (t + nz);
+            }
+        }
+        // relaxation, projection, dual update
+        each_x([&](int s, int i) {
+            ux[i] = (T)(al * ((double)z[s] - ut * (double)gx[i]) + (1.0 - al) * (double)ux[i]);
+        });
+        each_y([&](int s, int i) {
+            const double pv = pv_of(s, i);
+            double pr;
+            if (i < l) pr = pv > 0.0 ? pv : 0.0;
+            else if (mode == 0) pr = pv;
+            else if (mode == 1) pr = 0.0;
+            else pr = i == s0 ? aa : (aa / nz) * pv;
+            uy[i] = (T)pr;
+            vs[i] = (T)(pr - pv);
+        });
+        if (!fa.check || ((step + 1) % fa.check_every != 0 && step + 1 != fa.nsteps)) continue;
+        // termination test
+        each_x([&](int, int i) { lds[x_at(i)] = ux[i]; });
+        __syncthreads();
+        apply_a(ty);   // A u_x
+        each_y([&](int, int i) { lds[y_at(i)] = uy[i]; });
+        __syncthreads();
+        apply_at(q, 1.0, [](int, int) { return 0.0; });   // A^T u_y
+        double r6[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};   // Y: 0-2, X: 3-5
+        gptr<const T> dr = yvec<T>(d, YD), ec = xvec<T>(d, XE);
+        each_y([&](int s, int i) {
+            const double w = 1.0 / (double)dr[i];
+            const double e = ((double)ty[s] + (double)vs[i]) * w;
+            const double rp = e - tau * (double)by[i] * w;
+            r6[0] = fma(rp, rp, r6[0]);
+            r6[1] = fma(e, e, r6[1]);
+            r6[2] = fma((double)by[i], (double)uy[i], r6[2]);
+        });
+        each_x([&](int s, int i) {
+            const double w = 1.0 / (double)ec[i];
+            const double e = (double)q[s] * w;
+            const double rd = e + tau * (double)cx[i] * w;
+            r6[3] = fma(rd, rd, r6[3]);
+            r6[4] = fma(e, e, r6[4]);
+            r6[5] = fma((double)cx[i], (double)ux[i], r6[5]);
+        });
+        rsum<6>(r6, sh, turn);
+        const CheckOut co = check_outcome(sc, tau, kap, iter, r6[0], r6[1], r6[2], r6[3], r6[4], r6[5], fa.eps,
+                                          fa.max_iters);
+        status = co.status;
+        if (tid == 0) record_check(sc, co);
+        if (status != 0.0) break;
+        // exact recomputation of the carried products of the warm start
+        each_x([&](int s, int i) { lds[x_at(i)] = z[s]; });
+        __syncthreads();
+        apply_a(az);
+        each_y([&](int s, int i) { lds[y_at(i)] = az[s]; });
+        __syncthreads();
+        apply_at(kz, 1.0, [&](int s, int) { return (double)z[s]; });
+        __syncthreads();
+    }
+    each_x([&](int s, int i) {
+        xvec<T>(d, XZ)[i] = z[s];
+        xvec<T>(d, XK)[i] = kz[s];
+        if ((resident >> 2) & 1) xvec<T>(d, XU)[i] = ux[i];
+    });
+    each_y([&](int s, int i) {
+        yvec<T>(d, YA)[i] = az[s];
+        if (resident & 1) yvec<T>(d, YU)[i] = uy[i];
+        if (resident & 2) yvec<T>(d, YV)[i] = vs[i];
+    });
+    if (tid == 0) record_state(sc, fa, tau, kap, ut, iter, cgtot, cgmax, status);
+}
+
 template <typename T>
 __global__ __launch_bounds__(FNT) void k_fused(Tables tb, FusedArgs fa) {
     extern __shared__ __align__(16) unsigned char fsmem[];
-    __shared__ double sh[6 * (FNT / 64)];
+    __shared__ double sh[2 * 6 * (FNT / 64) + 1 + FNT];   // (register form: sums, cone head, tail partials)
+    __shared__ double idw[FUSED_REG_IDS];
     const InstDesc d = tb.inst[blockIdx.x];
     gptr<double> sc = scal(d);
     if (!(sc[SC_ACTIVE] != 0.0 && sc[SC_PHASE] == 2.0)) return;
+    if (d.fused >= FUSED_REG && !fa.refresh) {
+        T* lds = reinterpret_cast<T*>(fsmem);
+        switch (d.fused - FUSED_REG) {
+#define CGS_REG(V) \
+    case V: fused_reg<T, kRegVariants[V].r, kRegVariants[V].nx, kRegVariants[V].ny>(tb, fa, d, lds, sh, idw); break
+            CGS_REG(0);
+            CGS_REG(1);
+            CGS_REG(2);
+            CGS_REG(3);
+            CGS_REG(4);
+            CGS_REG(5);
+            CGS_REG(6);
+#undef CGS_REG
+            default:
+                if constexpr (sizeof(T) == 4)
+                    fused_reg<T, kRegVariants[7].r, kRegVariants[7].nx, kRegVariants[7].ny>(tb, fa, d, lds, sh, idw);
+        }
+        return;
+    }
     FVecs<T> fv;
 #pragma unroll
     for (int k = 0; k < NXV; ++k) fv.x[k] = (T*)xvec<T>(d, k);
@@ -448,15 +914,7 @@ __global__ __launch_bounds__(FNT) void k_fused(Tables tb, FusedArgs fa) {
         const CheckOut co = check_outcome(sc, tau, kap, iter, y0, y1, y2, x0, x1, x2, fa.eps,
                                           fa.max_iters);
         status = co.status;
-        if (tid == 0) {
-            sc[SC_CUX] = co.cux;
-            sc[SC_BUY] = co.buy;
-            sc[SC_RP] = co.rp;
-            sc[SC_RD] = co.rd;
-            sc[SC_GAP] = co.gap;
-            sc[SC_CX] = co.cx;
-            sc[SC_BY] = co.by;
-        }
+        if (tid == 0) record_check(sc, co);
         if (status == 0.0) {
             // exact recomputation of the carried products of the warm start
             f_apply<T>(tb, d, 0, az, zx, nullptr, 1.0, fa.kc, fsmem);
@@ -465,23 +923,14 @@ __global__ __launch_bounds__(FNT) void k_fused(Tables tb, FusedArgs fa) {
     }
     __syncthreads();
     fv_copy<T>(d, fv, false);
-    if (tid == 0) {
-        sc[SC_TAU] = tau;
-        sc[SC_KAPPA] = kap;
-        sc[SC_UT] = ut;
-        sc[SC_ITER] = iter;
-        sc[SC_CGTOT] = cgtot;
-        if (fa.check) {
-            sc[SC_CGMAXLAST] = cgmax;
-            sc[SC_CGMAX] = 0.0;
-        } else {
-            sc[SC_CGMAX] = cgmax;
-        }
-        if (status != 0.0) {
-            sc[SC_STATUS] = status;
-            sc[SC_ACTIVE] = 0.0;
-        }
-    }
+    if (tid == 0) record_state(sc, fa, tau, kap, ut, iter, cgtot, cgmax, status);
+}
+
+int64_t fused_reg_bytes(int prec, int64_t n, int64_t m, const ConvBlock& cb, int R, bool vectors) {
+    const int64_t es = prec == 0 ? 8 : 4;
+    int64_t e = reg_lds((int)n, (int)m, (int)cb.n_in, (int)cb.k, (int)cb.kpad, R).total;
+    if (vectors) e += 3 * ((n + 3) & ~int64_t(3)) + 4 * ((m + 3) & ~int64_t(3));
+    return e * es;
 }
 
 size_t fused_smem_bytes(int prec, int kc) {
@@ -535,8 +984,10 @@ void launch_fused(int prec, const Tables& t, FusedArgs fa, hipStream_t st) {
     const int known = (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) ? g_fused_lds[dev].load() : 0;
     const int cap = known > 0 ? known : 65536 - 1024;
     fa.lds_conv = ((int64_t)fused_smem_bytes(prec, fa.kc) + 15) & ~int64_t(15);
+    if (!fa.general) fa.lds_conv = 0;
     fa.lds_res = std::max<int64_t>(0, std::min<int64_t>(fa.res_want, (int64_t)cap - fa.lds_conv));
-    const size_t lds = (size_t)(fa.lds_conv + fa.lds_res);
+    fa.lds_reg = std::min<int64_t>(std::max(fa.reg_want, fa.lds_conv + fa.lds_res), cap);
+    const size_t lds = (size_t)std::max(fa.lds_conv + fa.lds_res, fa.lds_reg);
     if (prec == 0) k_fused<double><<<t.ninst, FNT, lds, st>>>(t, fa);
     else k_fused<float><<<t.ninst, FNT, lds, st>>>(t, fa);
 }

@@ -181,6 +181,7 @@ void launch_set_scalar(const InstDesc* insts, int inst, int slot, double v, hipS
 struct FusedArgs {
     int nsteps;
     int check;
+    int check_every;   // register form: steps between tests inside a launch (check = 1: and at its end)
     int refresh;     // 1: only recompute the carried A z and (I + A^T A) z, then return
     double alpha, eps, zeta, rate, floor_;
     int cg_max;
@@ -190,7 +191,25 @@ struct FusedArgs {
     // the bytes after it that hold an instance's most used vectors
     int64_t lds_conv, lds_res;
     int64_t res_want;   // bytes those vectors of the largest instance take (0: none)
+    int general;        // some instance takes the general form
+    int64_t reg_want;   // LDS bytes of the largest instance of the register form (0: none)
+    int64_t lds_reg;    // set by launch_fused: LDS bytes an instance of that form may use
 };
+// Register form of the fused steps: InstDesc::fused = FUSED_REG + the variant, which
+// takes r convolution outputs and at most nx / ny elements of an X / Y vector to each
+// of FUSED_THREADS threads (nx = r + 1, ny = 2 r + 1 hold a deconvolution of n <= 512 r,
+// 2 r + 1 and 3 r + 1 a lasso); at most FUSED_REG_IDS identity blocks.  The first
+// variant that holds an instance is its own; the last one is FP32 only (the FP64 state
+// of eight outputs exceeds the registers).
+struct RegVariant {
+    int r, nx, ny;
+};
+constexpr RegVariant kRegVariants[] = {{1, 2, 3}, {1, 3, 4}, {2, 3, 5}, {2, 5, 7},
+                                       {3, 4, 7}, {4, 5, 9}, {4, 9, 13}, {8, 9, 17}};
+constexpr int kNumRegVariants = 8;
+constexpr int FUSED_THREADS = 512, FUSED_REG = 16, FUSED_REG_IDS = 16;
+// LDS bytes an instance needs, with the step's vectors (used where they fit) or without
+int64_t fused_reg_bytes(int prec, int64_t n, int64_t m, const ConvBlock& cb, int R, bool vectors);
 size_t fused_smem_bytes(int prec, int kc);
 // bytes that every resident-vector candidate of an instance with n variables
 // and m rows takes in LDS (16-byte aligned each)

@@ -90,3 +90,56 @@ def test_convolution_with_identity_blocks(n, k, r0, c0, nid, engine):
             mag[o:o + ln] += abs(sc) * np.abs(v[i:i + ln])
         err = np.abs(s.apply(v, transpose=adj) - ref)
         assert np.all(err <= bound + (nid + 4) * u * mag)
+
+
+# sizes at the edges of the fused register form's variants (512 threads times 1, 2, 3, 4
+# or 8 outputs), one element past them, and the general form above the last; a waves' worth
+# and less; kernels shorter and longer than a step of eight taps
+@pytest.mark.parametrize("family,n,k", [("deconv", 20, 3), ("deconv", 482, 31), ("deconv", 483, 31),
+                                        ("deconv", 1000, 25), ("deconv", 1001, 25), ("deconv", 1435, 102),
+                                        ("deconv", 1436, 102), ("deconv", 2040, 9), ("deconv", 2050, 9),
+                                        ("lasso", 500, 13), ("lasso", 505, 13), ("lasso", 1020, 5),
+                                        ("lasso", 1100, 40)])
+def test_fused_register_form_iterates(family, n, k):
+    """FP64, CG to 1e-13: 12 steps (a test inside the launch after 5 and 10) leave the
+    oracle's embedding state to 1e-8, as the one-launch-per-kernel path's test asks."""
+    import oracle as o
+    import workloads as w
+    print("[case] fused register form", family, n, k, flush=True)
+    if family == "deconv":
+        d = w.deconv_instance(n, k, k / 7.0, 0.1, 1e-4, n + k)
+        pr, prog = P.deconv_problem(d["c"], d["b"]), o.deconv_program(d["c"], d["b"])
+    else:
+        d = w.conv_lasso_instance(n, k, k / 5.0, 1e-4, n + k)
+        pr = P.conv_lasso_problem(d["c"], d["b"], d["lam"])
+        prog = o.conv_lasso_program(d["c"], d["b"], d["lam"])
+    st = P.Settings.make(precision=P.FP64, cg_tol=0.0, cg_floor=1e-13, cg_max_iters=60, setup_tol=1e-14,
+                         setup_max_iters=2000, eps=1e-300, max_iters=12, check_every=5, fused_lone_max=0)
+    s = P.Solver(pr.op, pr.l, pr.q, st)
+    s.set_data(0, pr.b, pr.c)
+    info = s.solve()[0]
+    assert info["iters"] == 12 and info["status"] == P.MAX_ITERS
+    ux, uy, tau, vs, kap = s.state(0)
+    rux, ruy, rtau, rvs, rkap = o.scs_solve(prog, eps=1e-300, max_iters=12).u
+    scale = max(1.0, np.abs(rux).max(), np.abs(ruy).max(), np.abs(rvs).max())
+    for a, b in ((ux, rux), (uy, ruy), (vs, rvs)):
+        assert np.abs(a - b).max() <= 1e-8 * scale
+    assert abs(tau - rtau) <= 1e-8 * max(1, rtau) and abs(kap - rkap) <= 1e-8 * max(1, rkap)
+
+
+@pytest.mark.parametrize("n,k", [(300, 31), (1500, 151), (3500, 300), (4000, 97)])
+def test_fused_register_form_fp32_solves(n, k):
+    """FP32 solves in the fused path agree with the one-launch-per-kernel path's, which
+    the oracle's tests cover: the natural objectives, FP64 on the host, to 1e-4."""
+    import oracle as o
+    import workloads as w
+    print("[case] fused register form fp32", n, k, flush=True)
+    d = w.deconv_instance(n, k, k / 7.0, 0.05, 1e-4, n)
+    pr = P.deconv_problem(d["c"], d["b"])
+    f = []
+    for fused in (0, 65536):
+        s = P.Solver(pr.op, pr.l, pr.q, P.Settings.make(eps=1e-4, fused_max=fused, fused_lone_max=0))
+        s.set_data(0, pr.b, pr.c)
+        assert s.solve()[0]["status"] == P.SOLVED
+        f.append(o.deconv_objective(d["c"], d["b"], s.solution(0)[0][:n]))
+    assert abs(f[0] - f[1]) <= 1e-4 * f[0]
