@@ -305,6 +305,24 @@ void cgs_settings_default(cgs_settings* st) {
 // the data scales sb, sc.
 static int upload_instance_data(cgs::Engine& e, const cgs::Scaling& scl, char* base, int64_t n,
                                 int64_t m, const double* b, const double* c) {
+    const int64_t nxs = cgs::round_up(n, cgs::XY_ALIGN), nys = cgs::round_up(m, cgs::XY_ALIGN);
+    double sc2[2];
+    const int64_t total = 2 * (n + m) + 2;
+    if (total <= std::max(e.stg.cap, e.stg.host_cap)) {
+        // scaled straight into the staging buffer: one copy (none where the device
+        // buffer is too small: the kernel reads the pinned one), one launch, one wait
+        double *bh = e.stg.host, *dv = bh + m, *ch = dv + m, *ev = ch + n;
+        cgs::scale_data(scl, m, n, b, c, dv, ev, bh, ch, &sc2[0], &sc2[1]);
+        ev[n] = sc2[0];
+        ev[n + 1] = sc2[1];
+        if (total <= e.stg.cap)
+            CGS_HIP(hipMemcpyAsync(e.stg.dev, e.stg.host, (size_t)total * sizeof(double), hipMemcpyHostToDevice,
+                                   e.stream));
+        cgs::launch_put_data(e.prec, total <= e.stg.cap ? e.stg.dev : e.stg.host, base, n, m, nxs, nys, e.stream);
+        CGS_HIP(hipGetLastError());
+        CGS_HIP(hipStreamSynchronize(e.stream));
+        return CGS_OK;
+    }
     std::vector<double> dv, ev, bh, ch;
     try {
         dv.resize((size_t)m); bh.resize((size_t)m);
@@ -312,10 +330,8 @@ static int upload_instance_data(cgs::Engine& e, const cgs::Scaling& scl, char* b
     } catch (...) {
         return fail(CGS_ENOMEM, "host allocation failed");
     }
-    double sc2[2];
     cgs::scale_data(scl, m, n, b, c, dv.data(), ev.data(), bh.data(), ch.data(), &sc2[0], &sc2[1]);
     const size_t sz = cgs::elem_bytes(e.precision);
-    const int64_t nxs = cgs::round_up(n, cgs::XY_ALIGN), nys = cgs::round_up(m, cgs::XY_ALIGN);
     auto xv = [&](int k) { return base + cgs::REGION_HDR + (size_t)k * nxs * sz; };
     auto yv = [&](int k) { return base + cgs::REGION_HDR + ((size_t)cgs::NXV * nxs + (size_t)k * nys) * sz; };
     CGS_TRY(cgs::upload_f64(e.stg, e.stream, bh.data(), m, e.prec, yv(cgs::YB)));
@@ -368,7 +384,9 @@ int cgs::solver_create(const cgs_op* op, int64_t l, const int64_t* q, int64_t nq
     char* p = (char*)workspace;
     e.tab_dev = p; e.tab_cap = L.tab; p += L.tab;
     e.work_dev = p; e.work_cap = L.work; p += L.work;
-    CGS_TRY(e.init_host_buffers(L.tab, (int)batch, L.stg_doubles));
+    // (a point, and an instance's data, of up to 2^20 doubles cross in one piece)
+    const int64_t piece = 2 * (op->n + op->m) + 2;
+    CGS_TRY(e.init_host_buffers(L.tab, (int)batch, L.stg_doubles, piece <= (int64_t(1) << 20) ? piece : 0));
     e.stg.dev = (double*)p; p += L.stg;
     char* opdata = p; p += L.opb;
     if (st->precision == CGS_BF16 && L.part > 0) {
@@ -807,21 +825,7 @@ int cgs_solver_rounds(cgs_solver* s, int64_t* rounds, int64_t* reruns) {
 int cgs_solver_get_solution(cgs_solver* s, int64_t inst, double* x, double* y, double* sl) {
     if (!s) return fail(CGS_EINVAL, "solver is null");
     if (inst < 0 || inst >= s->batch) return fail(CGS_ENOTFOUND, "instance %lld", (long long)inst);
-    cgs::Engine& e = s->eng;
-    double* outs[3] = {x, y, sl};
-    const int64_t lens[3] = {s->n, s->m, s->m};
-    for (int w = 0; w < 3; ++w) {
-        if (!outs[w]) continue;
-        for (int64_t off = 0; off < lens[w]; off += e.stg.cap) {
-            const int64_t c = std::min(e.stg.cap, lens[w] - off);
-            cgs::launch_extract(e.prec, e.inst_dev, (int)inst, w, off, c, e.stg.dev, e.stream);
-            CGS_HIP(hipGetLastError());
-            CGS_HIP(hipMemcpyAsync(e.stg.host, e.stg.dev, c * sizeof(double), hipMemcpyDeviceToHost, e.stream));
-            CGS_HIP(hipStreamSynchronize(e.stream));
-            std::memcpy(outs[w] + off, e.stg.host, c * sizeof(double));
-        }
-    }
-    return CGS_OK;
+    return s->eng.get_point((int)inst, x, y, sl);
 }
 
 int cgs_solver_get_state(cgs_solver* s, int64_t inst, double* ux, double* uy, double* vs, double* scal) {
@@ -911,15 +915,14 @@ int cgs_solver_normal_solve(cgs_solver* s, const double* rhs, const double* z0, 
     e.apply(1, cgs::XQ, cgs::YT, cgs::XZ, 1.0, cgs::G_ALL);
     cgs::launch_cg_init(e.prec, e.T, cgs::XZ, cgs::XR, cgs::XP, cgs::XQ, cgs::XH, 1, 0.0, 0.0, tol,
                         max_iters, cgs::G_ALL, e.stream);
-    int done = 0;
-    while (done < max_iters) {
+    if (max_iters == 0) CGS_TRY(e.fetch_scalars());
+    for (int done = 0; done < max_iters;) {
         const int nb = std::min(8, max_iters - done);
         for (int j = 0; j < nb; ++j) e.cg_iter(cgs::XZ, cgs::G_ANY_CG, max_iters, 0, done + j);
         done += nb;
         CGS_TRY(e.fetch_scalars());
         if (e.scalars(0)[cgs::SC_CGACT] == 0.0) break;
     }
-    CGS_TRY(e.fetch_scalars());
     if (iters) *iters = (int32_t)e.scalars(0)[cgs::SC_CGIT];
     CGS_TRY(cgs::download_f64(e.stg, e.stream, e.prec, e.xptr(0, cgs::XZ), s->n, z));
     return CGS_OK;
@@ -970,7 +973,7 @@ int cgs_server_create(int64_t max_slots, const cgs_settings* st, void* workspace
     e.tab_dev = p; e.tab_cap = tab; p += tab;
     e.work_dev = p; e.work_cap = work; p += work;
     e.stg.dev = (double*)p; p += stg;
-    CGS_TRY(e.init_host_buffers(tab, (int)max_slots, sv->stg_doubles));
+    CGS_TRY(e.init_host_buffers(tab, (int)max_slots, sv->stg_doubles, 0));
     sv->arena = p;
     sv->arena_bytes = ws_bytes - (size_t)(p - (char*)workspace);
     sv->arena_bytes &= ~size_t(255);
@@ -1166,19 +1169,7 @@ int cgs_server_fetch(cgs_server* sv, int64_t ticket, double* x, double* y, doubl
     if (!r.finished || r.eng_index < 0) return fail(CGS_ESTATE, "ticket %lld is still running", (long long)ticket);
     cgs::Engine& e = sv->eng;
     const int ei = r.eng_index;   // finished requests keep their slot in the current tables
-    double* outs[3] = {x, y, sl};
-    const int64_t lens[3] = {r.n, r.m, r.m};
-    for (int w = 0; w < 3; ++w) {
-        if (!outs[w]) continue;
-        for (int64_t off = 0; off < lens[w]; off += e.stg.cap) {
-            const int64_t c = std::min(e.stg.cap, lens[w] - off);
-            cgs::launch_extract(e.prec, e.inst_dev, ei, w, off, c, e.stg.dev, e.stream);
-            CGS_HIP(hipGetLastError());
-            CGS_HIP(hipMemcpyAsync(e.stg.host, e.stg.dev, c * sizeof(double), hipMemcpyDeviceToHost, e.stream));
-            CGS_HIP(hipStreamSynchronize(e.stream));
-            std::memcpy(outs[w] + off, e.stg.host, c * sizeof(double));
-        }
-    }
+    CGS_TRY(e.get_point(ei, x, y, sl));
     if (info) *info = r.info;
     return cgs_server_cancel(sv, ticket);
 }

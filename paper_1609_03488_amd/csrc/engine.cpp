@@ -547,10 +547,11 @@ void Engine::adapt_cg() {
     cg_launch = std::max(1, std::min(st.cg_max_iters, (int)need));
 }
 
-int Engine::init_host_buffers(size_t tab_bytes, int max_inst, int64_t stg_doubles) {
+int Engine::init_host_buffers(size_t tab_bytes, int max_inst, int64_t stg_doubles, int64_t host_doubles) {
     const size_t tb = std::max<size_t>(tab_bytes, 256);
     const size_t sb = std::max<size_t>(1, (size_t)max_inst) * NSC * sizeof(double);
-    const size_t gb = (size_t)stg_doubles * sizeof(double);
+    if (pageable || host_doubles < stg_doubles) host_doubles = stg_doubles;
+    const size_t gb = (size_t)host_doubles * sizeof(double);
     if (pageable) {
         const size_t tw = (tb + 7) / 8, sw = sb / 8, gw = gb / 8;
         try {
@@ -569,6 +570,7 @@ int Engine::init_host_buffers(size_t tab_bytes, int max_inst, int64_t stg_double
     tab_host_cap = tab_bytes;
     scal_host_cap = max_inst;
     stg.cap = stg_doubles;
+    stg.host_cap = pageable ? 0 : host_doubles;
     return CGS_OK;
 }
 
@@ -1142,11 +1144,45 @@ int Engine::rollback() {
 }
 
 int Engine::fetch_scalars() {
-    launch_gather_scalars(inst_dev, T.ninst, gather_dev, stream);
+    // (pinned memory takes the kernel's stores: no copy behind it)
+    launch_gather_scalars(inst_dev, T.ninst, pageable ? gather_dev : scal_host, stream);
     CGS_HIP(hipGetLastError());
-    CGS_HIP(hipMemcpyAsync(scal_host, gather_dev, (size_t)T.ninst * NSC * sizeof(double),
-                           hipMemcpyDeviceToHost, stream));
+    if (pageable)
+        CGS_HIP(hipMemcpyAsync(scal_host, gather_dev, (size_t)T.ninst * NSC * sizeof(double),
+                               hipMemcpyDeviceToHost, stream));
     CGS_HIP(hipStreamSynchronize(stream));
+    return CGS_OK;
+}
+
+int Engine::get_point(int i, double* x, double* y, double* sl) {
+    const int64_t n = im.inst[(size_t)i].n, m = im.inst[(size_t)i].m;
+    double* outs[3] = {x, y, sl};
+    const int64_t lens[3] = {n, m, m};
+    if (n + 2 * m <= std::max(stg.cap, stg.host_cap)) {
+        // one launch, one wait (a copy and a wait for each vector took 75 us)
+        const bool direct = stg.host_cap > 0;
+        launch_extract_point(prec, inst_dev, i, n, m, direct ? stg.host : stg.dev, stream);
+        CGS_HIP(hipGetLastError());
+        if (!direct)
+            CGS_HIP(hipMemcpyAsync(stg.host, stg.dev, (size_t)(n + 2 * m) * sizeof(double), hipMemcpyDeviceToHost,
+                                   stream));
+        CGS_HIP(hipStreamSynchronize(stream));
+        const double* h = stg.host;
+        for (int w = 0; w < 3; h += lens[w], ++w)
+            if (outs[w]) std::memcpy(outs[w], h, (size_t)lens[w] * sizeof(double));
+        return CGS_OK;
+    }
+    for (int w = 0; w < 3; ++w) {
+        if (!outs[w]) continue;
+        for (int64_t off = 0; off < lens[w]; off += stg.cap) {
+            const int64_t c = std::min(stg.cap, lens[w] - off);
+            launch_extract(prec, inst_dev, i, w, off, c, stg.dev, stream);
+            CGS_HIP(hipGetLastError());
+            CGS_HIP(hipMemcpyAsync(stg.host, stg.dev, (size_t)c * sizeof(double), hipMemcpyDeviceToHost, stream));
+            CGS_HIP(hipStreamSynchronize(stream));
+            std::memcpy(outs[w] + off, stg.host, (size_t)c * sizeof(double));
+        }
+    }
     return CGS_OK;
 }
 

@@ -78,6 +78,8 @@ struct Staging {
     double* dev = nullptr;
     double* host = nullptr;
     int64_t cap = 0;
+    int64_t host_cap = 0;   // doubles of `host` (>= cap) a kernel may read or write in place
+                            // (pinned memory), 0 for a pageable buffer
 };
 int64_t staging_doubles(const cgs_op& op, int64_t max_vec);
 
@@ -230,7 +232,8 @@ class Engine {
     int rounds_since_build = 0;   // a graph is captured only once the tables have held a round
 
     ~Engine();
-    int init_host_buffers(size_t tab_bytes, int max_inst, int64_t stg_doubles);
+    // host_doubles: doubles of the pinned staging buffer (at least stg_doubles)
+    int init_host_buffers(size_t tab_bytes, int max_inst, int64_t stg_doubles, int64_t host_doubles);
     // Build and upload the tile tables of `recs`.
     int build(const std::vector<InstRec>& r);
     void drop_graph();
@@ -284,6 +287,8 @@ class Engine {
     bool truncated() const;
     // restore the snapshot of that round and run it again with more launches
     int rollback();
+    // x, y, s of an instance's point as FP64 host arrays (null: not wanted; synchronises)
+    int get_point(int i, double* x, double* y, double* sl);
     int fetch_scalars();          // gather per-instance scalars into scal_host (synchronises)
     const double* scalars(int i) const { return scal_host + (size_t)i * NSC; }
     int reset(int inst);          // inst < 0: all

@@ -16,6 +16,7 @@
 //    the method (tau, kappa, eta, CG alpha/beta, norms, residuals) is FP64.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 #include <utility>
 #include <vector>
@@ -1012,19 +1013,17 @@ __global__ __launch_bounds__(VEC_NT) void k_snapshot(Tables tb, int restore) {
 // -c^T x_ray or -b^T y_ray for certificates) or the raw iterate (3: u_x,
 // 4: u_y, 5: v_s) of the scaled problem.
 template <typename T>
-__global__ void k_extract(const InstDesc* insts, int inst, int what, int64_t off, int64_t len,
-                          double* out) {
-    const InstDesc d = insts[inst];
-    gptr<const double> sc = scal(d);
-    const double status = sc[SC_STATUS];
-    double scale = 1.0;
-    gptr<const T> v;
-    gptr<const T> w = nullptr;
-    bool divide = false;
-    if (what == 0 || what == 3) v = xvec<T>(d, XU);
-    else if (what == 1 || what == 4) v = yvec<T>(d, YU);
-    else v = yvec<T>(d, YV);
-    if (what <= 2) {
+struct Extract {
+    gptr<const T> v, w;
+    double scale;
+    bool divide;
+    DEVI Extract(const InstDesc& d, int what) : w(nullptr), scale(1.0), divide(false) {
+        gptr<const double> sc = scal(d);
+        const double status = sc[SC_STATUS];
+        if (what == 0 || what == 3) v = xvec<T>(d, XU);
+        else if (what == 1 || what == 4) v = yvec<T>(d, YU);
+        else v = yvec<T>(d, YV);
+        if (what > 2) return;
         double ray = sc[SC_TAU];   // x = x_ray / tau, ...
         if (status == 3.0) ray = (what == 1) ? -sc[SC_BUY] : NAN;
         else if (status == 4.0) ray = (what == 1) ? NAN : -sc[SC_CUX];
@@ -1040,12 +1039,49 @@ __global__ void k_extract(const InstDesc* insts, int inst, int what, int64_t off
             scale = 1.0 / (sc[SC_SB] * ray);
         }
     }
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < len;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        double e = (double)v[off + i];
-        if (w) e = divide ? e / (double)w[off + i] : e * (double)w[off + i];
-        out[i] = e * scale;
+    DEVI double at(int64_t i) const {
+        double e = (double)v[i];
+        if (w) e = divide ? e / (double)w[i] : e * (double)w[i];
+        return e * scale;
     }
+};
+template <typename T>
+__global__ void k_extract(const InstDesc* insts, int inst, int what, int64_t off, int64_t len,
+                          double* out) {
+    const Extract<T> x(insts[inst], what);
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < len;
+         i += (int64_t)gridDim.x * blockDim.x)
+        out[i] = x.at(off + i);
+}
+// x, y and s of an instance one after the other (gridDim.y = 3)
+template <typename T>
+__global__ void k_extract_point(const InstDesc* insts, int inst, double* out) {
+    const InstDesc d = insts[inst];
+    const Extract<T> x(d, blockIdx.y);
+    const int64_t len = blockIdx.y == 0 ? d.n : d.m;
+    double* o = out + (blockIdx.y == 0 ? 0 : d.n + (blockIdx.y - 1) * d.m);
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < len;
+         i += (int64_t)gridDim.x * blockDim.x)
+        o[i] = x.at(i);
+}
+// an instance's scaled data, FP64 [b^ (m) | D (m) | c^ (n) | E (n) | sb, sc], into its region
+template <typename T>
+__global__ void k_put_data(const double* src, char* base, int64_t n, int64_t m, int64_t nxs, int64_t nys) {
+    InstDesc d{};
+    d.base = base;
+    d.nxs = nxs;
+    d.nys = nys;
+    const int64_t total = 2 * (n + m);
+    gptr<T> b = yvec<T>(d, YB), dr = yvec<T>(d, YD), c = xvec<T>(d, XC), e = xvec<T>(d, XE);
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const T v = (T)src[i];
+        if (i < m) b[i] = v;
+        else if (i < 2 * m) dr[i - m] = v;
+        else if (i < 2 * m + n) c[i - 2 * m] = v;
+        else e[i - 2 * m - n] = v;
+    }
+    if (blockIdx.x == 0 && threadIdx.x < 2) scal(d)[threadIdx.x == 0 ? SC_SB : SC_SC] = src[total + threadIdx.x];
 }
 
 template <typename T>
@@ -1226,6 +1262,16 @@ void launch_extract(int prec, const InstDesc* inst_dev, int inst, int what, int6
                     int64_t len, double* out64, hipStream_t st) {
     CGS_DISPATCH(prec, k_extract, flat_grid(len, 256), 256, st, inst_dev, inst, what, off, len,
                  out64);
+}
+void launch_extract_point(int prec, const InstDesc* inst_dev, int inst, int64_t n, int64_t m, double* out,
+                          hipStream_t st) {
+    const dim3 g((unsigned)flat_grid(std::max(n, m), 256), 3);
+    if (prec == 0) k_extract_point<double><<<g, 256, 0, st>>>(inst_dev, inst, out);
+    else k_extract_point<float><<<g, 256, 0, st>>>(inst_dev, inst, out);
+}
+void launch_put_data(int prec, const double* src, char* base, int64_t n, int64_t m, int64_t nxs, int64_t nys,
+                     hipStream_t st) {
+    CGS_DISPATCH(prec, k_put_data, flat_grid(2 * (n + m), 256), 256, st, src, base, n, m, nxs, nys);
 }
 void launch_cast(int prec, const double* src, void* dst, int64_t n, hipStream_t st) {
     if (n <= 0) return;
