@@ -480,8 +480,8 @@ int cgs_solver_kernel_time(cgs_solver* s, int32_t kernel, int32_t reps, double* 
                         ++launches;
             } else {
                 for (const auto& d : dl)
-                    cgs::launch_gemv(e.prec, e.T, d, adj, adj ? cgs::XT : cgs::YT, adj ? cgs::YU : cgs::XU,
-                                     1.0, cgs::G_ALL, e.stream), ++launches;
+                    cgs::launch_gemv(e.prec, e.T, d, adj, adj ? cgs::XT : cgs::YT, adj ? cgs::YU : cgs::XU, -1,
+                                     1.0, cgs::G_ALL, 0, e.stream), ++launches;
             }
         } else {
             e.apply(0, cgs::YT, cgs::XP, -1, 1.0, cgs::G_ALL);

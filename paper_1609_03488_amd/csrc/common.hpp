@@ -184,6 +184,10 @@ struct DenseBlock {      // rows x cols block
     const void* a16lo;   // BF16 rounding of the remainder a - a16 (refinement products)
     const void* at16lo;
     double scale;
+    // bit 0 (A x) / bit 1 (A^T y): no other dense or convolution block writes into this
+    // block's output range
+    int32_t own;
+    int32_t pad_;
 };
 
 struct DenseTile {       // `nr` rows of the (possibly transposed) block from r0
@@ -225,7 +229,9 @@ constexpr int CONV_KC_MAX_F32 = 2048;  // taps staged per pass by k_fused
 constexpr int CONV_KC_MAX_F64 = 1024;
 constexpr int CONV_R_F32 = 8;        // taps are padded to a multiple of this
 constexpr int CONV_R_F64 = 4;
-constexpr int DENSE_ROWS = 4;        // rows per dense-GEMV tile
+// rows per tile of the dense products: a block's rows over 1024 workgroups (four to a
+// CU, each streaming its rows), at most DENSE_ROWS_MAX
+constexpr int DENSE_TILES = 1024, DENSE_ROWS_MAX = 16;
 constexpr int FFT_L = 2048;          // points per transform of the FFT convolution engine
 constexpr int FFT_KMAX = 1536;       // longest kernel it takes (>= 513 outputs per window)
 

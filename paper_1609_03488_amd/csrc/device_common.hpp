@@ -432,7 +432,7 @@ DEVI double owned_init(const InstDesc& d, const IdBlock* ids, int adj, int in, i
 // with trim the elements of owned ranges are left out (the tile's ends are trimmed
 // against them; an owned range inside the tile is skipped element by element).
 // Initialisation tiles riding on a convolution launch come without them.
-template <typename T>
+template <typename T, int U = 8>
 DEVI void init_tile(const Tables& tb, const InstDesc& d, const VecTile& tl, int adj, int out, int in,
                     int base, double sigma, bool trim) {
     gptr<T> o = adj ? xvec<T>(d, out) : yvec<T>(d, out);
@@ -458,7 +458,7 @@ DEVI void init_tile(const Tables& tb, const InstDesc& d, const VecTile& tl, int 
     // element, every load would wait for the previous element's store.  The
     // additions keep the order of the plain form, base first, then the blocks
     // in table order.
-    constexpr int IB = 4, U = 8;
+    constexpr int IB = 4;
     int64_t br0[IB], bc0[IB], bhi[IB];
     double bw[IB];
     int nb = 0;

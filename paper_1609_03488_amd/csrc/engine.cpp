@@ -267,6 +267,21 @@ void op_dev_shape(const cgs_op& op, int precision, OpDev* out, const double* mul
         }
         c.own = (fwd ? 1 : 0) | (adj ? 2 : 0);
     }
+    for (size_t i = 0; i < out->dense.size(); ++i) {
+        DenseBlock& b = out->dense[i];
+        bool fwd = true, adj = true;
+        for (size_t j = 0; j < out->dense.size(); ++j) {
+            if (j == i) continue;
+            const DenseBlock& o = out->dense[j];
+            if (overlap(b.row0, b.row0 + b.rows, o.row0, o.row0 + o.rows)) fwd = false;
+            if (overlap(b.col0, b.col0 + b.cols, o.col0, o.col0 + o.cols)) adj = false;
+        }
+        for (const ConvBlock& o : out->convs) {
+            if (overlap(b.row0, b.row0 + b.rows, o.row0, o.row0 + o.n_in + o.k - 1)) fwd = false;
+            if (overlap(b.col0, b.col0 + b.cols, o.col0, o.col0 + o.n_in)) adj = false;
+        }
+        b.own = (fwd ? 1 : 0) | (adj ? 2 : 0);
+    }
 }
 
 int op_upload(const cgs_op& op, int precision, char* dst, const Staging& stg, hipStream_t st,
@@ -464,10 +479,12 @@ void build_image(const std::vector<InstRec>& recs, int precision, TableImage& im
             const DenseBlock& db = r.op->dense[j];
             const int32_t bi = (int32_t)im.dblk.size();
             im.dblk.push_back(db);
-            for (int64_t s = 0; s < db.rows; s += DENSE_ROWS)
-                im.dfwd[j].push_back(DenseTile{ii, bi, s, (int32_t)std::min<int64_t>(DENSE_ROWS, db.rows - s), 0});
-            for (int64_t s = 0; s < db.cols; s += DENSE_ROWS)
-                im.dadj[j].push_back(DenseTile{ii, bi, s, (int32_t)std::min<int64_t>(DENSE_ROWS, db.cols - s), 0});
+            for (int adj = 0; adj < 2; ++adj) {
+                const int64_t rows = adj ? db.cols : db.rows;
+                const int64_t nr = std::min<int64_t>(DENSE_ROWS_MAX, (rows + DENSE_TILES - 1) / DENSE_TILES);
+                for (int64_t s = 0; s < rows; s += nr)
+                    (adj ? im.dadj : im.dfwd)[j].push_back(DenseTile{ii, bi, s, (int32_t)std::min(nr, rows - s), 0});
+            }
         }
         im.inst.push_back(d);
     }
@@ -485,9 +502,9 @@ size_t image_table_bytes(const TableImage& im) {
     for (const auto& v : im.fadj) t += vbytes(v);
     for (const auto& v : im.dfwd) t += vbytes(v);
     for (const auto& v : im.dadj) t += vbytes(v);
-    // initialisation tiles folded into convolution launches: the tiles outside
-    // owned ranges, and one more piece for a range inside a tile
-    t += vbytes(im.xt) + vbytes(im.yt) + 2 * vbytes(im.cblk);
+    // initialisation tiles folded into convolution or dense launches: the tiles
+    // outside owned ranges, and one more piece for a range inside a tile
+    t += vbytes(im.xt) + vbytes(im.yt) + 2 * vbytes(im.cblk) + 2 * vbytes(im.dblk);
     return t + 256;
 }
 
@@ -636,12 +653,17 @@ int Engine::build(const std::vector<InstRec>& r) {
     // initialisation rides on the first convolution launch as extra
     // workgroups (one launch fewer per apply); tiles wholly inside an owned
     // range need no initialisation at all.
+    // The same for the dense blocks of tables without a convolution (own_dense).
     std::vector<VecTile> init_tiles[2];
     for (int adj = 0; adj < 2; ++adj) {
-        fold_init[adj] = 0;
-        if ((adj ? im.cadj : im.cfwd).empty()) continue;
+        fold_init[adj] = own_dense[adj] = 0;
+        const bool conv = !(adj ? im.cadj : im.cfwd).empty();
+        if (!conv && im.dblk.empty()) continue;
         bool all = true;
-        for (const ConvBlock& cb : im.cblk) all = all && ((cb.own >> adj) & 1);
+        if (conv)
+            for (const ConvBlock& cb : im.cblk) all = all && ((cb.own >> adj) & 1);
+        else
+            for (const DenseBlock& db : im.dblk) all = all && ((db.own >> adj) & 1);
         if (!all) continue;
         for (const VecTile& t : adj ? im.xt : im.yt) {
             const InstDesc& d = im.inst[t.inst];
@@ -651,6 +673,11 @@ int Engine::build(const std::vector<InstRec>& r) {
                 const ConvBlock& cb = im.cblk[b];
                 const int64_t lo = adj ? cb.col0 : cb.row0;
                 own.emplace_back(lo, lo + (adj ? cb.n_in : cb.n_in + cb.k - 1));
+            }
+            for (int b = d.db0; !conv && b < d.db1; ++b) {
+                const DenseBlock& db = im.dblk[b];
+                const int64_t lo = adj ? db.col0 : db.row0;
+                own.emplace_back(lo, lo + (adj ? db.cols : db.rows));
             }
             std::sort(own.begin(), own.end());
             int64_t pos = t.start;
@@ -665,7 +692,7 @@ int Engine::build(const std::vector<InstRec>& r) {
             }
             piece(end);
         }
-        fold_init[adj] = 1;
+        (conv ? fold_init : own_dense)[adj] = 1;
     }
     // CG steps fold into the FFT engine's A^T launch when that launch (its
     // transform workgroups and its initialisation workgroups) writes every X
@@ -795,8 +822,19 @@ int Engine::build(const std::vector<InstRec>& r) {
         cl[0].init = (const VecTile*)put(init_tiles[adj].data(), init_tiles[adj].size() * sizeof(VecTile));
         cl[0].ninit = (int)init_tiles[adj].size();
     }
-    for (const auto& v : im.dfwd) df.push_back(DenseLaunch{(const DenseTile*)put(v.data(), v.size() * sizeof(DenseTile)), dbd, (int)v.size()});
-    for (const auto& v : im.dadj) da.push_back(DenseLaunch{(const DenseTile*)put(v.data(), v.size() * sizeof(DenseTile)), dbd, (int)v.size()});
+    for (int adj = 0; adj < 2; ++adj) {
+        const int64_t w = precision == CGS_FP64 ? 2 : 4;   // elements of a 16-byte vector
+        for (const auto& v : adj ? im.dadj : im.dfwd) {
+            int64_t vecs = 0;
+            for (const DenseTile& t : v) vecs = std::max(vecs, (adj ? im.dblk[t.blk].rows : im.dblk[t.blk].cols) / w);
+            (adj ? da : df).push_back(DenseLaunch{(const DenseTile*)put(v.data(), v.size() * sizeof(DenseTile)), dbd,
+                                                  (int)v.size(), vecs, nullptr, 0});
+        }
+        std::vector<DenseLaunch>& dl = adj ? da : df;
+        if (!own_dense[adj] || dl.empty()) continue;
+        dl[0].init = (const VecTile*)put(init_tiles[adj].data(), init_tiles[adj].size() * sizeof(VecTile));
+        dl[0].ninit = (int)init_tiles[adj].size();
+    }
     if (off > tab_cap) return fail(CGS_ENOMEM, "table overflow");
     CGS_HIP(hipMemcpyAsync(tab_dev, tab_host, off, hipMemcpyHostToDevice, stream));
     char* w = work_dev;
@@ -843,7 +881,8 @@ void Engine::apply(int adj, int out, int in, int base, double sigma, int gate) {
     // with no convolution launch in between, the first GEMM's packing launch
     // also writes the output's initial value
     const bool init_in_pack = use_gemm && cl.empty() && !fold_init[adj] && !recs[0].op->dense.empty();
-    if (!fold_init[adj] && !init_in_pack) launch_apply_init(prec, T, adj, out, in, base, sigma, gate, stream);
+    const int own = !use_gemm && own_dense[adj];   // (the dense launches write base and identity blocks)
+    if (!fold_init[adj] && !init_in_pack && !own) launch_apply_init(prec, T, adj, out, in, base, sigma, gate, stream);
     for (const auto& c : cl) conv(c, adj, out, in, base, sigma, gate);
     if (use_gemm) {
         // every instance shares the dense blocks: one MFMA GEMM per block
@@ -854,7 +893,7 @@ void Engine::apply(int adj, int out, int in, int base, double sigma, int gate) {
             first = false;
         }
     } else {
-        for (const auto& d : adj ? da : df) launch_gemv(prec, T, d, adj, out, in, sigma, gate, stream);
+        for (const auto& d : adj ? da : df) launch_gemv(prec, T, d, adj, out, in, base, sigma, gate, own, stream);
     }
 }
 

@@ -182,6 +182,7 @@ class Engine {
     double* gather_dev = nullptr;
     std::vector<ConvLaunch> cf, ca;
     int fold_init[2] = {0, 0};   // output initialisation rides on the first convolution launch
+    int own_dense[2] = {0, 0};   // or, without convolutions, on the dense launches
     // CG start and CG products folded into the FFT engine's A^T launch: when
     // that one launch writes every X element of every instance
     int fold_cg = 0;

@@ -216,75 +216,114 @@ __global__ __launch_bounds__(CONV_NT) void k_conv(Tables tb, ConvLaunch cl, int 
 }
 
 // ---------------------------------------------------------------- operator: dense block
-// out[row] += s * dot(a[row, :], in) for GEMV_RB rows per workgroup; all
-// threads stride over the columns with 16-byte loads of the (padded,
-// 16-byte aligned) rows; FP64 accumulation.  The adjoint walks the stored
-// transpose, so both directions read rows contiguously.
+// out[row] = v + s * dot(a[row, :], in) for the rows of a tile, v the row's base and
+// identity blocks (own: no other block writes the row) or what the output holds.  The
+// adjoint walks the stored transpose, so both directions read rows contiguously; FP64
+// accumulation, thread t over the 16-byte vectors t + 256 j of the row, then the waves.
+// NV > 0: a row is at most 256 NV vectors.  The thread keeps its part of the input in
+// registers and the workgroup streams its rows one after the other, each a contiguous
+// run of up to 48 KB, with the next row's loads in flight: 35.1 us per product of
+// 5000 x 10000 FP32 with its transpose in turn (400 MB, past the last-level cache:
+// 5.7 TB/s, where a plain read of 400 MB reaches 6.3), 36.6 with four rows side by side
+// and the input loaded again for them.  NV = 0: longer rows, that form.
+// Output elements no dense block writes are initialisation tiles of the same launch
+// (a launch of its own took 4.7-7.4 us per product).
 constexpr int GEMV_NT = 256;
-constexpr int GEMV_RB = DENSE_ROWS;
+constexpr int GEMV_RB = 4;
+template <typename T> using v16u = typename Vec16<T>::type __attribute__((aligned(sizeof(T))));
 
-template <typename T>
-__global__ __launch_bounds__(GEMV_NT) void k_gemv(Tables tb, DenseLaunch dl, int adj, int out, int in,
-                                                  double sigma, int gate) {
+template <typename T, int NV>
+__global__ __launch_bounds__(GEMV_NT) void k_gemv(Tables tb, DenseLaunch dl, int adj, int out, int in, int base,
+                                                  double sigma, int gate, int own) {
     using V = typename Vec16<T>::type;
     constexpr int VW = Vec16<T>::W;
-    __shared__ double sh[GEMV_RB][GEMV_NT / 64];
+    __shared__ double part[DENSE_ROWS_MAX][GEMV_NT / 64];
+    if ((int)blockIdx.x >= dl.ntiles) {
+        const VecTile it = dl.init[blockIdx.x - dl.ntiles];
+        const InstDesc di = tb.inst[it.inst];
+        // (two elements at a time: eight take 200 registers, half the products' waves)
+        if (gate_ok(scal(di), gate)) init_tile<T, 2>(tb, di, it, adj, out, in, base, sigma, false);
+        return;
+    }
     const DenseTile tl = dl.tiles[blockIdx.x];
     const InstDesc d = tb.inst[tl.inst];
-    if (!gate_ok(scal(d), gate)) return;
     const DenseBlock db = dl.blocks[tl.blk];
-    gptr<const T> a;
-    int64_t ld, ncols;
-    gptr<T> o;
-    gptr<const T> x;
-    if (!adj) {
-        a = (gptr<const T>)db.a;
-        ld = db.ld;
-        ncols = db.cols;
-        o = yvec<T>(d, out) + db.row0;
-        x = xvec<T>(d, in) + db.col0;
-    } else {
-        a = (gptr<const T>)db.at;
-        ld = db.ldt;
-        ncols = db.rows;
-        o = xvec<T>(d, out) + db.col0;
-        x = yvec<T>(d, in) + db.row0;
-    }
-    const int nr = tl.nr;
-    gptr<const T> arow = a + tl.r0 * ld;
-    double acc[GEMV_RB];
+    if (!gate_ok(scal(d), gate)) return;
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const int64_t ld = adj ? db.ldt : db.ld, ncols = adj ? db.rows : db.cols;
+    const int64_t g0 = (adj ? db.col0 : db.row0) + tl.r0;   // the tile's first output
+    gptr<const T> arow = (gptr<const T>)(adj ? db.at : db.a) + tl.r0 * ld;
+    gptr<T> o = (adj ? xvec<T>(d, out) : yvec<T>(d, out)) + g0;
+    gptr<const T> x = adj ? yvec<T>(d, in) + db.row0 : xvec<T>(d, in) + db.col0;
+    const int nr = tl.nr;   // <= DENSE_ROWS_MAX
+    T v0 = T(0);            // thread r < nr: what row r holds besides the products
+    if (tid < nr) v0 = own ? (T)owned_init<T>(d, tb.ids, adj, in, base, sigma, g0 + tid) : o[tid];
+    const int64_t nvec = ncols / VW, jt = nvec * VW + tid;   // (jt: the thread's element past the vectors)
+    auto wave_part = [&](int r, double acc) {
+        if (jt < ncols) acc = fma((double)arow[r * ld + jt], (double)x[jt], acc);
+        acc = wave_sum(acc);
+        if ((tid & 63) == 0) part[r][wave] = acc;
+    };
+    if constexpr (NV > 0) {
+        // (the longest rows leave the next row's loads to the CU's other workgroups:
+        // a second buffer would halve their number)
+        constexpr bool AHEAD = NV < 12;
+        V xv[NV], cur[NV], nxt[NV];
+        const V zero = {};
+        const int nv = (int)nvec;
+        auto load_row = [&](int r, V (&m)[NV]) {
+            gptr<const V> p = (gptr<const V>)(arow + r * ld);
 #pragma unroll
-    for (int r = 0; r < GEMV_RB; ++r) acc[r] = 0.0;
-    const int64_t nvec = ncols / VW;
-    for (int64_t v = threadIdx.x; v < nvec; v += GEMV_NT) {
-        T xv[VW];
+            for (int u = 0; u < NV; ++u) m[u] = tid + GEMV_NT * u < nv ? p[tid + GEMV_NT * u] : zero;
+        };
+        load_row(0, cur);
 #pragma unroll
-        for (int e = 0; e < VW; ++e) xv[e] = x[v * VW + e];
+        for (int u = 0; u < NV; ++u) {
+            const int i = tid + GEMV_NT * u;
+            xv[u] = i < nv ? (V)*(gptr<const v16u<T>>)(x + (int64_t)i * VW) : zero;
+        }
+        for (int r = 0; r < nr; ++r) {
+            if (AHEAD && r + 1 < nr) load_row(r + 1, nxt);
+            double acc = 0.0;
 #pragma unroll
-        for (int r = 0; r < GEMV_RB; ++r) {
-            if (r < nr) {
-                const V av = *(gptr<const V>)(arow + r * ld + v * VW);
-                T ae[VW];
-                vec_get<T>(av, ae);
+            for (int u = 0; u < NV; ++u) {
+                if (tid + GEMV_NT * u >= nv) break;
 #pragma unroll
-                for (int e = 0; e < VW; ++e) acc[r] = fma((double)ae[e], (double)xv[e], acc[r]);
+                for (int e = 0; e < VW; ++e) acc = fma((double)cur[u][e], (double)xv[u][e], acc);
+            }
+            if (!AHEAD && r + 1 < nr) load_row(r + 1, cur);
+            wave_part(r, acc);
+            if (AHEAD) {
+#pragma unroll
+                for (int u = 0; u < NV; ++u) cur[u] = nxt[u];
             }
         }
-    }
-    for (int64_t j = nvec * VW + threadIdx.x; j < ncols; j += GEMV_NT) {
-        const double xj = (double)x[j];
+    } else {
+        for (int rb = 0; rb < nr; rb += GEMV_RB) {
+            double acc[GEMV_RB];
 #pragma unroll
-        for (int r = 0; r < GEMV_RB; ++r)
-            if (r < nr) acc[r] = fma((double)arow[r * ld + j], xj, acc[r]);
-    }
-    const double s = sigma * db.scale;
+            for (int r = 0; r < GEMV_RB; ++r) acc[r] = 0.0;
+            for (int64_t v = tid; v < nvec; v += GEMV_NT) {
+                const V xv = (V)*(gptr<const v16u<T>>)(x + v * VW);
 #pragma unroll
-    for (int r = 0; r < GEMV_RB; ++r) {
-        const double tot = block_sum<GEMV_NT>(acc[r], sh[r]);
-        if (threadIdx.x == 0 && r < nr) {
-            gptr<T> op = o + tl.r0 + r;
-            *op = (T)((double)*op + s * tot);
+                for (int r = 0; r < GEMV_RB; ++r) {
+                    if (rb + r >= nr) continue;
+                    const V av = *(gptr<const V>)(arow + (rb + r) * ld + v * VW);
+#pragma unroll
+                    for (int e = 0; e < VW; ++e) acc[r] = fma((double)av[e], (double)xv[e], acc[r]);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < GEMV_RB; ++r)
+                if (rb + r < nr) wave_part(rb + r, acc[r]);
         }
+    }
+    __syncthreads();
+    if (tid < nr) {
+        double tot = 0.0;
+#pragma unroll
+        for (int w = 0; w < GEMV_NT / 64; ++w) tot += part[tid][w];
+        o[tid] = (T)((double)v0 + sigma * db.scale * tot);
     }
 }
 
@@ -1204,9 +1243,26 @@ void launch_conv(int prec, const Tables& t, const ConvLaunch& c, int adj, int ou
     }
 #undef CGS_CONV
 }
-void launch_gemv(int prec, const Tables& t, const DenseLaunch& d, int adj, int out, int in,
-                 double sigma, int gate, hipStream_t st) {
-    CGS_DISPATCH(prec, k_gemv, d.ntiles, GEMV_NT, st, t, d, adj, out, in, sigma, gate);
+template <typename T>
+static void gemv(const Tables& t, const DenseLaunch& d, int adj, int out, int in, int base, double sigma, int gate,
+                 int own, hipStream_t st) {
+    const int grid = d.ntiles + (own ? d.ninit : 0);
+    if (grid <= 0) return;
+    const int nv = (int)((d.vecs + GEMV_NT - 1) / GEMV_NT);   // vectors per thread of the longest row
+#define CGS_GEMV(NV) k_gemv<T, NV><<<grid, GEMV_NT, 0, st>>>(t, d, adj, out, in, base, sigma, gate, own)
+    if (nv <= 2) CGS_GEMV(2);
+    else if (nv <= 4) CGS_GEMV(4);
+    else if (nv <= 6) CGS_GEMV(6);
+    else if (nv <= 8) CGS_GEMV(8);
+    else if (nv <= 10) CGS_GEMV(10);
+    else if (nv <= 12) CGS_GEMV(12);
+    else CGS_GEMV(0);
+#undef CGS_GEMV
+}
+void launch_gemv(int prec, const Tables& t, const DenseLaunch& d, int adj, int out, int in, int base,
+                 double sigma, int gate, int own, hipStream_t st) {
+    if (prec == 0) gemv<double>(t, d, adj, out, in, base, sigma, gate, own, st);
+    else gemv<float>(t, d, adj, out, in, base, sigma, gate, own, st);
 }
 void launch_cg_init(int prec, const Tables& t, int z, int r, int p, int q, int h, int have_q,
                     double zeta, double rate, double floor_, int cg_max, int gate, hipStream_t st) {

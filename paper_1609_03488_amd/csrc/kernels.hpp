@@ -49,6 +49,11 @@ struct DenseLaunch {
     const DenseTile* tiles;
     const DenseBlock* blocks;
     int ntiles;
+    int64_t vecs;    // 16-byte vectors of the longest row of the launch's blocks
+    // initialisation tiles of the output elements no dense block writes, run by
+    // workgroups ntiles.. (only in a launch whose blocks own their outputs)
+    const VecTile* init;
+    int ninit;
 };
 
 // out[i] = base[i] (or 0) + sigma * sum over identity blocks; out/in/base are
@@ -71,9 +76,10 @@ void launch_conv_spectrum(const void* w, int64_t k, void* spec, hipStream_t st);
 // writes the FFT engine's twiddle table on the current device, the first time
 // (before any launch that reads it, outside stream capture; synchronises st)
 int fft_prepare(hipStream_t st);
-// out += sigma * scale * a (or a^T) * in for every dense tile.
-void launch_gemv(int prec, const Tables& t, const DenseLaunch& d, int adj, int out, int in,
-                 double sigma, int gate, hipStream_t st);
+// out += sigma * scale * a (or a^T) * in for every dense tile; own = 1: the rows are
+// written, base and identity blocks included, and the launch's initialisation tiles too
+void launch_gemv(int prec, const Tables& t, const DenseLaunch& d, int adj, int out, int in, int base,
+                 double sigma, int gate, int own, hipStream_t st);
 
 // CG (Section IV-B listing) on (I + A^T A) z = h with kinds z, r, p, q, h.
 // init: r = h - q (q = K z, or q = 0 when have_q = 0), p = r, rr = ||r||^2,

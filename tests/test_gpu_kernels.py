@@ -143,3 +143,35 @@ def test_fused_register_form_fp32_solves(n, k):
         assert s.solve()[0]["status"] == P.SOLVED
         f.append(o.deconv_objective(d["c"], d["b"], s.solution(0)[0][:n]))
     assert abs(f[0] - f[1]) <= 1e-4 * f[0]
+
+
+# columns at the edges of the row-streaming forms (256 threads x 16-byte vectors x 2, 4, ..,
+# 12; FP64 1024 columns a pair, FP32 2048) and past the last, with ends that are no whole
+# vector; one row, rows that split unevenly over the workgroups, more than 16 per tile;
+# the block off the 16-byte grid of the vectors, identity blocks beside and across it
+@pytest.mark.parametrize("m,n", [(1, 1), (3, 5), (70, 255), (300, 1023), (1030, 1025), (500, 2049), (17000, 33),
+                                 (40, 6145), (33, 12289), (9, 24600)])
+@pytest.mark.parametrize("prec", [P.FP64, P.FP32], ids=["fp64", "fp32"])
+def test_dense_products_edges(m, n, prec):
+    """A x and A^T y against NumPy in FP64: sums accumulate in FP64 and round once, so
+    |dev - ref| <= (4 u + cols 2^-52) sum |a||x| with u the working precision's."""
+    print("[case] dense products", m, n, prec, flush=True)
+    rng = np.random.default_rng(m * 7 + n)
+    r0, c0, rows, cols = 3, 1, m + 7, n + 2
+    A = rng.standard_normal((m, n)).astype(np.float32).astype(np.float64)
+    ln = min(rows, cols) - 1
+    op = P.Operator(rows, cols).add_dense(r0, c0, A, 0.5).add_identity(0, 0, ln, -0.25).add_identity(1, 1, ln, 2.0)
+    s = P.Solver(op, rows, [], P.Settings.make(precision=prec, normalize=0))
+    u = 2.0 ** -53 if prec == P.FP64 else 2.0 ** -24
+    for adj in (False, True):
+        v = rng.standard_normal(rows if adj else cols).astype(np.float32).astype(np.float64)
+        ref, mag = np.zeros(cols if adj else rows), np.zeros(cols if adj else rows)
+        for off, sc in ((0, -0.25), (1, 2.0)):
+            ref[off:off + ln] += sc * v[off:off + ln]
+            mag[off:off + ln] += abs(sc) * np.abs(v[off:off + ln])
+        src = v[r0:r0 + m] if adj else v[c0:c0 + n]
+        lo, M = (c0, A.T) if adj else (r0, A)
+        ref[lo:lo + M.shape[0]] += 0.5 * (M @ src)
+        mag[lo:lo + M.shape[0]] += 0.5 * (np.abs(M) @ np.abs(src))
+        err = np.abs(s.apply(v, transpose=adj) - ref)
+        assert np.all(err <= (4 * u + max(m, n) * 2.0 ** -52) * mag)
