@@ -634,7 +634,7 @@ int Engine::build(const std::vector<InstRec>& r) {
         d.fused = (st.fused_max > 0 && !use_gemm && d.n + d.m <= lim && dense <= FUSED_DENSE_MAX) ? 1 : 0;
         (d.fused ? n_fused : n_multi) += 1;
     }
-    fused_res = fused_reg = 0;
+    fused_res = fused_reg = setup_lds = 0;
     fused_general = 0;
     const int64_t lds = n_fused ? fused_prepare() : 0;
     for (InstDesc& d : im.inst) {
@@ -644,6 +644,8 @@ int Engine::build(const std::vector<InstRec>& r) {
             d.fused = FUSED_REG + v;
             fused_reg = std::max(fused_reg, std::min(lds, fused_reg_bytes(prec, d.n, d.m, im.cblk[d.cb0],
                                                                           kRegVariants[v].r, true)));
+            if (prec == 0 && setup_cg_takes(d, im.cblk[d.cb0], lds))
+                setup_lds = std::max(setup_lds, setup_cg_bytes(d, im.cblk[d.cb0]));
         } else {
             fused_general = 1;
             fused_res = std::max(fused_res, fused_resident_bytes(prec, d.n, d.m));
@@ -1235,8 +1237,15 @@ int Engine::setup() {
     launch_cg_init(prec, T, XG, XR, XP, XQ, XH, 1, 0.0, 0.0, setup_tol(), st.setup_max_iters,
                    G_SETUP, stream);
     int it = 0;
+    // instances whose whole loop runs in one launch; the others' runs launch by launch
+    bool rest = setup_lds == 0 || st.setup_max_iters > SETUP_CG_ITERS;
+    if (!rest) {
+        launch_setup_cg(T, setup_lds, st.setup_max_iters, stream);
+        for (const InstDesc& d : im.inst)
+            rest = rest || d.fused < FUSED_REG || !setup_cg_takes(d, im.cblk[d.cb0], setup_lds);
+    }
     while (it < st.setup_max_iters) {
-        const int nb = std::min(8, st.setup_max_iters - it);
+        const int nb = rest ? std::min(8, st.setup_max_iters - it) : 0;
         for (int j = 0; j < nb; ++j) cg_iter(XG, G_SETUP_CG, st.setup_max_iters, 0, it + j);
         it += nb;
         CGS_TRY(fetch_scalars());

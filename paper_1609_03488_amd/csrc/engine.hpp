@@ -205,6 +205,7 @@ class Engine {
     int64_t fused_res = 0;        // LDS bytes of the largest general fused instance's resident vectors
     int64_t fused_reg = 0;        // LDS bytes of the largest fused instance of the register form
     int fused_general = 0;        // some fused instance takes the general form
+    int64_t setup_lds = 0;        // LDS bytes of the largest instance k_setup_cg takes (0: none)
     // batched BF16 MFMA path for dense blocks shared by every instance
     int use_gemm = 0;
     int gemm_corr = 0;           // 1: add the refinement products (hi x lo)

@@ -926,6 +926,180 @@ __global__ __launch_bounds__(FNT) void k_fused(Tables tb, FusedArgs fa) {
     if (tid == 0) record_state(sc, fa, tau, kap, ut, iter, cgtot, cgmax, status);
 }
 
+// The CG loop of the setup solve (z = g_x; r, p and the start test from k_cg_init) for
+// FP64 instances of the register form whose X vector is one vector tile: one workgroup
+// and one launch instead of four launches per iteration and a wait of the host after
+// every eight.  Bound by the serial chain of the products (6 us an iteration at n = 1000,
+// k = 101): a 100-step solve at that size 4.2 -> 3.6 ms.  Products as in fused_reg; the
+// dot products and the update are those of k_cg_dot and k_cg_update, sum for sum
+// (256 threads over the tile, ||r'||^2 from the expansion), so the result is theirs.
+constexpr int DOT_NT = VEC_NT;
+template <typename T, int R, int NX, int NY>
+DEVI void setup_cg(const Tables& tb, const InstDesc& d, T* lds, double* sh, int cg_max) {
+    gptr<double> sc = scal(d);
+    const int tid = threadIdx.x;
+    const ConvBlock& cbr = tb.cblk[d.cb0];
+    const int n = (int)d.n, m = (int)d.m, n_in = (int)cbr.n_in, k = (int)cbr.k, kpad = (int)cbr.kpad;
+    const int col0 = (int)cbr.col0, row0 = (int)cbr.row0, no = n_in + k - 1;
+    const double cscale = cbr.scale;
+    cptr<T> wf = (cptr<T>)cbr.w_fwd, wa = (cptr<T>)cbr.w_adj;
+    const RegLds L = reg_lds(n, m, n_in, k, kpad, R);
+    T *lq = lds + L.total, *lr = lq + n;   // q and r, for the dot products
+    const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~63) * R;
+    auto each_x = [&](auto f) {
+#pragma unroll
+        for (int q = 0; q < NX; ++q)
+            if (q * FNT < n && tid + q * FNT < n) f(q, tid + q * FNT);
+    };
+    auto x_at = [&](int c) { return c >= col0 && c < col0 + n_in ? L.xi + k - 1 + c - col0 : L.xo + (c < col0 ? c : c - n_in); };
+    auto y_at = [&](int r) { return r >= row0 && r < row0 + no ? L.yi + r - row0 : L.yo + (r < row0 ? r : r - no); };
+    for (int i = tid; i < L.total; i += FNT) lds[i] = T(0);
+    __syncthreads();
+    gptr<T> zv = xvec<T>(d, XG);
+    T p[NX], r[NX], z[NX], q[NX];
+    each_x([&](int s, int i) {
+        z[s] = zv[i];
+        r[s] = xvec<T>(d, XR)[i];
+        p[s] = xvec<T>(d, XP)[i];
+        lds[x_at(i)] = p[s];
+        lr[i] = r[s];
+    });
+    __syncthreads();
+    auto sums = [&](int adj) {
+        const int nout = adj ? n_in : no;
+        if (wave0 < nout) {
+            T acc[R];
+            reg_conv<T, R>(acc, lds + (adj ? L.yi : L.xi) + tid * R, adj ? wa : wf, kpad);
+#pragma unroll
+            for (int e = 0; e < R; ++e)
+                if (tid * R + e < nout) lds[L.cs + tid * R + e] = acc[e];
+        }
+        __syncthreads();
+    };
+    // base + identity blocks (in table order) of row / column i, input `at` in LDS
+    auto ids = [&](int adj, int i, double v) {
+        for (int b = d.id0; b < d.id1; ++b) {
+            const IdBlock ib = tb.ids[b];
+            const int r0 = (int)(adj ? ib.col0 : ib.row0), c0 = (int)(adj ? ib.row0 : ib.col0);
+            if (i >= r0 && i < r0 + (int)ib.len) {
+                const int c = i - r0 + c0;
+                v += ib.scale * (double)lds[adj ? y_at(c) : x_at(c)];
+            }
+        }
+        return v;
+    };
+    const double tol = sc[SC_CGTOL];
+    double cgit = 0.0, pq = 0.0, al = 0.0, be = 0.0, last = sc[SC_RR];
+    bool more = true;
+    for (int it = 0; more; ++it) {
+        sums(0);
+#pragma unroll
+        for (int s = 0; s < NY; ++s) {
+            const int i = tid + s * FNT;
+            if (i >= m) break;
+            double v = ids(0, i, 0.0);
+            if (i >= row0 && i < row0 + no) v = v + cscale * (double)lds[L.cs + i - row0];
+            lds[y_at(i)] = (T)v;
+        }
+        __syncthreads();
+        sums(1);
+        each_x([&](int s, int i) {
+            double v = ids(1, i, (double)p[s]);
+            if (i >= col0 && i < col0 + n_in) v = v + cscale * (double)lds[L.cs + i - col0];
+            q[s] = (T)v;
+            lq[i] = q[s];
+        });
+        __syncthreads();
+        double s4[4] = {0.0, 0.0, 0.0, 0.0};
+        if (tid < DOT_NT) {
+            for (int i = tid; i < n; i += DOT_NT) {
+                const double pi = (double)lds[x_at(i)], qi = (double)lq[i], ri = (double)lr[i];
+                s4[0] = fma(pi, qi, s4[0]);
+                s4[1] = fma(ri, ri, s4[1]);
+                s4[2] = fma(ri, qi, s4[2]);
+                s4[3] = fma(qi, qi, s4[3]);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double t = wave_sum(s4[j]);
+                if ((tid & 63) == 0) sh[j * (DOT_NT / 64) + (tid >> 6)] = t;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            double t = 0.0;
+#pragma unroll
+            for (int w = 0; w < DOT_NT / 64; ++w) t += sh[j * (DOT_NT / 64) + w];
+            s4[j] = t;
+        }
+        pq = s4[0];
+        const double rr = s4[1], rq = s4[2], qq = s4[3];
+        al = rr / pq;
+        const bool ok = pq > 0.0 && std::isfinite(al);
+        const double rr1 = fma(al * al, qq, fma(-2.0 * al, rq, rr));
+        be = rr > 0.0 ? rr1 / rr : 0.0;
+        more = ok && std::isfinite(rr1) && sqrt(rr1) > tol && it + 1 < cg_max;
+        last = ok ? rr1 : rr;
+        if (ok) cgit += 1.0;
+        else al = 0.0;
+        each_x([&](int s, int i) {
+            if (ok) z[s] = (T)fma(al, (double)p[s], (double)z[s]);
+            if (more) {
+                r[s] = (T)fma(-al, (double)q[s], (double)r[s]);
+                p[s] = (T)fma(be, (double)p[s], (double)r[s]);
+                lds[x_at(i)] = p[s];
+                lr[i] = r[s];
+            }
+        });
+        __syncthreads();
+    }
+    each_x([&](int s, int i) { zv[i] = z[s]; });
+    if (tid == 0) {
+        sc[SC_PQ] = pq;
+        sc[SC_ALPHA] = al;
+        sc[SC_RR] = last;
+        sc[SC_BETA] = be;
+        sc[SC_CGIT] += cgit;
+        sc[SC_CGTOT] += cgit;
+        sc[SC_SETUPIT] += cgit;
+        if (sc[SC_CGIT] > sc[SC_CGMAX]) sc[SC_CGMAX] = sc[SC_CGIT];
+        sc[SC_CGACT] = 0.0;
+    }
+}
+
+__host__ __device__ int64_t setup_cg_bytes(const InstDesc& d, const ConvBlock& cb) {
+    const int R = kRegVariants[d.fused - FUSED_REG].r;
+    return (reg_lds((int)d.n, (int)d.m, (int)cb.n_in, (int)cb.k, (int)cb.kpad, R).total + 2 * d.n) *
+           (int64_t)sizeof(double);
+}
+
+// lds: bytes of dynamic LDS of the launch (the need of the largest instance taken)
+__global__ __launch_bounds__(FNT) void k_setup_cg(Tables tb, int cg_max, int64_t lds_bytes) {
+    extern __shared__ __align__(16) unsigned char fsmem[];
+    __shared__ double sh[4 * (DOT_NT / 64)];
+    const InstDesc d = tb.inst[blockIdx.x];
+    if (d.fused < FUSED_REG || !setup_cg_takes(d, tb.cblk[d.cb0], lds_bytes) || !gate_ok(scal(d), G_SETUP_CG)) return;
+    double* lds = reinterpret_cast<double*>(fsmem);
+    switch (d.fused - FUSED_REG) {
+#define CGS_SETUP(V) \
+    case V: setup_cg<double, kRegVariants[V].r, kRegVariants[V].nx, kRegVariants[V].ny>(tb, d, lds, sh, cg_max); break
+        CGS_SETUP(0);
+        CGS_SETUP(1);
+        CGS_SETUP(2);
+        CGS_SETUP(3);
+        CGS_SETUP(4);
+        CGS_SETUP(5);
+        CGS_SETUP(6);
+#undef CGS_SETUP
+        default: break;
+    }
+}
+
+void launch_setup_cg(const Tables& t, int64_t lds, int cg_max, hipStream_t st) {
+    if (t.ninst > 0) k_setup_cg<<<t.ninst, FNT, (size_t)lds, st>>>(t, cg_max, lds);
+}
+
 int64_t fused_reg_bytes(int prec, int64_t n, int64_t m, const ConvBlock& cb, int R, bool vectors) {
     const int64_t es = prec == 0 ? 8 : 4;
     int64_t e = reg_lds((int)n, (int)m, (int)cb.n_in, (int)cb.k, (int)cb.kpad, R).total;
@@ -971,6 +1145,8 @@ int fused_prepare() {
             (hipFuncSetAttribute((const void*)k_fused<double>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn) !=
                  hipSuccess ||
              hipFuncSetAttribute((const void*)k_fused<float>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn) !=
+                 hipSuccess ||
+             hipFuncSetAttribute((const void*)k_setup_cg, hipFuncAttributeMaxDynamicSharedMemorySize, dyn) !=
                  hipSuccess))
             dyn = 65536 - fixed;
         g_fused_lds[dev].store(dyn);   // (two threads that get here store the same value)

@@ -221,6 +221,16 @@ constexpr RegVariant kRegVariants[] = {{1, 2, 3}, {1, 3, 4}, {2, 3, 5}, {2, 5, 7
                                        {3, 4, 7}, {4, 5, 9}, {4, 9, 13}, {8, 9, 17}};
 constexpr int kNumRegVariants = 8;
 constexpr int FUSED_THREADS = 512, FUSED_REG = 16, FUSED_REG_IDS = 16;
+// The CG loop of the FP64 setup solve in one launch (k_setup_cg), for instances of the
+// register form (d.fused >= FUSED_REG) with one X tile whose vectors fit the LDS; iteration
+// limits up to SETUP_CG_ITERS, so that a launch ends within about 0.1 s (6 us an iteration)
+// and a larger limit, which only a tolerance below rounding reaches, stays with the host's loop.
+constexpr int SETUP_CG_ITERS = 16384;
+__host__ __device__ int64_t setup_cg_bytes(const InstDesc& d, const ConvBlock& cb);
+__host__ __device__ inline bool setup_cg_takes(const InstDesc& d, const ConvBlock& cb, int64_t lds) {
+    return d.xt1 - d.xt0 == 1 && setup_cg_bytes(d, cb) <= lds;
+}
+void launch_setup_cg(const Tables& t, int64_t lds, int cg_max, hipStream_t st);
 // LDS bytes an instance needs, with the step's vectors (used where they fit) or without
 int64_t fused_reg_bytes(int prec, int64_t n, int64_t m, const ConvBlock& cb, int R, bool vectors);
 size_t fused_smem_bytes(int prec, int kc);

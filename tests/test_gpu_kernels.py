@@ -145,6 +145,34 @@ def test_fused_register_form_fp32_solves(n, k):
     assert abs(f[0] - f[1]) <= 1e-4 * f[0]
 
 
+# X vectors of one element a thread up to a whole tile (2048) and past it (launch by
+# launch); a limit of 1 and 3 iterations, and one above the single launch's
+@pytest.mark.parametrize("n,k,limit", [(20, 3, 2000), (256, 31, 2000), (600, 25, 1), (600, 25, 3), (600, 25, 16384),
+                                       (600, 25, 16385), (1000, 101, 2000), (2046, 9, 2000), (2049, 9, 2000)])
+def test_setup_solve_in_one_launch(n, k, limit):
+    """FP64 setup solve of the fused path against the launch-by-launch one: the same sums,
+    so the same number of CG iterations, and a first step (CG to 1e-13) that agrees to 1e-10."""
+    import workloads as w
+    print("[case] setup solve", n, k, limit, flush=True)
+    d = w.deconv_instance(n, k, k / 7.0, 0.1, 1e-4, n + k)
+    pr = P.deconv_problem(d["c"], d["b"])
+    out = []
+    for fused in (0, 65536):
+        s = P.Solver(pr.op, pr.l, pr.q, P.Settings.make(
+            precision=P.FP64, cg_tol=0.0, cg_floor=1e-13, cg_max_iters=200, setup_tol=1e-12, setup_max_iters=limit,
+            fused_max=fused, fused_lone_max=0))
+        s.set_data(0, pr.b, pr.c)
+        s.iterate(0)
+        its = s.residuals()[0]["cg_iters"]
+        s.iterate(1)
+        out.append((its, s.state(0)))
+    assert out[0][0] == out[1][0] and 1 <= out[0][0] <= limit
+    scale = max(1.0, *(np.abs(v).max() for v in out[0][1][:2]), np.abs(out[0][1][3]).max())
+    for i in (0, 1, 3):
+        assert np.abs(out[0][1][i] - out[1][1][i]).max() <= 1e-10 * scale
+    assert abs(out[0][1][2] - out[1][1][2]) <= 1e-10 * scale
+
+
 # columns at the edges of the row-streaming forms (256 threads x 16-byte vectors x 2, 4, ..,
 # 12; FP64 1024 columns a pair, FP32 2048) and past the last, with ends that are no whole
 # vector; one row, rows that split unevenly over the workgroups, more than 16 per tile;
