@@ -883,7 +883,7 @@ void Engine::apply(int adj, int out, int in, int base, double sigma, int gate) {
     // with no convolution launch in between, the first GEMM's packing launch
     // also writes the output's initial value
     const bool init_in_pack = use_gemm && cl.empty() && !fold_init[adj] && !recs[0].op->dense.empty();
-    const int own = !use_gemm && own_dense[adj];   // (the dense launches write base and identity blocks)
+    const int own = own_dense[adj];   // (the dense launches write base and identity blocks)
     if (!fold_init[adj] && !init_in_pack && !own) launch_apply_init(prec, T, adj, out, in, base, sigma, gate, stream);
     for (const auto& c : cl) conv(c, adj, out, in, base, sigma, gate);
     if (use_gemm) {
@@ -891,7 +891,8 @@ void Engine::apply(int adj, int out, int in, int base, double sigma, int gate) {
         bool first = true;
         for (const DenseBlock& db : recs[0].op->dense) {
             launch_gemm_apply(T, db, adj, out, in, sigma, gate, gemm_corr, panel, panel_stride, gemm_part,
-                              gemm_target, stream, first && init_in_pack, base);
+                              gemm_target, stream, first && init_in_pack, base,
+                              own ? &(adj ? da : df)[0] : nullptr);
             first = false;
         }
     } else {

@@ -12,7 +12,8 @@
 //            (X_hi + X_mid + X_lo) W_hi, a fixed linear map (the BF16 matrix) of
 //            the FP32 input; with `corr` the products (X_hi + X_mid) W_lo are
 //            added (matrix to about 16 bits);
-//   reduce : out_b[n] += s * sum over K splits (fixed order), gated per instance.
+//   reduce : out_b[n] += s * sum over K splits (fixed order), gated per instance; of
+//            blocks that own their output range, base and identity blocks with it.
 // The order of the K terms inside a dot product is irrelevant to the result's
 // definition, so each lane feeds the A (panel) and B (W) operands the same
 // k indices: k0 + 8 * (lane / 32) + e, e = 0..7.
@@ -51,37 +52,58 @@ DEVI int64_t packed_index(int64_t row, int64_t k, int64_t ksteps) {
 // ---------------------------------------------------------------- pack
 // Panels for b < mpad, k < kpad; instance b's input is its vector `in`
 // (X when !adj, Y when adj) starting at `off`, K valid entries; zeros beyond.
-// Blocks past the kblocks * mpad packing blocks are the output's
-// initialisation tiles (base + identity blocks, as k_apply_init), which the
-// apply's reduce then adds to: the output is not an input of the pack.
+// A wave packs one (32-row tile, 16-k step): each lane reads eight consecutive inputs
+// and stores its three 16-byte vectors, the wave 1 KB of each panel in one piece.
+// Bound by latency: the launch takes as long as its initialisation tiles, 10 us of
+// dependent loads (one element per thread, in two-byte stores: 0.3 us more).
+// Blocks past the npack packing blocks are the output's initialisation
+// tiles (base + identity blocks, as k_apply_init; the output is not an input of the
+// pack): `init` where the reduce writes its range itself (own), every vector tile
+// where it adds to them.
 __global__ __launch_bounds__(256) void k_gemm_pack(Tables tb, int ninst, int adj, int in, int64_t off,
-                                                    int64_t K, int64_t kpad, int kblocks, int mpad,
+                                                    int64_t K, int64_t kpad, int npack, int mpad,
                                                     uint16_t* hi, uint16_t* mid, uint16_t* lo, int out,
-                                                    int base, double sigma, int gate) {
-    const int npack = kblocks * mpad;
+                                                    int base, double sigma, int gate, const VecTile* init) {
     if ((int)blockIdx.x >= npack) {
         const int t = (int)blockIdx.x - npack;
-        const VecTile tl = adj ? tb.xt[t] : tb.yt[t];
+        const VecTile tl = init ? init[t] : adj ? tb.xt[t] : tb.yt[t];
         const InstDesc d = tb.inst[tl.inst];
-        if (gate_ok(scal(d), gate)) init_tile<float>(tb, d, tl, adj, out, in, base, sigma, true);
+        if (gate_ok(scal(d), gate)) init_tile<float>(tb, d, tl, adj, out, in, base, sigma, init == nullptr);
         return;
     }
-    const int b = (int)blockIdx.x / kblocks;
-    const int64_t k = (int64_t)((int)blockIdx.x % kblocks) * 256 + threadIdx.x;
-    if (k >= kpad) return;
-    float v = 0.0f;
+    const int ksteps = (int)(kpad / 16), lane = threadIdx.x & 63;
+    const int step = (int)blockIdx.x * 4 + (threadIdx.x >> 6);   // (tile, step) of the wave
+    if (step >= ksteps * (mpad / 32)) return;
+    const int b = step / ksteps * 32 + (lane & 31);
+    const int64_t k = (int64_t)(step % ksteps) * 16 + (lane >> 5) * 8;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = 0.0f;
     if (b < ninst && k < K) {
-        const InstDesc d = tb.inst[b];
-        gptr<const float> src = adj ? yvec<const float>(d, in) : xvec<const float>(d, in);
-        v = src[off + k];
+        const InstDesc& d = tb.inst[b];
+        gptr<const float> src = (adj ? yvec<const float>(d, in) : xvec<const float>(d, in)) + off + k;
+        if (k + 8 <= K) {
+            typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+            const f32x4u a = *(gptr<const f32x4u>)src, c = *(gptr<const f32x4u>)(src + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = a[e], v[4 + e] = c[e];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = k + e < K ? src[e] : 0.0f;
+        }
     }
-    const uint16_t h = f32_to_bf16_rne(v);
-    const float r1 = v - bf16_to_f32(h);           // exact in FP32
-    const uint16_t md = f32_to_bf16_rne(r1);
-    const int64_t i = packed_index(b, k, kpad / 16);
-    hi[i] = h;
-    mid[i] = md;
-    lo[i] = f32_to_bf16_rne(r1 - bf16_to_f32(md));
+    u16x8 h, md, l;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        h[e] = f32_to_bf16_rne(v[e]);
+        const float r1 = v[e] - bf16_to_f32(h[e]);           // exact in FP32
+        md[e] = f32_to_bf16_rne(r1);
+        l[e] = f32_to_bf16_rne(r1 - bf16_to_f32(md[e]));
+    }
+    const int64_t i = (int64_t)step * 64 + lane;
+    reinterpret_cast<u16x8*>(hi)[i] = h;
+    reinterpret_cast<u16x8*>(mid)[i] = md;
+    reinterpret_cast<u16x8*>(lo)[i] = l;
 }
 
 // W (rows x ld FP32, row-major, ld = kpad) -> packed BF16 hi and lo (BF16
@@ -109,6 +131,12 @@ __global__ __launch_bounds__(256) void k_gemm_pack_w(const float* w, int64_t row
 // a time in two buffers, loading chunk c + 1 (and each wave its W blocks of
 // chunk c + 1) while the matrix cores work on chunk c.  Every wave reads W
 // once; the panels cross from L2 once per workgroup instead of once per wave.
+// 64 instances of a 2000 x 8000 block: 14.7 us for 32 MB of W, 8 MB of partials and
+// 6.1 GFLOP (5.3 us at HBM, 5 us at the matrix cores); a workgroup per CU walks 31 K
+// steps, a chunk's latency at a time.  Neither chunks of eight steps (15.6 us, half the
+// launch's start gone into filling them) nor an order that keeps each XCD to its own
+// splits' panels (14.9 us) was faster.  A launch none of whose instances takes part,
+// two in five of a batch's CG launches, ends after 3 us.
 constexpr int GEMM_NT = 256;
 constexpr int GEMM_TN = 128;
 constexpr int GEMM_TM = 64;
@@ -126,7 +154,8 @@ __global__ __launch_bounds__(GEMM_NT) void k_gemm_bf16(const uint16_t* __restric
                                                        const uint16_t* __restrict__ x_lo,
                                                        int ksteps_per_split,
                                                        float* __restrict__ part, int64_t npad,
-                                                       int mpad) {
+                                                       int mpad, const InstDesc* __restrict__ insts,
+                                                       int ninst, int gate) {
     __shared__ u16x8 xs[2][GEMM_XCH];   // [buffer][(kk * 6 + panel) * 64 + lane]
     constexpr int PER = GEMM_XCH / GEMM_NT;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -178,6 +207,10 @@ __global__ __launch_bounds__(GEMM_NT) void k_gemm_bf16(const uint16_t* __restric
     };
     f32x16 acc0 = {}, acc1 = {};
     load_chunk(0, wc, lc);
+    // none of the M tile's 64 instances takes part (lane: instance): nothing reads its
+    // partials.  Tested behind the first loads, which hide the scalars' latency.
+    const int inst = mt0 * 32 + lane;
+    if (!__any(inst < ninst && gate_ok(scal(insts[inst < ninst ? inst : 0]), gate))) return;
     stage(0);
     __syncthreads();
     for (int c = 0; c < nch; ++c) {
@@ -236,33 +269,33 @@ __global__ __launch_bounds__(GEMM_NT) void k_gemm_bf16(const uint16_t* __restric
 }
 
 // ---------------------------------------------------------------- reduce
-__global__ __launch_bounds__(256) void k_gemm_reduce(const InstDesc* insts, int ninst, int adj, int out,
-                                                      int64_t off, int64_t N, const float* part,
-                                                      int nsplit, int64_t npad, int mpad, double s,
-                                                      int gate_kind) {
+// own: the block writes its output range itself, base and identity blocks included (to
+// the working precision first, as an initialisation tile leaves them)
+__global__ __launch_bounds__(256) void k_gemm_reduce(const InstDesc* insts, const IdBlock* ids, int adj, int out,
+                                                      int in, int base, int64_t off, int64_t N, const float* part,
+                                                      int nsplit, int64_t npad, int mpad, double sigma,
+                                                      double scale, int gate, int own) {
     const int b = blockIdx.y;
-    if (b >= ninst) return;
-    const InstDesc d = insts[b];
-    gptr<const double> sc = (gptr<const double>)d.base;
-    bool on;
-    switch (gate_kind) {
-        case G_ALL: on = true; break;
-        case G_SETUP: on = sc[SC_ACTIVE] != 0.0 && sc[SC_PHASE] == 0.0; break;
-        case G_SETUP_CG: on = sc[SC_ACTIVE] != 0.0 && sc[SC_PHASE] == 0.0 && sc[SC_CGACT] != 0.0; break;
-        case G_ADMM:
-        case G_CHECK: on = sc[SC_ACTIVE] != 0.0 && sc[SC_PHASE] == 1.0; break;
-        case G_ADMM_CG: on = sc[SC_ACTIVE] != 0.0 && sc[SC_PHASE] == 1.0 && sc[SC_CGACT] != 0.0; break;
-        case G_ANY_CG: on = sc[SC_CGACT] != 0.0; break;
-        case G_CHECK_ANY: on = sc[SC_ACTIVE] != 0.0 && sc[SC_PHASE] >= 1.0; break;
-        default: on = false;
-    }
-    if (!on) return;
     const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (n >= N) return;
-    float acc = 0.0f;
-    for (int q = 0; q < nsplit; ++q) acc += part[((int64_t)q * mpad + b) * npad + n];
-    gptr<float> o = adj ? xvec<float>(d, out) : yvec<float>(d, out);
-    o[off + n] = (float)((double)o[off + n] + s * (double)acc);
+    const InstDesc d = insts[b];
+    if (!gate_ok(scal(d), gate) || n >= N) return;
+    const float* p = part + (int64_t)b * npad + n;
+    constexpr int U = 8;   // splits whose loads are in flight together
+    float v[U], acc = 0.0f;
+    auto load = [&](int q0) {
+#pragma unroll
+        for (int q = 0; q < U; ++q) v[q] = q0 + q < nsplit ? p[(int64_t)(q0 + q) * mpad * npad] : 0.0f;
+    };
+    load(0);
+    gptr<float> o = (adj ? xvec<float>(d, out) : yvec<float>(d, out)) + off + n;
+    const float v0 = own ? (float)owned_init<float>(d, ids, adj, in, base, sigma, off + n) : *o;
+    for (int q0 = 0; q0 < nsplit; q0 += U) {
+        if (q0) load(q0);
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if (q0 + q < nsplit) acc += v[q];
+    }
+    *o = (float)((double)v0 + scale * (double)acc);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -293,7 +326,7 @@ void launch_gemm_pack_w(const float* w, int64_t rows, int64_t kpad, uint16_t* hi
 
 void launch_gemm_apply(const Tables& tb, const DenseBlock& db, int adj, int out, int in, double sigma,
                        int gate, int corr, uint16_t* panel, size_t panel_stride, float* part,
-                       int target_wgs, hipStream_t st, bool init, int base) {
+                       int target_wgs, hipStream_t st, bool init, int base, const DenseLaunch* own) {
     const InstDesc* insts = tb.inst;
     const int ninst = tb.ninst;
     uint16_t* panel_hi = panel;
@@ -307,21 +340,21 @@ void launch_gemm_apply(const Tables& tb, const DenseBlock& db, int adj, int out,
     const int64_t off_in = adj ? db.row0 : db.col0;
     const int64_t off_out = adj ? db.col0 : db.row0;
     const GemmPlan g = gemm_plan(N, kpad, ninst, target_wgs);
-    const int kblocks = (int)((kpad + 255) / 256);
-    const int ninit = init ? (adj ? tb.nx_tiles : tb.ny_tiles) : 0;
-    k_gemm_pack<<<(unsigned)(kblocks * g.mpad + ninit), 256, 0, st>>>(
-        tb, ninst, adj, in, off_in, K, kpad, kblocks, g.mpad, panel_hi, panel_mid, panel_lo, out, base,
-        sigma, gate);
+    const int npack = (int)((kpad / 16 * (g.mpad / 32) + 3) / 4);   // (a wave per (tile, step))
+    const int ninit = !init ? 0 : own ? own->ninit : adj ? tb.nx_tiles : tb.ny_tiles;
+    k_gemm_pack<<<(unsigned)(npack + ninit), 256, 0, st>>>(
+        tb, ninst, adj, in, off_in, K, kpad, npack, g.mpad, panel_hi, panel_mid, panel_lo, out, base,
+        sigma, gate, own ? own->init : nullptr);
     dim3 gg((unsigned)g.ntiles, (unsigned)g.nsplit, (unsigned)(g.mpad / GEMM_TM));
     if (corr)
         k_gemm_bf16<1><<<gg, GEMM_NT, 0, st>>>(w_hi, w_lo, N, kpad, panel_hi, panel_mid, panel_lo,
-                                               g.ksteps_per_split, part, g.npad, g.mpad);
+                                               g.ksteps_per_split, part, g.npad, g.mpad, insts, ninst, gate);
     else
         k_gemm_bf16<0><<<gg, GEMM_NT, 0, st>>>(w_hi, w_lo, N, kpad, panel_hi, panel_mid, panel_lo,
-                                               g.ksteps_per_split, part, g.npad, g.mpad);
+                                               g.ksteps_per_split, part, g.npad, g.mpad, insts, ninst, gate);
     dim3 rg((unsigned)((N + 255) / 256), (unsigned)ninst);
-    k_gemm_reduce<<<rg, 256, 0, st>>>(insts, ninst, adj, out, off_out, N, part, g.nsplit, g.npad, g.mpad,
-                                      sigma * db.scale, gate);
+    k_gemm_reduce<<<rg, 256, 0, st>>>(insts, tb.ids, adj, out, in, base, off_out, N, part, g.nsplit, g.npad, g.mpad,
+                                      sigma, sigma * db.scale, gate, own != nullptr);
 }
 
 }  // namespace cgs

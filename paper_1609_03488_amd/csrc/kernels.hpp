@@ -261,9 +261,12 @@ size_t gemm_part_bytes(const GemmPlan& g);
 // A^T when adj), W in BF16 (plus refinement products when corr); panel holds
 // three mpad x kpad BF16 panels, part the split-K partials.  With init the
 // packing launch also writes the output's initial value (base + identity
-// blocks, as launch_apply_init) before the products are added.
+// blocks, as launch_apply_init) before the products are added; with own (the first
+// dense launch of a direction whose dense blocks own their ranges) only that of the
+// elements outside the blocks, and the reduce writes the block's range whole.
 void launch_gemm_apply(const Tables& tb, const DenseBlock& db, int adj, int out, int in, double sigma,
                        int gate, int corr, uint16_t* panel, size_t panel_stride, float* part,
-                       int target_wgs, hipStream_t st, bool init = false, int base = -1);
+                       int target_wgs, hipStream_t st, bool init = false, int base = -1,
+                       const DenseLaunch* own = nullptr);
 
 }  // namespace cgs

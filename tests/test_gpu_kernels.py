@@ -145,6 +145,36 @@ def test_fused_register_form_fp32_solves(n, k):
     assert abs(f[0] - f[1]) <= 1e-4 * f[0]
 
 
+# one row and column; K that is no whole vector, step or padding; tiles of 128 outputs and
+# one past; more instances than a 64-row tile, and identity blocks beside and across the block
+@pytest.mark.parametrize("m,n,batch", [(1, 1, 2), (7, 129, 3), (130, 33, 33), (100, 250, 65)])
+def test_batched_bf16_iterates(m, n, batch):
+    """BF16 products of a batch whose dense block is exact in BF16: the embedding state after
+    three steps (CG to 1e-6) agrees with the FP32 solver's, instance by instance.  Products
+    differ by rounding, 2^-24 of a sum of n terms; CG stops at 1e-6: 1e-4 bounds both."""
+    print("[case] batched bf16", m, n, batch, flush=True)
+    rng = np.random.default_rng(m + n)
+    A = rng.integers(-4, 5, (m, n)) / 4.0
+    r0, c0 = 2, 1
+    rows, cols = m + n + 5, n + 3
+    op = P.Operator(rows, cols).add_dense(r0, c0, A).add_identity(0, 0, min(rows, cols) - 1, -0.5)
+    op.add_identity(rows - cols, 0, cols, 1.0)
+    data = [(np.abs(rng.standard_normal(rows)) + 1.0, rng.standard_normal(cols)) for _ in range(batch)]
+    out = []
+    for prec in (P.BF16, P.FP32):
+        s = P.Solver(op, rows, [], P.Settings.make(precision=prec, normalize=0, cg_tol=0.0, cg_floor=1e-6,
+                                                   cg_max_iters=200, setup_tol=1e-6, setup_max_iters=2000),
+                     batch=batch)
+        for i, (b, c) in enumerate(data):
+            s.set_data(i, b, c)
+        s.iterate(3)
+        out.append([s.state(i) for i in range(batch)])
+    for x, y in zip(*out):
+        scale = max(1.0, np.abs(y[0]).max(), np.abs(y[1]).max(), np.abs(y[3]).max())
+        for j in (0, 1, 3):
+            assert np.abs(x[j] - y[j]).max() <= 1e-4 * scale
+
+
 # X vectors of one element a thread up to a whole tile (2048) and past it (launch by
 # launch); a limit of 1 and 3 iterations, and one above the single launch's
 @pytest.mark.parametrize("n,k,limit", [(20, 3, 2000), (256, 31, 2000), (600, 25, 1), (600, 25, 3), (600, 25, 16384),
