@@ -175,11 +175,22 @@ DEVI double sum_parts(const double* part, int t0, int t1, int j, double* sh) {
     return block_sum<NT>(s, sh);
 }
 
-// All four X-tile partial slots of the instance at once (sh: 4 * VEC_NT / 64).
-DEVI void inst_xsum4(const Tables& tb, const InstDesc& d, double (&s)[4], double* sh) {
+// The partials of k_cg_dot (Tables::cpart, a record per X tile) over the instance's
+// tiles; with start, also those of k_cg_init (slots 0 and 1 of Tables::spart: ||r||^2,
+// ||h||^2 of the CG start), all loaded in the same pass (sh: 6 * VEC_NT / 64 doubles).
+// (Not in xpart, where the update that ends CG leaves the projection's scalars.)
+DEVI void inst_xsum4(const Tables& tb, const InstDesc& d, double (&s)[4], bool start, double& h0, double& h1,
+                     double* sh) {
+    double a[6];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) s[j] = thread_sum<VEC_NT, 4>(tb.xpart + j, d.xt0, d.xt1, 4);
-    block_sum4<VEC_NT>(s, sh);
+    for (int j = 0; j < 4; ++j) a[j] = thread_sum<VEC_NT, 4>(tb.cpart + j, d.xt0, d.xt1, 4);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) a[4 + j] = start ? thread_sum<VEC_NT, 4>(tb.spart + j, d.xt0, d.xt1, 4) : 0.0;
+    block_sumN<VEC_NT, 6>(a, sh);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s[j] = a[j];
+    h0 = a[4];
+    h1 = a[5];
 }
 
 // The same over the partials of a CG step folded into the instance's A^T

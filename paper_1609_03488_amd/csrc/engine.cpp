@@ -903,7 +903,7 @@ void Engine::apply(int adj, int out, int in, int base, double sigma, int gate) {
 // One CG iteration of the Section IV-B listing on (I + A^T A):
 // q = p + A^T (A p); alpha = rr/<p,q>; z += alpha p; r -= alpha q; beta; p = r + beta p.
 void Engine::cg_iter(int z, int gate, int cg_max, int track, int it, int last, int start) {
-    if (start) {
+    if (start && folded_cg()) {
         // first iteration of an ADMM step on the folded path: the products run
         // whatever the CG start test says (a step without CG iterations is
         // rare) and the update evaluates the test from the right-hand side's
@@ -932,7 +932,11 @@ void Engine::cg_iter(int z, int gate, int cg_max, int track, int it, int last, i
         launch_cg_update(prec, T, z, XR, XR, XQ, it, cg_max, gate, track, stream, 1, last, cs);
         return;
     }
-    apply(0, YT, XP, -1, 1.0, gate);
+    // (the products of a step's first iteration run whatever the start test says)
+    const int pgate = start ? (int)G_ADMM : gate;
+    apply(0, YT, XP, -1, 1.0, pgate);
+    // on the ADMM path the update that ends CG also takes the tau products
+    const int tau = gate == G_ADMM_CG && track ? 1 : 0;
     if (folded_cg()) {
         // q = p + A^T (A p) with the dot partials and the iteration mark formed
         // as each element of q is written (the work of k_cg_dot)
@@ -943,15 +947,15 @@ void Engine::cg_iter(int z, int gate, int cg_max, int track, int it, int last, i
         c.fit = it;
         c.part = T.cpart;
         conv(c, 1, XQ, YT, XP, 1.0, gate);
-        // (on the ADMM path the update that ends CG also takes the tau products)
-        const int tau = gate == G_ADMM_CG && track ? 1 : 0;
         launch_cg_update(prec, T, z, XR, XP, XQ, it, cg_max, gate, track, stream, 1, last,
                          CgStart{0.0, 0.0, 0.0, 0, tau, tau, st.alpha});
         return;
     }
-    apply(1, XQ, YT, XP, 1.0, gate);
-    launch_cg_dot(prec, T, XP, XQ, XR, it, gate, stream);
-    launch_cg_update(prec, T, z, XR, XP, XQ, it, cg_max, gate, track, stream, 0, last);
+    apply(1, XQ, YT, XP, 1.0, pgate);
+    launch_cg_dot(prec, T, XP, XQ, XR, it, pgate, stream);
+    launch_cg_update(prec, T, z, XR, XP, XQ, it, cg_max, gate, track, stream, 0, last,
+                     start ? CgStart{st.cg_tol, st.cg_rate, cg_floor(), 1, tau, tau, st.alpha}
+                           : CgStart{0.0, 0.0, 0.0, 0, tau, tau, st.alpha});
 }
 
 // One ADMM step of the homogeneous self-dual embedding.  The CG warm start z
@@ -972,23 +976,14 @@ void Engine::admm_step() {
         c.part = T.spart;
         c.idrows = idrows ? YT + 1 : 0;
         conv(c, 1, XH, YW, XU, -1.0, G_ADMM);
-        const int nl = std::max(1, cg_launch);
-        for (int i = 0; i < nl; ++i)
-            cg_iter(XZ, G_ADMM_CG, st.cg_max_iters, 1, i, spec_now && i == nl - 1, i == 0);
     } else {
         apply(1, XH, YW, XU, -1.0, G_ADMM);                      // h = u_x - A^T w_y
-        launch_cg_init(prec, T, XZ, XR, XP, XK, XH, 1, st.cg_tol, st.cg_rate, cg_floor(),
-                       st.cg_max_iters, G_ADMM, stream);         // r = h - K z
-        for (int i = 0; i < cg_launch; ++i)
-            cg_iter(XZ, G_ADMM_CG, st.cg_max_iters, 1, i, spec_now && i == cg_launch - 1);
+        launch_cg_start(prec, T, XZ, XR, XP, XK, XH, G_ADMM, stream);   // r = h - K z
     }
-    if (folded_cg()) {
-        // z_y, the tau products and the cone terms came from the last CG update
-        launch_project(prec, T, st.alpha, stream);               // relax, project, dual update
-        return;
-    }
-    // z_y = w_y + A z; c^T z_x + b^T z_y; the cone terms of u_bar - v (CgStart::cone)
-    launch_tau_dots(prec, T, st.alpha, stream);
+    const int nl = std::max(1, cg_launch);
+    for (int i = 0; i < nl; ++i)
+        cg_iter(XZ, G_ADMM_CG, st.cg_max_iters, 1, i, spec_now && i == nl - 1, i == 0);
+    // the tau products and the cone terms came from the update that ended CG
     launch_project(prec, T, st.alpha, stream);                   // relax, project, dual update
 }
 

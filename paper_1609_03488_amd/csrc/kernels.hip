@@ -330,8 +330,7 @@ __global__ __launch_bounds__(GEMV_NT) void k_gemv(Tables tb, DenseLaunch dl, int
 // ---------------------------------------------------------------- CG
 template <typename T>
 __global__ __launch_bounds__(VEC_NT) void k_cg_init(Tables tb, int z, int r, int p, int q, int h,
-                                                    int have_q, double zeta, double rate,
-                                                    double floor_, int cg_max, int gate) {
+                                                    int have_q, int gate, double* parts) {
     __shared__ double sh[VEC_NT / 64];
     const VecTile tl = tb.xt[blockIdx.x];
     const InstDesc d = tb.inst[tl.inst];
@@ -352,7 +351,7 @@ __global__ __launch_bounds__(VEC_NT) void k_cg_init(Tables tb, int z, int r, int
     }
     s0 = block_sum<VEC_NT>(s0, sh);
     s1 = block_sum<VEC_NT>(s1, sh);
-    double* part = tb.xpart + 4 * (int64_t)blockIdx.x;
+    double* part = parts + 4 * (int64_t)blockIdx.x;
     if (threadIdx.x == 0) {
         part[0] = s0;
         part[1] = s1;
@@ -384,7 +383,7 @@ __global__ __launch_bounds__(VEC_NT) void k_cg_dot(Tables tb, int p, int q, int 
     }
     block_sum4<VEC_NT>(s, sh);
     if (threadIdx.x == 0) {
-        double* part = tb.xpart + 4 * (int64_t)blockIdx.x;
+        double* part = tb.cpart + 4 * (int64_t)blockIdx.x;
         part[0] = s[0];
         part[1] = s[1];
         part[2] = s[2];
@@ -573,7 +572,7 @@ __global__ __launch_bounds__(VEC_NT) void k_cg_update(Tables tb, int z, int r, i
     double s[4];
     double h0 = 0.0, h1 = 0.0;
     if (folded) inst_csum4(tb, d, s, cs.on != 0, h0, h1, sh);   // partials of the A^T launch(es)
-    else inst_xsum4(tb, d, s, sh);                              // partials of k_cg_dot
+    else inst_xsum4(tb, d, s, cs.on != 0, h0, h1, sh);          // partials of k_cg_dot
     double tol;
     if (cs.on) {
         // the step's CG start test, from the right-hand side launch's partials
@@ -619,7 +618,7 @@ __global__ __launch_bounds__(VEC_NT) void k_cg_update(Tables tb, int z, int r, i
         if (last && more) sc[SC_PHASE] = 3.0;
         sc[SC_CGACT] = more ? 1.0 : 0.0;
     }
-    // the step's last CG update also does the work of k_tau_dots on the final
+    // the step's last CG update also forms the tau products on the final
     // z and A z (cs.tau: every instance's CG ends in an update of this loop)
     const bool tw = cs.tau && !more;
     if ((!ok || (xt.is_y && !track)) && !tw) return;
@@ -636,22 +635,6 @@ __global__ __launch_bounds__(VEC_NT) void k_wy(Tables tb, int gate) {
     gptr<T> w = yvec<T>(d, YW);
     for (int64_t i = tl.start + threadIdx.x; i < tl.start + tl.len; i += VEC_NT)
         w[i] = (T)((double)u[i] + (double)v[i]);
-}
-
-// The products of u~_tau = (w_tau + c^T z_x + b^T z_y) / eta (exact solve of
-// (I+Q) u~ = w, last row) after CG, on the one-launch-per-kernel path: the
-// partials of c^T z_x and b^T z_y (z_y = w_y + carried A z), and the cone terms
-// of the projection (the work the update that ends CG does on the folded path,
-// with z and A z as CG left them; CgStart::cone)
-template <typename T>
-__global__ __launch_bounds__(VEC_NT) void k_tau_dots(Tables tb, double alpha) {
-    __shared__ double sh[4 * (VEC_NT / 64)];
-    const XYTile xt = xy_tile(tb);
-    const InstDesc d = tb.inst[xt.t.inst];
-    gptr<double> sc = scal(d);
-    if (!gate_ok(sc, G_ADMM)) return;
-    const CgStart cs{0.0, 0.0, 0.0, 0, 1, 1, alpha};
-    cg_elems<T>(tb, d, xt, sc, cs, false, 0.0, 0.0, false, false, true, XZ, XR, XP, XQ, sh);
 }
 
 // A thread's elements of a Y tile of u_y, A z, g_y, v_s, loaded at once
@@ -1266,9 +1249,11 @@ void launch_gemv(int prec, const Tables& t, const DenseLaunch& d, int adj, int o
 }
 void launch_cg_init(int prec, const Tables& t, int z, int r, int p, int q, int h, int have_q,
                     double zeta, double rate, double floor_, int cg_max, int gate, hipStream_t st) {
-    CGS_DISPATCH(prec, k_cg_init, t.nx_tiles, VEC_NT, st, t, z, r, p, q, h, have_q, zeta, rate,
-                 floor_, cg_max, gate);
+    CGS_DISPATCH(prec, k_cg_init, t.nx_tiles, VEC_NT, st, t, z, r, p, q, h, have_q, gate, t.xpart);
     k_finalize<<<t.ninst, VEC_NT, 0, st>>>(t, FIN_CG_INIT, gate, FinArgs{zeta, rate, floor_, cg_max, 0});
+}
+void launch_cg_start(int prec, const Tables& t, int z, int r, int p, int q, int h, int gate, hipStream_t st) {
+    CGS_DISPATCH(prec, k_cg_init, t.nx_tiles, VEC_NT, st, t, z, r, p, q, h, 1, gate, t.spart);
 }
 void launch_cg_dot(int prec, const Tables& t, int p, int q, int r, int it, int gate, hipStream_t st) {
     CGS_DISPATCH(prec, k_cg_dot, t.nx_tiles, VEC_NT, st, t, p, q, r, it, gate);
@@ -1285,9 +1270,6 @@ void launch_snapshot(int prec, const Tables& t, int restore, hipStream_t st) {
 }
 void launch_wy(int prec, const Tables& t, int gate, hipStream_t st) {
     CGS_DISPATCH(prec, k_wy, t.ny_tiles, VEC_NT, st, t, gate);
-}
-void launch_tau_dots(int prec, const Tables& t, double alpha, hipStream_t st) {
-    CGS_DISPATCH(prec, k_tau_dots, t.nx_tiles + t.ny_tiles, VEC_NT, st, t, alpha);
 }
 void launch_project(int prec, const Tables& t, double alpha, hipStream_t st) {
     CGS_DISPATCH(prec, k_project, t.nx_tiles + t.ny_tiles, VEC_NT, st, t, alpha);

@@ -86,6 +86,9 @@ void launch_gemv(int prec, const Tables& t, const DenseLaunch& d, int adj, int o
 //       tol = ||h|| * max(floor, zeta / (k+1)^rate), CG active iff ||r|| > tol.
 void launch_cg_init(int prec, const Tables& t, int z, int r, int p, int q, int h, int have_q,
                     double zeta, double rate, double floor, int cg_max, int gate, hipStream_t st);
+// The same for an ADMM step, whose first update takes the start test (CgStart):
+// r = h - q, p = r, partials of ||r||^2 and ||h||^2 to Tables::spart.
+void launch_cg_start(int prec, const Tables& t, int z, int r, int p, int q, int h, int gate, hipStream_t st);
 // partials of <p, q>, ||r||^2, <r, q>, ||q||^2; marks iteration `it` as in progress
 void launch_cg_dot(int prec, const Tables& t, int p, int q, int r, int it, int gate, hipStream_t st);
 // alpha = ||r||^2 / <p, q>; z += alpha p; r -= alpha q; beta = ||r'||^2 / ||r||^2
@@ -93,15 +96,16 @@ void launch_cg_dot(int prec, const Tables& t, int p, int q, int r, int it, int g
 // p = r' + beta p while CG goes on.
 // track = 1: also K z += alpha q and A z += alpha (A p) (carried products)
 // `it`: CG iteration of the current loop (must match the preceding launch_cg_dot)
-// The CG start test evaluated by the first update of a step (folded path: the
-// right-hand side's partials are in Tables::spart and the first iteration's
-// products ran ungated)
+// The CG start test evaluated by the first update of a step: the right-hand side's
+// partials are in Tables::spart, and the first iteration's products ran whatever its
+// outcome (a step whose CG makes no iteration is rare).  Two launches a step fewer, at
+// 5 us each, than with the test and the tau products in launches of their own.
 struct CgStart {
     double zeta, rate, floor_;
     int on;
     // 1: the update in which an instance's CG ends also does the work of
-    // launch_tau_dots on the final z and A z (folded ADMM path,
-    // where some update of the loop always runs)
+    // the tau products c^T z_x and b^T z_y (z_y = w_y + A z) on the final z and A z
+    // (ADMM path, where some update of the loop always runs)
     int tau;
     // with tau: that update also forms the cone terms of the projection that
     // follows (launch_project): relative to
@@ -134,10 +138,6 @@ void launch_snapshot(int prec, const Tables& t, int restore, hipStream_t st);
 // ---- ADMM step pieces (Section V-B: subspace projection, then cone projection)
 // w_y = u_y + v_s
 void launch_wy(int prec, const Tables& t, int gate, hipStream_t st);
-// after CG on the one-launch-per-kernel path: the partials of c^T z_x and
-// b^T z_y, z_y = w_y + (carried A z) formed and not stored, and the cone terms
-// of CgStart::cone (the work the update that ends CG does on the folded path)
-void launch_tau_dots(int prec, const Tables& t, double alpha, hipStream_t st);
 // relaxation, projection onto K, dual update of every X/Y entry: every
 // workgroup forms u~_tau = (tau + kappa + c^T z_x + b^T z_y) / eta from the tau
 // products' partials and the cone norms from the cone terms (CgStart::cone)

@@ -145,6 +145,36 @@ def test_fused_register_form_fp32_solves(n, k):
     assert abs(f[0] - f[1]) <= 1e-4 * f[0]
 
 
+# CG start tests that always end a step's CG before its first iteration, that do so for
+# some steps, and never; one X tile, several, and a batch
+@pytest.mark.parametrize("n,k,batch", [(300, 31, 3), (2500, 41, 1)])
+@pytest.mark.parametrize("cg_tol", [1e3, 0.3, 1e-9])
+def test_steps_without_cg_iterations(n, k, batch, cg_tol):
+    """FP64: 12 steps of the launch-by-launch path, whose first update takes the start test,
+    against the fused path's, which tests before it iterates: equal counts of CG iterations,
+    and the state to 1e-9 of its size (sums differ in order only)."""
+    import workloads as w
+    print("[case] steps without CG iterations", n, k, batch, cg_tol, flush=True)
+    d = w.deconv_instance(n, k, k / 7.0, 0.1, 1e-4, n)
+    pr = P.deconv_problem(d["c"], d["b"])
+    out = []
+    for fused in (0, 65536):
+        s = P.Solver(pr.op, pr.l, pr.q, P.Settings.make(precision=P.FP64, cg_tol=cg_tol, cg_floor=1e-12, setup_tol=1e-13,
+                                                        cg_max_iters=60, setup_max_iters=2000, fused_max=fused,
+                                                        fused_lone_max=0), batch=batch)
+        for i in range(batch):
+            s.set_data(i, pr.b * (1.0 + i), pr.c)
+        s.iterate(0)
+        its0 = [r["cg_iters"] for r in s.residuals()]
+        s.iterate(12)
+        out.append(([r["cg_iters"] - i0 for r, i0 in zip(s.residuals(), its0)], [s.state(i) for i in range(batch)]))
+    assert out[0][0] == out[1][0] and (cg_tol < 1e3) == (min(out[0][0]) > 0)
+    for x, y in zip(out[0][1], out[1][1]):
+        scale = max(1.0, np.abs(y[0]).max(), np.abs(y[1]).max(), np.abs(y[3]).max())
+        for j in (0, 1, 3):
+            assert np.abs(x[j] - y[j]).max() <= 1e-9 * scale
+
+
 # one row and column; K that is no whole vector, step or padding; tiles of 128 outputs and
 # one past; more instances than a 64-row tile, and identity blocks beside and across the block
 @pytest.mark.parametrize("m,n,batch", [(1, 1, 2), (7, 129, 3), (130, 33, 33), (100, 250, 65)])
