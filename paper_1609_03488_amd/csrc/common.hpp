@@ -136,6 +136,18 @@ struct VecTile {
     int32_t pad;
 };
 
+// A piece of a vector tile outside every owned output range (an initialisation tile that
+// rides on a product's launch), in half a VecTile's bytes: a range inside a tile leaves
+// two, and the tables stay within the bytes of the whole tiles.
+struct InitPiece {
+    int32_t inst;
+    uint32_t start_lo;
+    uint16_t start_hi, len;   // len <= VEC_TILE
+    __host__ __device__ VecTile tile() const {
+        return VecTile{inst, -1, (int64_t)start_hi << 32 | start_lo, len, 0};
+    }
+};
+
 struct SocSeg {
     int32_t inst;
     int32_t ntiles;      // Y tiles covering the segment
@@ -190,12 +202,10 @@ struct DenseBlock {      // rows x cols block
     int32_t pad_;
 };
 
-struct DenseTile {       // `nr` rows of the (possibly transposed) block from r0
+struct DenseTile {       // rows from t * dense_tile_rows of the (possibly transposed) block
     int32_t inst;
     int32_t blk;
-    int64_t r0;
-    int32_t nr;
-    int32_t pad;
+    uint32_t t;
 };
 
 struct Tables {
@@ -230,8 +240,12 @@ constexpr int CONV_KC_MAX_F64 = 1024;
 constexpr int CONV_R_F32 = 8;        // taps are padded to a multiple of this
 constexpr int CONV_R_F64 = 4;
 // rows per tile of the dense products: a block's rows over 1024 workgroups (four to a
-// CU, each streaming its rows), at most DENSE_ROWS_MAX
+// CU, each streaming its rows), at least two (the tables' bytes), at most DENSE_ROWS_MAX
 constexpr int DENSE_TILES = 1024, DENSE_ROWS_MAX = 16;
+__host__ __device__ inline int64_t dense_tile_rows(int64_t rows) {
+    const int64_t nr = (rows + DENSE_TILES - 1) / DENSE_TILES;
+    return nr < 2 ? 2 : nr < DENSE_ROWS_MAX ? nr : DENSE_ROWS_MAX;
+}
 constexpr int FFT_L = 2048;          // points per transform of the FFT convolution engine
 constexpr int FFT_KMAX = 1536;       // longest kernel it takes (>= 513 outputs per window)
 

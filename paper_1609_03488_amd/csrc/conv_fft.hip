@@ -328,7 +328,7 @@ __global__ __launch_bounds__(FT) void k_conv_fft(Tables tb, ConvLaunch cl, int a
     // one's loads, such a tile was the longest chain of most launches.
     const int t = threadIdx.x;
     const bool init = bid >= cl.nftiles;
-    const VecTile it = init ? cl.init[bid - cl.nftiles] : VecTile{};
+    const VecTile it = init ? cl.init[bid - cl.nftiles].tile() : VecTile{};
     const ConvTile tl = init ? ConvTile{it.inst, 0, 0} : cl.ftiles[bid];
     const InstDesc d = tb.inst[tl.inst];
     ConvBlock cb{};

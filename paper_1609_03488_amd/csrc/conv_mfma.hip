@@ -38,7 +38,7 @@ __global__ __launch_bounds__(CM_NT) void k_conv_mfma(Tables tb, ConvLaunch cl, i
                                                      int base, double sigma, int gate) {
     extern __shared__ __align__(16) unsigned char cm_smem[];
     if ((int)blockIdx.x >= cl.ntiles) {   // initialisation tiles riding on the launch
-        const VecTile it = cl.init[blockIdx.x - cl.ntiles];
+        const VecTile it = cl.init[blockIdx.x - cl.ntiles].tile();
         const InstDesc di = tb.inst[it.inst];
         if (gate_ok(scal(di), gate)) init_tile<float>(tb, di, it, adj, out, in, base, sigma, false);
         return;

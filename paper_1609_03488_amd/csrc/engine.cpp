@@ -481,12 +481,56 @@ void build_image(const std::vector<InstRec>& recs, int precision, TableImage& im
             im.dblk.push_back(db);
             for (int adj = 0; adj < 2; ++adj) {
                 const int64_t rows = adj ? db.cols : db.rows;
-                const int64_t nr = std::min<int64_t>(DENSE_ROWS_MAX, (rows + DENSE_TILES - 1) / DENSE_TILES);
-                for (int64_t s = 0; s < rows; s += nr)
-                    (adj ? im.dadj : im.dfwd)[j].push_back(DenseTile{ii, bi, s, (int32_t)std::min(nr, rows - s), 0});
+                const int64_t nt = (rows + dense_tile_rows(rows) - 1) / dense_tile_rows(rows);
+                for (int64_t t = 0; t < nt; ++t)
+                    (adj ? im.dadj : im.dfwd)[j].push_back(DenseTile{ii, bi, (uint32_t)t});
             }
         }
         im.inst.push_back(d);
+    }
+    // When every convolution owns its output range in a direction, the output
+    // initialisation rides on the first convolution launch as extra
+    // workgroups (one launch fewer per apply); tiles wholly inside an owned
+    // range need no initialisation at all.
+    // The same for the dense blocks of tables without a convolution (own_dense).
+    for (int adj = 0; adj < 2; ++adj) {
+        const bool conv = !(adj ? im.cadj : im.cfwd).empty();
+        if (!conv && im.dblk.empty()) continue;
+        bool all = true;
+        if (conv)
+            for (const ConvBlock& cb : im.cblk) all = all && ((cb.own >> adj) & 1);
+        else
+            for (const DenseBlock& db : im.dblk) all = all && ((db.own >> adj) & 1);
+        if (!all) continue;
+        for (const VecTile& t : adj ? im.xt : im.yt) {
+            const InstDesc& d = im.inst[t.inst];
+            // the pieces of the tile outside every owned range
+            std::vector<std::pair<int64_t, int64_t>> own;
+            for (int b = d.cb0; b < d.cb1; ++b) {
+                const ConvBlock& cb = im.cblk[b];
+                const int64_t lo = adj ? cb.col0 : cb.row0;
+                own.emplace_back(lo, lo + (adj ? cb.n_in : cb.n_in + cb.k - 1));
+            }
+            for (int b = d.db0; !conv && b < d.db1; ++b) {
+                const DenseBlock& db = im.dblk[b];
+                const int64_t lo = adj ? db.col0 : db.row0;
+                own.emplace_back(lo, lo + (adj ? db.cols : db.rows));
+            }
+            std::sort(own.begin(), own.end());
+            int64_t pos = t.start;
+            const int64_t end = t.start + t.len;
+            auto piece = [&](int64_t to) {
+                if (to > pos)
+                    im.init[adj].push_back(InitPiece{t.inst, (uint32_t)pos, (uint16_t)(pos >> 32), (uint16_t)(to - pos)});
+            };
+            for (const auto& r : own) {
+                if (r.second <= pos || r.first >= end) continue;
+                piece(r.first);
+                pos = std::max(pos, r.second);
+            }
+            piece(end);
+        }
+        im.all_own[adj] = 1;
     }
 }
 
@@ -502,23 +546,20 @@ size_t image_table_bytes(const TableImage& im) {
     for (const auto& v : im.fadj) t += vbytes(v);
     for (const auto& v : im.dfwd) t += vbytes(v);
     for (const auto& v : im.dadj) t += vbytes(v);
-    // initialisation tiles folded into convolution or dense launches: the tiles
-    // outside owned ranges, and one more piece for a range inside a tile
-    t += vbytes(im.xt) + vbytes(im.yt) + 2 * vbytes(im.cblk) + 2 * vbytes(im.dblk);
-    return t + 256;
+    return t + vbytes(im.init[0]) + vbytes(im.init[1]);
 }
 
 // most workgroups of a folded A^T launch: transforms and initialisation tiles
 static size_t folded_wgs(const TableImage& im) {
-    return (im.fadj.empty() ? 0 : im.fadj[0].size()) + im.xt.size() + im.cblk.size();
+    return (im.fadj.empty() ? 0 : im.fadj[0].size()) + std::max(im.xt.size(), im.init[1].size());
 }
 
 size_t image_work_bytes(const TableImage& im) {
     const size_t nfa = folded_wgs(im);
     return align256(4 * im.xt.size() * 8) + align256(4 * im.yt.size() * 8) +
            align256(2 * im.seg.size() * 8) + align256(im.seg.size() * 4) +
-           2 * align256(4 * nfa * 8) + align256(4 * (im.xt.size() + im.yt.size()) * 8) +
-           align256(im.inst.size() * NSC * 8) + 256;
+           2 * align256(4 * nfa * 8) + align256((im.xt.size() + 4 * im.yt.size()) * 8) +
+           align256(im.inst.size() * NSC * 8);
 }
 
 // ---------------------------------------------------------------- engine
@@ -651,50 +692,10 @@ int Engine::build(const std::vector<InstRec>& r) {
             fused_res = std::max(fused_res, fused_resident_bytes(prec, d.n, d.m));
         }
     }
-    // When every convolution owns its output range in a direction, the output
-    // initialisation rides on the first convolution launch as extra
-    // workgroups (one launch fewer per apply); tiles wholly inside an owned
-    // range need no initialisation at all.
-    // The same for the dense blocks of tables without a convolution (own_dense).
-    std::vector<VecTile> init_tiles[2];
     for (int adj = 0; adj < 2; ++adj) {
-        fold_init[adj] = own_dense[adj] = 0;
         const bool conv = !(adj ? im.cadj : im.cfwd).empty();
-        if (!conv && im.dblk.empty()) continue;
-        bool all = true;
-        if (conv)
-            for (const ConvBlock& cb : im.cblk) all = all && ((cb.own >> adj) & 1);
-        else
-            for (const DenseBlock& db : im.dblk) all = all && ((db.own >> adj) & 1);
-        if (!all) continue;
-        for (const VecTile& t : adj ? im.xt : im.yt) {
-            const InstDesc& d = im.inst[t.inst];
-            // the pieces of the tile outside every owned range
-            std::vector<std::pair<int64_t, int64_t>> own;
-            for (int b = d.cb0; b < d.cb1; ++b) {
-                const ConvBlock& cb = im.cblk[b];
-                const int64_t lo = adj ? cb.col0 : cb.row0;
-                own.emplace_back(lo, lo + (adj ? cb.n_in : cb.n_in + cb.k - 1));
-            }
-            for (int b = d.db0; !conv && b < d.db1; ++b) {
-                const DenseBlock& db = im.dblk[b];
-                const int64_t lo = adj ? db.col0 : db.row0;
-                own.emplace_back(lo, lo + (adj ? db.cols : db.rows));
-            }
-            std::sort(own.begin(), own.end());
-            int64_t pos = t.start;
-            const int64_t end = t.start + t.len;
-            auto piece = [&](int64_t to) {
-                if (to > pos) init_tiles[adj].push_back(VecTile{t.inst, t.seg, pos, (int32_t)(to - pos), 0});
-            };
-            for (const auto& r : own) {
-                if (r.second <= pos || r.first >= end) continue;
-                piece(r.first);
-                pos = std::max(pos, r.second);
-            }
-            piece(end);
-        }
-        (conv ? fold_init : own_dense)[adj] = 1;
+        fold_init[adj] = conv && im.all_own[adj];
+        own_dense[adj] = !conv && im.all_own[adj];
     }
     // CG steps fold into the FFT engine's A^T launch when that launch (its
     // transform workgroups and its initialisation workgroups) writes every X
@@ -740,8 +741,8 @@ int Engine::build(const std::vector<InstRec>& r) {
             if (d.cp1 == 0) d.cp0 = i;
             d.cp1 = i + 1;
         }
-        for (int i = 0; i < (int)init_tiles[1].size(); ++i) {
-            InstDesc& d = im.inst[init_tiles[1][i].inst];
+        for (int i = 0; i < (int)im.init[1].size(); ++i) {
+            InstDesc& d = im.inst[im.init[1][i].inst];
             if (d.ip1 == 0) d.ip0 = nft + i;
             d.ip1 = nft + i + 1;
         }
@@ -821,8 +822,8 @@ int Engine::build(const std::vector<InstRec>& r) {
     for (int adj = 0; adj < 2; ++adj) {
         std::vector<ConvLaunch>& cl = adj ? ca : cf;
         if (!fold_init[adj] || cl.empty()) continue;
-        cl[0].init = (const VecTile*)put(init_tiles[adj].data(), init_tiles[adj].size() * sizeof(VecTile));
-        cl[0].ninit = (int)init_tiles[adj].size();
+        cl[0].init = (const InitPiece*)put(im.init[adj].data(), im.init[adj].size() * sizeof(InitPiece));
+        cl[0].ninit = (int)im.init[adj].size();
     }
     for (int adj = 0; adj < 2; ++adj) {
         const int64_t w = precision == CGS_FP64 ? 2 : 4;   // elements of a 16-byte vector
@@ -834,8 +835,8 @@ int Engine::build(const std::vector<InstRec>& r) {
         }
         std::vector<DenseLaunch>& dl = adj ? da : df;
         if (!own_dense[adj] || dl.empty()) continue;
-        dl[0].init = (const VecTile*)put(init_tiles[adj].data(), init_tiles[adj].size() * sizeof(VecTile));
-        dl[0].ninit = (int)init_tiles[adj].size();
+        dl[0].init = (const InitPiece*)put(im.init[adj].data(), im.init[adj].size() * sizeof(InitPiece));
+        dl[0].ninit = (int)im.init[adj].size();
     }
     if (off > tab_cap) return fail(CGS_ENOMEM, "table overflow");
     CGS_HIP(hipMemcpyAsync(tab_dev, tab_host, off, hipMemcpyHostToDevice, stream));
@@ -846,7 +847,7 @@ int Engine::build(const std::vector<InstRec>& r) {
     T.seg_cnt = (int*)w; w += align256(im.seg.size() * 4);
     T.cpart = (double*)w; w += align256(4 * folded_wgs(im) * 8);
     T.spart = (double*)w; w += align256(4 * folded_wgs(im) * 8);
-    T.tpart = (double*)w; w += align256(4 * (im.xt.size() + im.yt.size()) * 8);
+    T.tpart = (double*)w; w += align256((im.xt.size() + 4 * im.yt.size()) * 8);
     gather_dev = (double*)w;
     if (!im.seg.empty()) CGS_HIP(hipMemsetAsync(T.seg_cnt, 0, im.seg.size() * 4, stream));
     T.nx_tiles = (int)im.xt.size();

@@ -148,6 +148,9 @@ struct TableImage {
     std::vector<std::vector<ConvTile>> ffwd, fadj;   // the same slots as FFT-engine tiles
     std::vector<DenseBlock> dblk;
     std::vector<std::vector<DenseTile>> dfwd, dadj;  // per dense slot
+    // per direction: the blocks own their output ranges, and the pieces outside them
+    int all_own[2] = {0, 0};
+    std::vector<InitPiece> init[2];
 };
 // vec_tile: elements per X/Y vector tile, VEC_TILE_MIN..VEC_TILE
 void build_image(const std::vector<InstRec>& recs, int precision, TableImage& im, int vec_tile = VEC_TILE);

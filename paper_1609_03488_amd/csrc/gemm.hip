@@ -63,10 +63,10 @@ DEVI int64_t packed_index(int64_t row, int64_t k, int64_t ksteps) {
 __global__ __launch_bounds__(256) void k_gemm_pack(Tables tb, int ninst, int adj, int in, int64_t off,
                                                     int64_t K, int64_t kpad, int npack, int mpad,
                                                     uint16_t* hi, uint16_t* mid, uint16_t* lo, int out,
-                                                    int base, double sigma, int gate, const VecTile* init) {
+                                                    int base, double sigma, int gate, const InitPiece* init) {
     if ((int)blockIdx.x >= npack) {
         const int t = (int)blockIdx.x - npack;
-        const VecTile tl = init ? init[t] : adj ? tb.xt[t] : tb.yt[t];
+        const VecTile tl = init ? init[t].tile() : adj ? tb.xt[t] : tb.yt[t];
         const InstDesc d = tb.inst[tl.inst];
         if (gate_ok(scal(d), gate)) init_tile<float>(tb, d, tl, adj, out, in, base, sigma, init == nullptr);
         return;

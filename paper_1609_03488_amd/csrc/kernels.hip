@@ -91,7 +91,7 @@ __global__ __launch_bounds__(CONV_NT) void k_conv(Tables tb, ConvLaunch cl, int 
         // initialisation tiles riding on the launch, in parts: a whole tile on one
         // wave is a chain of 12.5 us, longer than most launches of few tiles
         const int w = (int)blockIdx.x - cl.ntiles * sub, np = conv_init_parts(sub), len = VEC_TILE / np;
-        VecTile it = cl.init[w / np];
+        VecTile it = cl.init[w / np].tile();
         const int p0 = (w % np) * len;
         if (p0 >= it.len) return;
         it.start += p0;
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(GEMV_NT) void k_gemv(Tables tb, DenseLaunch dl, int
     constexpr int VW = Vec16<T>::W;
     __shared__ double part[DENSE_ROWS_MAX][GEMV_NT / 64];
     if ((int)blockIdx.x >= dl.ntiles) {
-        const VecTile it = dl.init[blockIdx.x - dl.ntiles];
+        const VecTile it = dl.init[blockIdx.x - dl.ntiles].tile();
         const InstDesc di = tb.inst[it.inst];
         // (two elements at a time: eight take 200 registers, half the products' waves)
         if (gate_ok(scal(di), gate)) init_tile<T, 2>(tb, di, it, adj, out, in, base, sigma, false);
@@ -251,11 +251,12 @@ __global__ __launch_bounds__(GEMV_NT) void k_gemv(Tables tb, DenseLaunch dl, int
     if (!gate_ok(scal(d), gate)) return;
     const int tid = threadIdx.x, wave = tid >> 6;
     const int64_t ld = adj ? db.ldt : db.ld, ncols = adj ? db.rows : db.cols;
-    const int64_t g0 = (adj ? db.col0 : db.row0) + tl.r0;   // the tile's first output
-    gptr<const T> arow = (gptr<const T>)(adj ? db.at : db.a) + tl.r0 * ld;
+    const int64_t rows = adj ? db.cols : db.rows, per = dense_tile_rows(rows), r0 = (int64_t)tl.t * per;
+    const int64_t g0 = (adj ? db.col0 : db.row0) + r0;   // the tile's first output
+    gptr<const T> arow = (gptr<const T>)(adj ? db.at : db.a) + r0 * ld;
     gptr<T> o = (adj ? xvec<T>(d, out) : yvec<T>(d, out)) + g0;
     gptr<const T> x = adj ? yvec<T>(d, in) + db.row0 : xvec<T>(d, in) + db.col0;
-    const int nr = tl.nr;   // <= DENSE_ROWS_MAX
+    const int nr = (int)(rows - r0 < per ? rows - r0 : per);   // <= DENSE_ROWS_MAX
     T v0 = T(0);            // thread r < nr: what row r holds besides the products
     if (tid < nr) v0 = own ? (T)owned_init<T>(d, tb.ids, adj, in, base, sigma, g0 + tid) : o[tid];
     const int64_t nvec = ncols / VW, jt = nvec * VW + tid;   // (jt: the thread's element past the vectors)
@@ -534,7 +535,7 @@ DEVI void cg_elems(const Tables& tb, const InstDesc& d, const XYTile& xt, gptr<c
         // (z_y is not stored: the projection forms it again from u_y, v_s and A z)
     }
     if (!tw) return;
-    const int64_t ntl = (int64_t)tb.nx_tiles + tb.ny_tiles, b = (int64_t)tb.nx_tiles + xt.index;
+    const int64_t ntl = tb.ny_tiles, b = (int64_t)tb.nx_tiles + xt.index;
     if (cone) {
         block_sum4<VEC_NT>(s, sh);
         if (threadIdx.x == 0) {
@@ -684,7 +685,7 @@ __global__ __launch_bounds__(VEC_NT) void k_project(Tables tb, double alpha) {
         // in one fixed order by every workgroup
         const double* xp0 = tb.xpart + 4 * (int64_t)d.xt0;
         const double e_pt = xp0[1], wtau = xp0[2];
-        const int64_t ntl = (int64_t)tb.nx_tiles + tb.ny_tiles;
+        const int64_t ntl = tb.ny_tiles;
         const double* ty = tb.tpart + tb.nx_tiles;   // slot 0 of the Y tiles
         double s[4] = {0.0, 0.0, 0.0, 0.0};
         s[0] = thread_sum<VEC_NT, 4>(tb.tpart, d.xt0, d.xt1, 1) + thread_sum<VEC_NT, 4>(ty, d.yt0, d.yt1, 1);

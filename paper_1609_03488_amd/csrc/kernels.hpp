@@ -18,7 +18,7 @@ struct ConvLaunch {
     // output-initialisation tiles run by workgroups ntiles.. of the same launch
     // (only when every convolution owns its output range in this direction, so
     // that the two kinds of workgroups write disjoint elements)
-    const VecTile* init;
+    const InitPiece* init;
     int ninit;
     // the same outputs as tiles of the FFT engine (two windows of FFT_L - k + 1
     // outputs each); fft = 1 when every block of the launch has spectra
@@ -52,7 +52,7 @@ struct DenseLaunch {
     int64_t vecs;    // 16-byte vectors of the longest row of the launch's blocks
     // initialisation tiles of the output elements no dense block writes, run by
     // workgroups ntiles.. (only in a launch whose blocks own their outputs)
-    const VecTile* init;
+    const InitPiece* init;
     int ninit;
 };
 
