@@ -173,7 +173,10 @@ typedef struct {
                               passes it stops there; only the host's decisions
                               (CG launches per step, a rerun, the end of the solve)
                               wait for the end of the batch of intervals.  Results
-                              do not depend on it.  A server always uses 1.         */
+                              do not depend on it.  A server always uses 1.  Where
+                              every instance is small enough for the fused steps'
+                              register form the host reads after at least 16
+                              intervals: that launch ends its solve by itself.      */
 } cgs_settings;
 
 /* Per-instance result. */

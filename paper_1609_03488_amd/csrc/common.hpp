@@ -40,8 +40,8 @@ enum YVec : int {
     YG,       // g_y
     YB,       // b
     YW,       // w_y = u_y + v_s
-    YZ,       // z_y = w_y + A z_x (stored by the fused kernel only; the other
-              // kernels form it from u_y, v_s and A z where they need it)
+    YZ,       // z_y = w_y + A z_x (stored by the fused kernel's general form only;
+              // the other kernels form it from u_y, v_s and A z where they need it)
     YT,       // scratch (A p, A u_x)
     YA,       // A z, carried through the CG updates
     YD,       // row scaling D of the equilibrated operator D A E
@@ -220,11 +220,11 @@ struct Tables {
     const struct DenseBlock* dblk;
     double* xpart;       // 4 per X tile
     double* ypart;       // 4 per Y tile
-    double* cpart;       // 4 per workgroup of the A^T convolution launch (folded CG products)
-    double* spart;       // the same for the right-hand side's A^T launch (folded CG start)
+    double* cpart;       // CG products: 4 per workgroup of the folded A^T launch, or per X tile (k_cg_dot)
+    double* spart;       // CG start: the same for the right-hand side's A^T launch, or k_cg_init's
     // slot-major partials of the update that ends CG for the projection that
-    // follows (CgStart::cone): tpart[j * (nx_tiles + ny_tiles) + b] for the
-    // workgroup b of an X-then-Y tile launch, slots 0 (tau products) to 3
+    // follows (CgStart::cone): slot 0 (tau products) of the X tiles, then slots 0 to 3
+    // of the Y tiles, tpart[nx_tiles + j * ny_tiles + tile]
     double* tpart;
     int nx_tiles, ny_tiles, nseg, ninst;
 };

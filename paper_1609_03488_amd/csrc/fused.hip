@@ -930,7 +930,7 @@ __global__ __launch_bounds__(FNT) void k_fused(Tables tb, FusedArgs fa) {
 // FP64 instances of the register form whose X vector is one vector tile: one workgroup
 // and one launch instead of four launches per iteration and a wait of the host after
 // every eight.  Bound by the serial chain of the products (6 us an iteration at n = 1000,
-// k = 101): a 100-step solve at that size 4.2 -> 3.6 ms.  Products as in fused_reg; the
+// k = 101): a 60-step solve at that size 4.2 -> 3.6 ms.  Products as in fused_reg; the
 // dot products and the update are those of k_cg_dot and k_cg_update, sum for sum
 // (256 threads over the tile, ||r'||^2 from the expansion), so the result is theirs.
 constexpr int DOT_NT = VEC_NT;
