@@ -376,7 +376,7 @@ int cgs::solver_create(const cgs_op* op, int64_t l, const int64_t* q, int64_t nq
     e.precision = st->precision;
     e.prec = cgs::work_prec(st->precision);
     e.st = *st;
-    e.stream = (hipStream_t)stream;
+    CGS_TRY(e.attach((hipStream_t)stream));
     e.cg_launch = st->cg_max_iters;
     e.vec_tile = st->vec_tile ? st->vec_tile : cgs::VEC_TILE;
     e.lone = batch == 1 ? 1 : 0;
@@ -957,7 +957,7 @@ int cgs_server_create(int64_t max_slots, const cgs_settings* st, void* workspace
     e.precision = st->precision;
     e.prec = cgs::work_prec(st->precision);
     e.st = *st;
-    e.stream = (hipStream_t)stream;
+    CGS_TRY(e.attach((hipStream_t)stream));
     e.st.cg_adaptive = 0;     // results must not depend on the other requests in the mix
     e.st.intervals_per_sync = 1;   // requests arrive and leave at every check
     e.per_interval = 1;

@@ -575,6 +575,13 @@ Engine::~Engine() {
     }
 }
 
+int Engine::attach(hipStream_t st) {
+    stream = st;
+    if (st != nullptr) CGS_HIP(hipStreamGetDevice(st, &device));
+    else CGS_HIP(hipGetDevice(&device));
+    return CGS_OK;
+}
+
 void Engine::drop_graph() {
     for (CachedGraph& g : graphs) {
         (void)hipGraphExecDestroy(g.exec);
@@ -677,7 +684,7 @@ int Engine::build(const std::vector<InstRec>& r) {
     }
     fused_res = fused_reg = setup_lds = 0;
     fused_general = 0;
-    const int64_t lds = n_fused ? fused_prepare() : 0;
+    const int64_t lds = fused_lds = n_fused ? fused_prepare(device) : 0;
     for (InstDesc& d : im.inst) {
         if (!d.fused) continue;
         const int v = fused_reg_variant(im, d, prec, lds);
@@ -1030,6 +1037,7 @@ void Engine::refresh() {
         fa.refresh = 1;
         fa.general = 1;   // (in the general form: the two forms' products are the same)
         fa.kc = fused_kc;
+        fa.lds_cap = fused_lds;
         launch_fused(prec, T, fa, stream);
     }
     if (n_multi) {
@@ -1052,6 +1060,7 @@ void Engine::fused_steps(int nsteps, int check) {
     fa.cg_max = st.cg_max_iters;
     fa.max_iters = st.max_iters;
     fa.kc = fused_kc;
+    fa.lds_cap = fused_lds;
     fa.res_want = fused_res;
     fa.general = fused_general;
     fa.reg_want = fused_reg;

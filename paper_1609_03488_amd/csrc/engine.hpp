@@ -167,6 +167,7 @@ class Engine {
     int prec = 1;                 // element type selector of the kernels
     cgs_settings st{};
     hipStream_t stream = nullptr;
+    int device = 0;               // the stream's device, which need not be a calling thread's current one
 
     char* tab_dev = nullptr;  size_t tab_cap = 0;
     char* work_dev = nullptr; size_t work_cap = 0;
@@ -205,6 +206,7 @@ class Engine {
     int n_fused = 0, n_multi = 0;
     int lone = 0;                // a solver with a single instance (fused_lone_max applies)
     int fused_kc = 8;
+    int64_t fused_lds = 0;        // dynamic LDS bytes a fused workgroup may take on `device`
     int64_t fused_res = 0;        // LDS bytes of the largest general fused instance's resident vectors
     int64_t fused_reg = 0;        // LDS bytes of the largest fused instance of the register form
     int fused_general = 0;        // some fused instance takes the general form
@@ -237,6 +239,7 @@ class Engine {
     int rounds_since_build = 0;   // a graph is captured only once the tables have held a round
 
     ~Engine();
+    int attach(hipStream_t st);   // the stream the handle's work goes to, and its device
     // host_doubles: doubles of the pinned staging buffer (at least stg_doubles)
     int init_host_buffers(size_t tab_bytes, int max_inst, int64_t stg_doubles, int64_t host_doubles);
     // Build and upload the tile tables of `recs`.

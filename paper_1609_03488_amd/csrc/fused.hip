@@ -1120,8 +1120,7 @@ int64_t fused_resident_bytes(int prec, int64_t n, int64_t m) {
     return b;
 }
 
-// Dynamic LDS per workgroup that the fused kernels may take on each device
-// (0: not yet queried; then what fits in the 64 KB that needs no attribute)
+// Dynamic LDS per workgroup that the fused kernels may take on each device (0: not yet queried)
 static std::atomic<int> g_fused_lds[64];   // (zero-initialised: static storage)
 
 static int fused_static_lds() {
@@ -1132,10 +1131,13 @@ static int fused_static_lds() {
     return b > 0 ? b : 1024;
 }
 
-int fused_prepare() {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 65536 - 1024;
+// (the kernels' attributes belong to the calling thread's current device)
+int fused_prepare(int dev) {
+    if (dev < 0 || dev >= 64) return 65536 - 1024;
     if (g_fused_lds[dev].load() == 0) {
+        int cur = dev;
+        (void)hipGetDevice(&cur);
+        if (cur != dev && hipSetDevice(dev) != hipSuccess) return 65536 - 1024;
         const int fixed = fused_static_lds();   // the kernels' own __shared__ arrays
         int v = 0;
         if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || v <= 0)
@@ -1150,19 +1152,18 @@ int fused_prepare() {
                  hipSuccess))
             dyn = 65536 - fixed;
         g_fused_lds[dev].store(dyn);   // (two threads that get here store the same value)
+        if (cur != dev) (void)hipSetDevice(cur);
     }
     return g_fused_lds[dev].load();
 }
 
 void launch_fused(int prec, const Tables& t, FusedArgs fa, hipStream_t st) {
     if (t.ninst <= 0) return;
-    int dev = 0;
-    const int known = (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) ? g_fused_lds[dev].load() : 0;
-    const int cap = known > 0 ? known : 65536 - 1024;
+    const int64_t cap = fa.lds_cap;
     fa.lds_conv = ((int64_t)fused_smem_bytes(prec, fa.kc) + 15) & ~int64_t(15);
     if (!fa.general) fa.lds_conv = 0;
-    fa.lds_res = std::max<int64_t>(0, std::min<int64_t>(fa.res_want, (int64_t)cap - fa.lds_conv));
-    fa.lds_reg = std::min<int64_t>(std::max(fa.reg_want, fa.lds_conv + fa.lds_res), cap);
+    fa.lds_res = std::max<int64_t>(0, std::min<int64_t>(fa.res_want, cap - fa.lds_conv));
+    fa.lds_reg = std::min(std::max(fa.reg_want, fa.lds_conv + fa.lds_res), cap);
     const size_t lds = (size_t)std::max(fa.lds_conv + fa.lds_res, fa.lds_reg);
     if (prec == 0) k_fused<double><<<t.ninst, FNT, lds, st>>>(t, fa);
     else k_fused<float><<<t.ninst, FNT, lds, st>>>(t, fa);

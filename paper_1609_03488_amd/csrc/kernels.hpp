@@ -203,6 +203,7 @@ struct FusedArgs {
     // set by launch_fused: LDS bytes of the convolution's staging area, and
     // the bytes after it that hold an instance's most used vectors
     int64_t lds_conv, lds_res;
+    int64_t lds_cap;    // dynamic LDS bytes a workgroup may take on the stream's device (fused_prepare)
     int64_t res_want;   // bytes those vectors of the largest instance take (0: none)
     int general;        // some instance takes the general form
     int64_t reg_want;   // LDS bytes of the largest instance of the register form (0: none)
@@ -237,9 +238,10 @@ size_t fused_smem_bytes(int prec, int kc);
 // bytes that every resident-vector candidate of an instance with n variables
 // and m rows takes in LDS (16-byte aligned each)
 int64_t fused_resident_bytes(int prec, int64_t n, int64_t m);
-// queries the device's LDS per workgroup and lets the fused kernels take it
-// (once per device, outside any stream capture); returns that limit
-int fused_prepare();
+// queries the LDS per workgroup of device dev (whatever device is current) and lets the
+// fused kernels take it (once per device, outside any stream capture); returns that limit,
+// by which an instance's form is chosen and which every launch gets as FusedArgs::lds_cap
+int fused_prepare(int dev);
 void launch_fused(int prec, const Tables& t, FusedArgs fa, hipStream_t st);
 
 // ---- batched dense applies as BF16 MFMA GEMMs (gemm.hip)

@@ -1,0 +1,117 @@
+"""What the library's host code launches, on the CPU: fake_hip.cpp stands in for the HIP
+runtime, with several devices, in a process of its own (no PyTorch, whose runtime would be
+loaded otherwise).  Each scenario runs in a child and prints its launches."""
+import ctypes as C
+import json
+import os
+import re
+import subprocess
+import sys
+import types
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+DOUBLES = 32            # scalars of an instance, in the order of enum Scal
+
+
+class Fake:
+    """The fake runtime and the library bound to it; `launches` of the calls made."""
+
+    def __init__(self, path):
+        self.hip = C.CDLL(path, mode=C.RTLD_GLOBAL)
+        sys.modules["torch"] = types.ModuleType("torch")
+        sys.modules["torch"].Tensor = type("Tensor", (), {})
+        sys.path.insert(0, ROOT)
+        import paper_1609_03488_amd as P
+        self.P, self.launches, self.scalars, self.on_launch = P, [], {}, None
+        with open(os.path.join(ROOT, "paper_1609_03488_amd", "csrc", "common.hpp")) as f:
+            body = re.search(r"enum Scal : int \{(.*?)NSC_USED", f.read(), re.S).group(1)
+        self.slot = {n: i for i, n in enumerate(re.findall(r"\bSC_[A-Z]+\b", re.sub(r"//.*", "", body)))}
+        kind = C.CFUNCTYPE(None, C.c_char_p, C.POINTER(C.c_uint), C.c_size_t, C.c_int, C.POINTER(C.c_void_p))
+        self._call = kind(self._launched)
+        self.hip.fake_callback(self._call)
+        self.hip.fake_stream.restype = C.c_void_p
+        P.lib()
+
+    def _launched(self, name, grid, lds, device, args):
+        name = re.search(r"k_[a-z0-9_]+", name.decode()).group(0)
+        self.launches.append(dict(name=name, grid=[grid[0], grid[1], grid[2]], lds=lds, device=device))
+        if name == "k_gather_scalars":   # the instances' scalars, the same for all
+            n = C.cast(args[1], C.POINTER(C.c_int))[0]
+            out = C.cast(C.cast(args[2], C.POINTER(C.c_void_p))[0], C.POINTER(C.c_double))
+            for i in range(n):
+                for k, v in self.scalars.items():
+                    out[i * DOUBLES + self.slot[k]] = v
+        if self.on_launch:
+            self.on_launch(self.launches[-1], args)
+
+    def solver(self, pr, device=0, batch=1, **kw):
+        """Handle of a solver whose stream is on `device`; every instance has data."""
+        P, L = self.P, self.P.lib()
+        st = P.Settings.make(use_graph=0, **kw)
+        q = np.asarray(pr.q, dtype=np.int64)
+        head = (pr.op._h, int(pr.l), q.ctypes.data_as(C.POINTER(C.c_int64)), len(q), C.byref(st))
+        nb = C.c_size_t()
+        assert L.cgs_workspace_bytes(*head, batch, C.byref(nb)) == 0
+        buf = np.zeros(nb.value + 256, dtype=np.uint8)
+        ptr = buf.ctypes.data + (-buf.ctypes.data) % 256
+        h = C.c_void_p()
+        rc = L.cgs_solver_create(*head, batch, ptr, nb.value, self.hip.fake_stream(device), C.byref(h))
+        assert rc == 0, L.cgs_last_error()
+        self.keep = getattr(self, "keep", []) + [(buf, pr)]
+        b, c = (np.ascontiguousarray(v, dtype=np.float64) for v in (pr.b, pr.c))
+        for i in range(batch):
+            assert L.cgs_solver_set_data(h, i, b.ctypes.data_as(C.POINTER(C.c_double)),
+                                         c.ctypes.data_as(C.POINTER(C.c_double))) == 0
+        return h
+
+    def deconv(self, n, k):
+        return self.P.deconv_problem(np.ones(k) / k, np.ones(n + k - 1))
+
+    def ok(self, rc):
+        assert rc == 0, self.P.lib().cgs_last_error()
+
+
+def lds_by_current_device(f, create, launch):
+    """LDS of the fused launches of a solver on device 1, created and run while the calling
+    thread's current device is `create` and `launch`."""
+    f.hip.fake_set_device(int(create))
+    h = f.solver(f.deconv(1700, 201), device=1, precision=f.P.FP64, fused_lone_max=0)
+    f.hip.fake_set_device(int(launch))
+    f.ok(f.P.lib().cgs_solver_iterate(h, 3))
+    return [(v["lds"], v["device"]) for v in f.launches if v["name"] == "k_fused"]
+
+
+SCENARIOS = {v.__name__: v for v in (lds_by_current_device,)}
+
+
+@pytest.fixture(scope="session")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "fake_hip.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(HERE, "fake_hip.cpp"), "-o", so], check=True)
+
+    def run(scenario, *args):
+        r = subprocess.run([sys.executable, os.path.abspath(__file__), so, scenario.__name__, *map(str, args)],
+                           capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        return json.loads(r.stdout.splitlines()[-1])
+
+    return run
+
+
+# the register form of this size needs 67 KB, more than the 64 KB that need no attribute
+@pytest.mark.parametrize("create,launch", [(1, 0), (0, 1), (0, 0), (2, 3)])
+def test_fused_lds_is_the_handles_devices(fake, create, launch):
+    """Chosen and launched by the device of the handle's stream, whatever device the calling
+    thread has current."""
+    want = fake(lds_by_current_device, 1, 1)
+    assert want and all(lds > 65536 and dev == 1 for lds, dev in want[-1:])
+    assert fake(lds_by_current_device, create, launch) == want
+
+
+if __name__ == "__main__":
+    print(json.dumps(SCENARIOS[sys.argv[2]](Fake(sys.argv[1]), *sys.argv[3:])))
