@@ -20,15 +20,11 @@
 
 #include <cmath>
 #include <cstdint>
-#include <mutex>
 
-#include "cgs.h"
 #include "kernels.hpp"
 #include "device_common.hpp"
 
 namespace cgs {
-
-int fail(int code, const char* fmt, ...);
 
 namespace {
 
@@ -88,17 +84,12 @@ DEVI int tw_index(int e) {   // entry -> m
     if (e < TW512) return (((e - TW64) / 64 + 1) * ((e - TW64) % 64) * (FFT_L / 512)) & (FFT_L - 1);
     return (((e - TW512) / 512 + 1) * ((e - TW512) % 512)) & (FFT_L - 1);
 }
-// The table's values, in device memory (one copy per GPU, written once per GPU by
-// fft_prepare).  A workgroup copies them to LDS beside its window loads; computing
-// them (eight sincospi per thread) took about 0.6 us of every launch.
+// The table's values, in device memory (one copy per GPU).  k_conv_spectrum, which an
+// operator's upload runs on its device ahead of every product, computes them and stores
+// those that are not there yet (once there, no entry is written again).  A workgroup of
+// a product copies them to LDS beside its window loads; computing them there (eight
+// sincospi per thread) took about 0.6 us of every launch.
 __device__ float2 g_twiddles[TW_N];
-__global__ __launch_bounds__(FT) void k_twiddles() {
-    for (int e = threadIdx.x; e < TW_N; e += FT) {
-        float s, c;
-        sincospif(-2.0f * (float)tw_index(e) / (float)FFT_L, &s, &c);
-        g_twiddles[e] = make_float2(c, s);
-    }
-}
 constexpr int TW_PER = (TW_N + FT - 1) / FT;
 struct TwRegs {
     float2 v[TW_PER];
@@ -254,9 +245,14 @@ __global__ __launch_bounds__(FT) void k_conv_spectrum(const float* w, int k, flo
     __shared__ cf lds[LDS_L];
     __shared__ cf tw[TW_N];
     const int t = threadIdx.x;
-    TwRegs twr;
-    twr.load();
-    twr.store(tw);
+    for (int e = t; e < TW_N; e += FT) {
+        float sn, cs;
+        sincospif(-2.0f * (float)tw_index(e) / (float)FFT_L, &sn, &cs);
+        tw[e] = {cs, sn};
+        const float2 have = g_twiddles[e];
+        if (__float_as_uint(have.x) != __float_as_uint(cs) || __float_as_uint(have.y) != __float_as_uint(sn))
+            g_twiddles[e] = make_float2(cs, sn);
+    }
     cf v[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
@@ -504,23 +500,6 @@ __global__ __launch_bounds__(FT) void k_conv_fft(Tables tb, ConvLaunch cl, int a
         }
     }
     if (FOLD) fold_partials(cl.part, f, red);
-}
-
-int fft_prepare(hipStream_t st) {
-    static std::mutex mu;
-    static bool done[64] = {};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return fail(CGS_EHIP, "hipGetDevice failed: %s", hipGetErrorString(e));
-    if (dev < 0 || dev >= 64) return fail(CGS_EINVAL, "device %d out of range", dev);
-    std::lock_guard<std::mutex> lock(mu);
-    if (done[dev]) return CGS_OK;
-    k_twiddles<<<1, FT, 0, st>>>();
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return fail(CGS_EHIP, "twiddle table failed: %s", hipGetErrorString(e));
-    done[dev] = true;
-    return CGS_OK;
 }
 
 void launch_conv_spectrum(const void* w, int64_t k, void* spec, hipStream_t st) {

@@ -308,7 +308,6 @@ int op_upload(const cgs_op& op, int precision, char* dst, const Staging& stg, hi
             launch_cast(prec, stg.dev + kpad, p, kpad, st);
             p += align256(kpad * sz);
             if (prec == 1 && k <= FFT_KMAX) {   // spectra for the FFT engine
-                CGS_TRY(fft_prepare(st));
                 cb.s_fwd = p;
                 launch_conv_spectrum(cb.w_fwd, k, p, st);
                 p += align256((size_t)FFT_L * 8);

@@ -73,9 +73,6 @@ size_t conv_mfma_smem_bytes(int kc);
 void launch_conv_fft(const Tables& t, const ConvLaunch& c, int adj, int out, int in, int base,
                      double sigma, int gate, hipStream_t st);
 void launch_conv_spectrum(const void* w, int64_t k, void* spec, hipStream_t st);
-// writes the FFT engine's twiddle table on the current device, the first time
-// (before any launch that reads it, outside stream capture; synchronises st)
-int fft_prepare(hipStream_t st);
 // out += sigma * scale * a (or a^T) * in for every dense tile; own = 1: the rows are
 // written, base and identity blocks included, and the launch's initialisation tiles too
 void launch_gemv(int prec, const Tables& t, const DenseLaunch& d, int adj, int out, int in, int base,

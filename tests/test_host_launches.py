@@ -85,7 +85,17 @@ def lds_by_current_device(f, create, launch):
     return [(v["lds"], v["device"]) for v in f.launches if v["name"] == "k_fused"]
 
 
-SCENARIOS = {v.__name__: v for v in (lds_by_current_device,)}
+def launches_of_creation(f, before):
+    """Launches on device 0 that create an FP32 solver there, after (before = 1) one on a
+    stream of device 1 was created with the same device current."""
+    if int(before):
+        f.solver(f.deconv(3000, 201), device=1)
+        f.launches.clear()
+    f.solver(f.deconv(3000, 201), device=0)
+    return [(v["name"], v["grid"]) for v in f.launches if v["device"] == 0]
+
+
+SCENARIOS = {v.__name__: v for v in (lds_by_current_device, launches_of_creation)}
 
 
 @pytest.fixture(scope="session")
@@ -111,6 +121,14 @@ def test_fused_lds_is_the_handles_devices(fake, create, launch):
     want = fake(lds_by_current_device, 1, 1)
     assert want and all(lds > 65536 and dev == 1 for lds, dev in want[-1:])
     assert fake(lds_by_current_device, create, launch) == want
+
+
+def test_creation_does_not_depend_on_other_devices(fake):
+    """What a solver needs on its device (the FFT engine's table) is written there whichever
+    devices' streams served others before."""
+    alone = fake(launches_of_creation, 0)
+    assert any(name == "k_conv_spectrum" for name, _ in alone)
+    assert fake(launches_of_creation, 1) == alone
 
 
 if __name__ == "__main__":
