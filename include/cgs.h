@@ -175,8 +175,10 @@ typedef struct {
                               wait for the end of the batch of intervals.  Results
                               do not depend on it.  A server always uses 1.  Where
                               every instance is small enough for the fused steps'
-                              register form the host reads after at least 16
-                              intervals: that launch ends its solve by itself.      */
+                              register form one launch runs up to 16 intervals (fewer
+                              where check_every * cg_max_iters * 16 > 8000) and ends
+                              its solve by itself; the host reads after at least
+                              that many.                                            */
 } cgs_settings;
 
 /* Per-instance result. */

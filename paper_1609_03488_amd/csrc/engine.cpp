@@ -1066,11 +1066,11 @@ void Engine::fused_steps(int nsteps, int check) {
     launch_fused(prec, T, fa, stream);
 }
 
-// nsteps steps of the fused instances with a test after every check_every of them: one
-// launch where all take the register form, else one per interval
+// nsteps steps of the fused instances with a test after every check_every of them: a launch
+// for fused_intervals() of these where all take the register form, else one per interval
 void Engine::fused_round(int nsteps) {
-    const int per = fused_general ? st.check_every : nsteps;
-    for (int done = 0; done < nsteps; done += per) fused_steps(std::min(per, nsteps - done), 1);
+    const int64_t per = st.check_every * (fused_general ? 1 : fused_intervals());
+    for (int64_t done = 0; done < nsteps; done += per) fused_steps((int)std::min(per, nsteps - done), 1);
 }
 
 void Engine::steps_with_checks(int nsteps) {

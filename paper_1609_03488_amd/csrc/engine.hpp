@@ -266,14 +266,20 @@ class Engine {
     void admm_step();
     void fused_steps(int nsteps, int check);
     void fused_round(int nsteps);
-    // steps of a round: intervals_per_sync check intervals, or FUSED_INTERVALS where every
-    // instance takes the fused register form: its launch tests and stops inside, and the
-    // host has no decision to take between intervals
+    // Check intervals of one launch of the fused register form, which tests and stops inside:
+    // FUSED_INTERVALS, as far as their steps have at most FUSED_LAUNCH_CG CG iterations (about
+    // 0.4 s at 50 us, the largest instances'), never less than one.
     static constexpr int FUSED_INTERVALS = 16;
-    int round_steps() const {
-        const int iv = n_multi == 0 && !fused_general && fused_reg > 0 && !per_interval
-                           ? std::max(FUSED_INTERVALS, st.intervals_per_sync)
-                           : std::max(1, st.intervals_per_sync);
+    static constexpr int64_t FUSED_LAUNCH_CG = 8000;
+    int64_t fused_intervals() const {
+        const int64_t fit = FUSED_LAUNCH_CG / ((int64_t)st.check_every * st.cg_max_iters);
+        return std::max<int64_t>(1, std::min<int64_t>(FUSED_INTERVALS, fit));
+    }
+    // steps of a round: intervals_per_sync check intervals, or a launch's where every instance
+    // takes the fused register form: the host has no decision to take between intervals
+    int64_t round_steps() const {
+        int64_t iv = std::max(1, st.intervals_per_sync);
+        if (n_multi == 0 && !fused_general && fused_reg > 0 && !per_interval) iv = std::max(iv, fused_intervals());
         return st.check_every * iv;
     }
     int per_interval = 0;   // a server: the host reads every instance's scalars at every check

@@ -263,3 +263,23 @@ def test_dense_products_edges(m, n, prec):
         mag[lo:lo + M.shape[0]] += 0.5 * (np.abs(M) @ np.abs(src))
         err = np.abs(s.apply(v, transpose=adj) - ref)
         assert np.all(err <= (4 * u + max(m, n) * 2.0 ** -52) * mag)
+
+
+# the steps up to the first test beyond 31 bits, as counted over a round, and beyond 30
+@pytest.mark.parametrize("check_every", [2 ** 28, 2 ** 30, 2 ** 31 - 1])
+@pytest.mark.parametrize("fused", [0, 65536], ids=["multikernel", "fused"])
+def test_check_interval_beyond_the_step_limit(check_every, fused):
+    """The test runs once, at max_iters: the solve is that of check_every = max_iters, bit for
+    bit, though the point passes a test long before."""
+    import workloads as w
+    print("[case] check interval beyond the limit", check_every, fused, flush=True)
+    d = w.deconv_instance(300, 31, 31 / 7.0, 0.1, 1e-4, 300)
+    pr = P.deconv_problem(d["c"], d["b"])
+    out = []
+    for every in (check_every, 400, 10):
+        s = P.Solver(pr.op, pr.l, pr.q, P.Settings.make(eps=1e-3, max_iters=400, check_every=every, fused_max=fused))
+        s.set_data(0, pr.b, pr.c)
+        out.append((s.solve()[0]["iters"],) + s.solution(0))
+    assert out[0][0] == out[1][0] == 400 and out[2][0] < 400
+    for a, b in zip(out[0][1:], out[1][1:]):
+        np.testing.assert_array_equal(a, b)

@@ -95,7 +95,28 @@ def launches_of_creation(f, before):
     return [(v["name"], v["grid"]) for v in f.launches if v["device"] == 0]
 
 
-SCENARIOS = {v.__name__: v for v in (lds_by_current_device, launches_of_creation)}
+def steps_of_launches(f, check_every, intervals, cg_max, max_iters):
+    """Steps of each fused launch of a solve that runs to its iteration limit."""
+    steps = []
+
+    def fused(launch, args):
+        if launch["name"] != "k_fused":
+            return
+        a = C.cast(args[1], C.POINTER(C.c_int))       # FusedArgs: nsteps, check, ...
+        if a[1]:
+            steps.append(a[0])
+            f.scalars["SC_ITER"] += a[0]
+            f.scalars["SC_ACTIVE"] = 1.0 if f.scalars["SC_ITER"] < int(max_iters) else 0.0
+
+    f.scalars = dict(SC_ACTIVE=1.0, SC_PHASE=2.0, SC_ITER=0.0)
+    f.on_launch = fused
+    h = f.solver(f.deconv(300, 31), check_every=int(check_every), intervals_per_sync=int(intervals),
+                 cg_max_iters=int(cg_max), max_iters=int(max_iters))
+    f.ok(f.P.lib().cgs_solve(h, None))
+    return steps
+
+
+SCENARIOS = {v.__name__: v for v in (lds_by_current_device, launches_of_creation, steps_of_launches)}
 
 
 @pytest.fixture(scope="session")
@@ -129,6 +150,17 @@ def test_creation_does_not_depend_on_other_devices(fake):
     alone = fake(launches_of_creation, 0)
     assert any(name == "k_conv_spectrum" for name, _ in alone)
     assert fake(launches_of_creation, 1) == alone
+
+
+# the product of a round's intervals and check_every past 31 bits; the default; intervals
+# longer than a launch of 16 would be; more intervals a round than a launch; long CG solves
+@pytest.mark.parametrize("check_every,intervals,cg_max,max_iters,want", [
+    (2 ** 28, 2, 10, 300, [300]), (10 ** 9, 2, 10, 300, [300]), (2 ** 31 - 1, 64, 10, 300, [300]),
+    (10, 2, 10, 400, [160, 160, 80]), (1000, 2, 10, 4500, [1000, 1000, 1000, 1000, 500]),
+    (10, 64, 10, 700, [160, 160, 160, 160, 60]), (10, 2, 10000, 40, [10, 10, 10, 10]), (1, 2, 10, 40, [16, 16, 8])])
+def test_steps_of_a_fused_launch(fake, check_every, intervals, cg_max, max_iters, want):
+    """At most 16 intervals and 8000 CG iterations to a launch, at least one interval."""
+    assert fake(steps_of_launches, check_every, intervals, cg_max, max_iters) == want
 
 
 if __name__ == "__main__":
