@@ -987,9 +987,12 @@ void Engine::admm_step() {
         apply(1, XH, YW, XU, -1.0, G_ADMM);                      // h = u_x - A^T w_y
         launch_cg_start(prec, T, XZ, XR, XP, XK, XH, G_ADMM, stream);   // r = h - K z
     }
+    // The last launch ends the step's CG: at its iteration limit (fewer launches than
+    // cg_max_iters outside a round, as the autotuner's timed steps have, are a lower limit),
+    // or, in a round that predicts the launches, by suspending an instance whose CG would go on.
     const int nl = std::max(1, cg_launch);
-    for (int i = 0; i < nl; ++i)
-        cg_iter(XZ, G_ADMM_CG, st.cg_max_iters, 1, i, spec_now && i == nl - 1, i == 0);
+    const int limit = spec_now ? st.cg_max_iters : nl;
+    for (int i = 0; i < nl; ++i) cg_iter(XZ, G_ADMM_CG, limit, 1, i, spec_now && i == nl - 1, i == 0);
     // the tau products and the cone terms came from the update that ended CG
     launch_project(prec, T, st.alpha, stream);                   // relax, project, dual update
 }

@@ -116,7 +116,28 @@ def steps_of_launches(f, check_every, intervals, cg_max, max_iters):
     return steps
 
 
-SCENARIOS = {v.__name__: v for v in (lds_by_current_device, launches_of_creation, steps_of_launches)}
+def timed_steps(f, family, precision):
+    """For each step the autotuner runs: iteration, limit and suspension flag of its last CG
+    update."""
+    last, steps = [], []
+
+    def seen(launch, args):
+        if launch["name"] == "k_cg_update":   # (tables, z, r, p, q, it, cg_max, gate, track, folded, last, start)
+            last[:] = [C.cast(args[i], C.POINTER(C.c_int))[0] for i in (5, 6, 10)]
+        if launch["name"] == "k_project":
+            steps.append(list(last))
+
+    if family == "deconv":
+        pr = f.deconv(20000, 201)
+    else:
+        pr = f.P.lasso_problem(np.ones((40, 90)) / 40, np.ones(40), 0.1)
+    h = f.solver(pr, precision=int(precision), fused_max=0, batch=3 if int(precision) == f.P.BF16 else 1)
+    f.on_launch = seen
+    f.ok(f.P.lib().cgs_solver_autotune(h, 2, (C.c_int32 * 4)()))
+    return steps
+
+
+SCENARIOS = {v.__name__: v for v in (lds_by_current_device, launches_of_creation, steps_of_launches, timed_steps)}
 
 
 @pytest.fixture(scope="session")
@@ -161,6 +182,14 @@ def test_creation_does_not_depend_on_other_devices(fake):
 def test_steps_of_a_fused_launch(fake, check_every, intervals, cg_max, max_iters, want):
     """At most 16 intervals and 8000 CG iterations to a launch, at least one interval."""
     assert fake(steps_of_launches, check_every, intervals, cg_max, max_iters) == want
+
+
+@pytest.mark.parametrize("family,precision", [("deconv", 0), ("deconv", 1), ("dense", 0), ("dense", 1), ("dense", 2)])
+def test_every_timed_step_ends_its_cg(fake, family, precision):
+    """The projection reads what the update that ends CG leaves: the last update of each step
+    the autotuner times is at the iteration limit or may suspend the instance."""
+    steps = fake(timed_steps, family, precision)
+    assert steps and all(it + 1 == limit or last for it, limit, last in steps)
 
 
 if __name__ == "__main__":
