@@ -524,6 +524,7 @@ static int time_steps(cgs_solver* s, int reps, double* ms_per_step) {
     e.refresh();
     const int keep = e.cg_launch;
     e.cg_launch = 1;
+    e.test_first = 0;
     for (int i = 0; i < 3; ++i) e.admm_step();
     hipEvent_t a, b;
     CGS_HIP(hipEventCreate(&a));
@@ -806,6 +807,7 @@ int cgs_solver_iterate(cgs_solver* s, int32_t iters) {
     cgs::Engine& e = s->eng;
     CGS_TRY(run_setup_if_needed(s, nullptr));
     e.cg_launch = e.st.cg_max_iters;
+    e.choose_start_test();
     e.refresh();
     if (e.n_fused) e.fused_steps(iters, 0);
     if (e.n_multi)

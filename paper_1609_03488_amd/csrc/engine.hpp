@@ -225,16 +225,19 @@ class Engine {
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
 
-    // instantiated check-interval graphs, by (steps, CG launches per step); the
-    // launch count moves between a few values over a solve
+    // instantiated check-interval graphs, by (steps, CG launches per step, place of the start
+    // test); these move between a few values over a solve (up to four launch counts, both
+    // places: a cache of four instantiated some of them again in every solve)
     struct CachedGraph {
-        int steps, cg, spec;
+        int steps, cg, spec, first;
         hipGraph_t graph;
         hipGraphExec_t exec;
         int64_t used;
     };
     std::vector<CachedGraph> graphs;
-    static constexpr size_t GRAPH_CACHE = 4;
+    static constexpr size_t GRAPH_CACHE = 8;
+    int test_first = 0;           // the CG start test runs ahead of a step's products (choose_start_test)
+    std::vector<double> seen;     // steps and CG iterations of each instance at the last choice
     bool spec_now = false;        // the round being enqueued records a step that needs more CG launches
     int rounds_since_build = 0;   // a graph is captured only once the tables have held a round
 
@@ -290,6 +293,7 @@ class Engine {
                     int gate);
     void refresh();
     void adapt_cg();
+    void choose_start_test();
     // ---- host loops
     int setup();                  // instances with phase 0 (synchronises)
     // nsteps ADMM steps, a termination test after every check_every of them and

@@ -568,7 +568,14 @@ __global__ __launch_bounds__(VEC_NT) void k_cg_update(Tables tb, int z, int r, i
     const XYTile xt = xy_tile(tb);
     const InstDesc d = tb.inst[xt.t.inst];
     gptr<double> sc = scal(d);
-    if (!gate_ok(sc, gate) || sc[SC_CGRUN] != (double)it) return;
+    const double run = sc[SC_CGRUN];
+    if (!gate_ok(sc, gate)) return;
+    if (run != (double)it) {
+        // the start test ahead of the products ended the step's CG
+        if (cs.tested && run < 0.0)
+            cg_elems<T>(tb, d, xt, sc, cs, false, 0.0, 0.0, false, false, true, z, r, p, q, sh);
+        return;
+    }
     const bool rec = !xt.is_y && xt.index == d.xt0 && threadIdx.x == 0;
     double s[4];
     double h0 = 0.0, h1 = 0.0;

@@ -95,8 +95,10 @@ void launch_cg_dot(int prec, const Tables& t, int p, int q, int r, int it, int g
 // `it`: CG iteration of the current loop (must match the preceding launch_cg_dot)
 // The CG start test evaluated by the first update of a step: the right-hand side's
 // partials are in Tables::spart, and the first iteration's products ran whatever its
-// outcome (a step whose CG makes no iteration is rare).  Two launches a step fewer, at
-// 5 us each, than with the test and the tau products in launches of their own.
+// outcome; off the folded path, rounds in which steps make no iteration take the test in
+// a launch ahead of the products instead (on = 0, tested = 1; Engine::choose_start_test).
+// Two launches a step fewer, at 5 us each, than with the test and the tau products in
+// launches of their own; one fewer with tested.
 struct CgStart {
     double zeta, rate, floor_;
     int on;
@@ -120,6 +122,9 @@ struct CgStart {
     // first CG iteration of a folded ADMM step reads p = r from r's vector
     // (the right-hand side launch does not copy it) and writes p' to XP.
     int pn = -1;
+    // 1: the step's start test ran ahead of its products (launch_cg_init): where it ended
+    // CG, this update (of the first iteration) takes the tau products of the start
+    int tested = 0;
 };
 void launch_cg_update(int prec, const Tables& t, int z, int r, int p, int q, int it, int cg_max,
                       int gate, int track, hipStream_t st, int folded = 0, int last = 0,

@@ -283,3 +283,38 @@ def test_check_interval_beyond_the_step_limit(check_every, fused):
     assert out[0][0] == out[1][0] == 400 and out[2][0] < 400
     for a, b in zip(out[0][1:], out[1][1:]):
         np.testing.assert_array_equal(a, b)
+
+
+# dense products (alone, and a batch whose members differ) and a convolution's; CG solves that
+# all iterate (None), and a tolerance that early steps meet from the warm start
+@pytest.mark.parametrize("family,prec,batch,cg_tol", [("lasso", P.FP64, 1, None), ("lasso", P.FP32, 3, None),
+                                                      ("lasso", P.FP64, 1, 3.0), ("lasso", P.FP32, 3, 3.0),
+                                                      ("deconv", P.FP64, 2, 3.0)])
+def test_start_test_ahead_of_the_products(family, prec, batch, cg_tol):
+    """The host moves the CG start test ahead of the first products when it reads that steps
+    made no iteration: with a read after every interval it does, with one after 64 intervals
+    it cannot, and the solves are the same, bit for bit."""
+    import workloads as w
+    print("[case] start test ahead of the products", family, prec, batch, cg_tol, flush=True)
+    rng = np.random.default_rng(5)
+    if family == "lasso":
+        A = (rng.standard_normal((300, 900)) / 17).astype(np.float32)
+        pr = P.lasso_problem(A, rng.standard_normal(300), 0.3)
+        tol = dict(normalize=2)
+    else:
+        d = w.deconv_instance(3000, 41, 6.0, 0.1, 1e-4, 1)
+        pr, tol = P.deconv_problem(d["c"], d["b"]), {}
+    if cg_tol is not None:
+        tol["cg_tol"] = cg_tol
+    out = []
+    for intervals in (1, 64):
+        s = P.Solver(pr.op, pr.l, pr.q, P.Settings.make(precision=prec, eps=1e-300, max_iters=600, fused_max=0,
+                                                        intervals_per_sync=intervals, **tol), batch=batch)
+        for i in range(batch):
+            s.set_data(i, pr.b * (1.0 + i), pr.c)
+        r = s.solve()
+        out.append([[(v["iters"], v["cg_iters"]) for v in r]] + [s.state(i) for i in range(batch)])
+    assert out[0][0] == out[1][0]
+    for x, y in zip(out[0][1:], out[1][1:]):
+        for a, b in zip(x, y):
+            np.testing.assert_array_equal(a, b)

@@ -137,7 +137,30 @@ def timed_steps(f, family, precision):
     return steps
 
 
-SCENARIOS = {v.__name__: v for v in (lds_by_current_device, launches_of_creation, steps_of_launches, timed_steps)}
+def product_gates(f, cg_per_step):
+    """Gates of the dense products of each step of a solve whose steps make cg_per_step CG
+    iterations (checks left out)."""
+    steps, gates = [], []
+
+    def seen(launch, args):
+        if launch["name"] == "k_gemv":      # (tables, launch, adj, out, in, base, sigma, gate, own)
+            gates.append(C.cast(args[7], C.POINTER(C.c_int))[0])
+        if launch["name"] == "k_project":
+            steps.append(gates[-3:])
+            f.scalars["SC_ITER"] += 1.0
+            f.scalars["SC_CGTOT"] += float(cg_per_step)
+            f.scalars["SC_ACTIVE"] = 1.0 if f.scalars["SC_ITER"] < 60 else 0.0
+
+    pr = f.P.lasso_problem(np.ones((40, 90)) / 40, np.ones(40), 0.1)
+    h = f.solver(pr, fused_max=0, cg_max_iters=1)
+    f.scalars = dict(SC_ACTIVE=1.0, SC_PHASE=1.0, SC_ITER=0.0, SC_CGTOT=9.0)
+    f.on_launch = seen
+    f.ok(f.P.lib().cgs_solve(h, None))
+    return steps
+
+
+SCENARIOS = {v.__name__: v for v in (lds_by_current_device, launches_of_creation, steps_of_launches, timed_steps,
+                                     product_gates)}
 
 
 @pytest.fixture(scope="session")
@@ -190,6 +213,18 @@ def test_every_timed_step_ends_its_cg(fake, family, precision):
     the autotuner times is at the iteration limit or may suspend the instance."""
     steps = fake(timed_steps, family, precision)
     assert steps and all(it + 1 == limit or last for it, limit, last in steps)
+
+
+G_ADMM, G_ADMM_CG = 3, 4      # enum Gate
+
+
+@pytest.mark.parametrize("cg_per_step", [0, 1])
+def test_idle_cg_leaves_the_products_out(fake, cg_per_step):
+    """Once the host has seen a round of steps without CG iterations, the next ones gate the
+    first iteration's products on the start test; with iterations it keeps them ungated."""
+    steps = fake(product_gates, cg_per_step)
+    assert len(steps) == 60 and all(s == [G_ADMM] * 3 for s in steps[:20])
+    assert all(s == [G_ADMM] + [G_ADMM if cg_per_step else G_ADMM_CG] * 2 for s in steps[20:])
 
 
 if __name__ == "__main__":
