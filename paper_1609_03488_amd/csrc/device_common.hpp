@@ -324,9 +324,11 @@ DEVI void st4(gptr<T> p, const Chunks& c, int j, const v4<T>& v) {
 //   A x : w = reversed taps, off = -(k-1), in = x (zero outside [0, n_in));
 //   A^T y: w = taps,          off = 0,      in = y.
 // Each lane keeps R outputs in registers and slides a register window over an
-// LDS copy of the tile's input window, staged with batched loads.  Two forms, both
-// summing in tap order: k_conv (one wave, taps by scalar loads) and conv_sums (a
-// tile of R outputs per thread of a workgroup, taps staged in LDS, for k_fused).
+// LDS copy of the tile's input window, staged with batched loads.  Three forms, all
+// summing in tap order: conv_sums (a tile of R outputs per thread of a workgroup, taps
+// staged in LDS; k_conv on one wave, and k_fused), the narrow form of k_conv (taps staged
+// in LDS, a register of 16 broadcast by DPP) and the register form of k_fused (taps by
+// scalar loads, input in LDS as it is).
 constexpr int CONV_NT = 64;
 template <typename T> struct ConvCfg;
 template <> struct ConvCfg<float> { static constexpr int R = 8; };

@@ -43,12 +43,12 @@ __global__ __launch_bounds__(VEC_NT) void k_apply_init(Tables tb, int adj, int o
 
 // Direct convolution: one wave sums 64 R outputs, lane l the R ones from R l, over
 // all taps in tap order (the order, and so the result, depends on neither R nor
-// the form of the loop).  Two forms, chosen by the launch's tile count (conv_sub):
-//  * R = ConvCfg::R, many tiles: each step of 2 R taps reads its window values and
+// the form of the loop).  Two forms (conv_sub chooses):
+//  * R = ConvCfg::R (conv_sums): each step of 2 R taps reads its window values and
 //    taps from LDS; the other waves of the SIMD cover the reads.
-//  * R half of that (NARROW), few tiles: the launch is one wave's chain over the taps
-//    (n = 3000, k = 1365 in FP64: 18 waves on the chip at R = 4, 25.2 us).  The
-//    window values of the next 16 taps are read while the current ones are summed,
+//  * R half of that (NARROW), few tiles and long kernels: the launch is one wave's chain
+//    over the taps (n = 3000, k = 1365 in FP64: 18 waves on the chip at R = 4, 25.2 us).
+//    The window values of the next 16 taps are read while the current ones are summed,
 //    and the taps, which as broadcast reads cost as much LDS time as the window,
 //    travel in a register, 16 to a row of lanes, and reach the row's lanes through
 //    DPP broadcasts: 17.4 us, bound by the latency of the dependent FP64 sums
@@ -82,22 +82,25 @@ DEVI void conv_row(T (&acc)[R], T (&c)[R], const T (&v)[CONV_U], T tw, std::inte
     for (int j = 0; j < R; ++j) c[j] = v[CONV_U - R + j];
 }
 
-__host__ __device__ constexpr int conv_init_parts(int sub) { return sub > 1 ? 8 : 2; }
+// (the waves a SIMD that the registers are held to, FP64 162 and 89, matter through the
+// allocation alone: with no such bound the narrow form took 159 and ran 2 % slower, the wide
+// one 87 and ran 4-9 % slower from k = 257 on; a bound of four or six costs 20 and 5 %)
 template <typename T, int R>
-__global__ __launch_bounds__(CONV_NT) void k_conv(Tables tb, ConvLaunch cl, int sub, int adj, int out, int in,
-                                                  int base, double sigma, int gate) {
+__global__ __launch_bounds__(CONV_NT, R < ConvCfg<T>::R ? 3 : 5) void k_conv(Tables tb, ConvLaunch cl, int sub,
+                                                  int parts, int adj, int out, int in, int base, double sigma, int gate) {
     extern __shared__ __align__(16) unsigned char conv_smem[];
     if ((int)blockIdx.x >= cl.ntiles * sub) {
         // initialisation tiles riding on the launch, in parts: a whole tile on one
         // wave is a chain of 12.5 us, longer than most launches of few tiles
-        const int w = (int)blockIdx.x - cl.ntiles * sub, np = conv_init_parts(sub), len = VEC_TILE / np;
-        VecTile it = cl.init[w / np].tile();
-        const int p0 = (w % np) * len;
+        const int w = (int)blockIdx.x - cl.ntiles * sub, len = VEC_TILE / parts;
+        VecTile it = cl.init[w / parts].tile();
+        const int p0 = (w % parts) * len;
         if (p0 >= it.len) return;
         it.start += p0;
         it.len = it.len - p0 < len ? it.len - p0 : len;
         const InstDesc di = tb.inst[it.inst];
-        if (gate_ok(scal(di), gate)) init_tile<T>(tb, di, it, adj, out, in, base, sigma, false);
+        // (four elements at a time: eight take 128 registers, the sums 87, FP32 65)
+        if (gate_ok(scal(di), gate)) init_tile<T, 4>(tb, di, it, adj, out, in, base, sigma, false);
         return;
     }
     const int tix = (int)blockIdx.x / sub;
@@ -107,8 +110,6 @@ __global__ __launch_bounds__(CONV_NT) void k_conv(Tables tb, ConvLaunch cl, int 
     if (!gate_ok(scal(d), gate)) return;
     constexpr int TILE = CONV_NT * R, U = CONV_U;
     constexpr bool NARROW = R < ConvCfg<T>::R;
-    T* taps = reinterpret_cast<T*>(conv_smem);   // kc entries
-    T* win = taps + cl.kc;                       // TILE + kc entries
     const int lane = threadIdx.x, li = lane * R;
     const int64_t ot = tl.start + (int64_t)((int)blockIdx.x - tix * sub) * TILE;
     const int64_t n_out = adj ? cb.n_in : cb.n_in + cb.k - 1;
@@ -120,46 +121,57 @@ __global__ __launch_bounds__(CONV_NT) void k_conv(Tables tb, ConvLaunch cl, int 
     gptr<const T> w = (gptr<const T>)(adj ? cb.w_adj : cb.w_fwd);
     const bool own = (cb.own >> adj) & 1;
     const int no = n_out - ot - li < R ? (int)(n_out - ot - li) : R;   // the lane's outputs (<= 0: none)
-    double ov[R];   // what they hold besides the sums
+    const double s = sigma * cb.scale;
+    // what the lane's outputs r0 .. r0 + 3 (of fewer, all) hold besides the sums
+    constexpr int NH = R < 4 ? R : 4;
+    auto held = [&](int r0, double (&ov)[NH]) {
+        if (own) {
+            owned_init_n<T, NH>(d, tb.ids, adj, in, base, sigma, g0 + ot + li + r0, no - r0, ov);
+        } else {
+#pragma unroll
+            for (int r = 0; r < NH; ++r) ov[r] = r < no - r0 ? (double)o[ot + li + r0 + r] : 0.0;
+        }
+    };
+    auto write = [&](int r0, const double (&ov)[NH], const T (&acc)[R]) {
+#pragma unroll
+        for (int r = 0; r < NH; ++r)
+            if (r < no - r0) o[ot + li + r0 + r] = (T)(ov[r] + s * (double)acc[r0 + r]);
+    };
     T acc[R];
+    if constexpr (NARROW) {
+        T* taps = reinterpret_cast<T*>(conv_smem);   // kc entries
+        T* win = taps + cl.kc;                       // TILE + kc entries
+        static_assert(R <= 4, "one piece of outputs");
+        double ov[NH];
 #pragma unroll
-    for (int r = 0; r < R; ++r) acc[r] = T(0);
-    for (int64_t t0 = 0; t0 < cb.kpad; t0 += cl.kc) {
-        const int kc = (int)((cb.kpad - t0) < cl.kc ? (cb.kpad - t0) : cl.kc);
-        const int nwin = TILE + kc;
-        // the window's positions [qlo, qhi) lie inside the block's inputs
-        const int64_t i0 = ot + off + t0;
-        const int qlo = i0 < 0 ? (int)-i0 : 0;
-        const int qhi = n_in - i0 < nwin ? (int)(n_in - i0) : nwin;
-        gptr<const T> sw = src + i0;
-        if (t0) __syncthreads();
-        constexpr int NB = 16;   // window loads in flight per lane
-        for (int b0 = 0; b0 < nwin; b0 += NB * CONV_NT) {
-            T v[NB], tv[NB];
+        for (int r = 0; r < R; ++r) acc[r] = T(0);
+        for (int64_t t0 = 0; t0 < cb.kpad; t0 += cl.kc) {
+            const int kc = (int)((cb.kpad - t0) < cl.kc ? (cb.kpad - t0) : cl.kc);
+            const int nwin = TILE + kc;
+            // the window's positions [qlo, qhi) lie inside the block's inputs
+            const int64_t i0 = ot + off + t0;
+            const int qlo = i0 < 0 ? (int)-i0 : 0;
+            const int qhi = n_in - i0 < nwin ? (int)(n_in - i0) : nwin;
+            gptr<const T> sw = src + i0;
+            if (t0) __syncthreads();
+            constexpr int NB = 16;   // window loads in flight per lane
+            for (int b0 = 0; b0 < nwin; b0 += NB * CONV_NT) {
+                T v[NB], tv[NB];
 #pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int i = b0 + j * CONV_NT + lane;
-                v[j] = (i >= qlo && i < qhi) ? sw[i] : T(0);
-                tv[j] = i < kc ? w[t0 + i] : T(0);
-            }
-            if (t0 == 0 && b0 == 0) {   // (while the window's loads are in flight)
-                if (own) {
-                    owned_init_n<T, R>(d, tb.ids, adj, in, base, sigma, g0 + ot + li, no, ov);
-                } else {
+                for (int j = 0; j < NB; ++j) {
+                    const int i = b0 + j * CONV_NT + lane;
+                    v[j] = (i >= qlo && i < qhi) ? sw[i] : T(0);
+                    tv[j] = i < kc ? w[t0 + i] : T(0);
+                }
+                if (t0 == 0 && b0 == 0) held(0, ov);   // (while the window's loads are in flight)
 #pragma unroll
-                    for (int r = 0; r < R; ++r) ov[r] = r < no ? (double)o[ot + li + r] : 0.0;
+                for (int j = 0; j < NB; ++j) {
+                    const int i = b0 + j * CONV_NT + lane;
+                    if (i < nwin) win[i] = v[j];
+                    if (i < kc) taps[i] = tv[j];
                 }
             }
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int i = b0 + j * CONV_NT + lane;
-                if (i < nwin) win[i] = v[j];
-                if (i < kc) taps[i] = tv[j];
-            }
-        }
-        __syncthreads();
-        int tt = 0;
-        if constexpr (NARROW) {
+            __syncthreads();
             // steps of U taps in two register buffers (the barriers keep the
             // compiler from sinking the next step's reads to where they are
             // used); tap tt + (lane % 16) in every row of 16 lanes
@@ -187,32 +199,25 @@ __global__ __launch_bounds__(CONV_NT) void k_conv(Tables tb, ConvLaunch cl, int 
                 conv_row<T, R>(acc, c, xb, te, seq);
             }
             if (nu & 1) conv_row<T, R>(acc, c, xa, ta, seq);
-            tt = nu * U;
-        } else {
-            T a[R], b[R], tw[R];
-            lds_vec<T, R>(a, win + li);
-            for (; tt + 2 * R <= kc; tt += 2 * R) {
-                lds_vec<T, R>(b, win + li + tt + R);
-                lds_vec<T, R>(tw, taps + tt);
-                conv_step<T, R>(acc, a, b, tw);
-                lds_vec<T, R>(a, win + li + tt + 2 * R);
-                lds_vec<T, R>(tw, taps + tt + R);
-                conv_step<T, R>(acc, b, a, tw);
+            for (int tt = nu * U; tt < kc; tt += 4) {   // (kc is a multiple of 4)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const T tv = taps[tt + t];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) acc[r] = fma(tv, win[li + tt + t + r], acc[r]);
+                }
             }
         }
-        for (; tt < kc; tt += 4) {   // (kc is a multiple of 4)
+        write(0, ov, acc);
+    } else {
+        conv_sums<T, CONV_NT>(cb, adj, src, ot, cl.kc, conv_smem, acc);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const T tv = taps[tt + t];
-#pragma unroll
-                for (int r = 0; r < R; ++r) acc[r] = fma(tv, win[li + tt + t + r], acc[r]);
-            }
+        for (int r0 = 0; r0 < R; r0 += NH) {   // (all at once: 102 registers in FP32, half a wave fewer)
+            double ov[NH];
+            held(r0, ov);
+            write(r0, ov, acc);
         }
     }
-    const double s = sigma * cb.scale;
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-        if (r < no) o[ot + li + r] = (T)(ov[r] + s * (double)acc[r]);
 }
 
 // ---------------------------------------------------------------- operator: dense block
@@ -1212,19 +1217,30 @@ void launch_apply_init(int prec, const Tables& t, int adj, int out, int in, int 
     CGS_DISPATCH(prec, k_apply_init, adj ? t.nx_tiles : t.ny_tiles, VEC_NT, st, t, adj, out, in,
                  base, sigma, gate);
 }
-// Workgroups per tile of the tile tables: two, in the narrow form of k_conv, up to
-// 512 tiles, where the chip has at most two waves per SIMD in the other form and a
-// wave's own chain bounds the launch (FP64, k = 257: 118 tiles 9.1 -> 7.0 us).
-static int conv_sub(int tiles) { return tiles <= 512 ? 2 : 1; }
+// Workgroups per tile of the tile tables: two, in the narrow form of k_conv, where a wave's
+// own chain bounds the launch: up to 512 tiles (at most two waves per SIMD in the other
+// form) and kernels long enough for the chain to outweigh the narrow form's longer start.
+// us per launch, wide / narrow, first at 20-30 tiles, then at 490-510:
+//   FP64 k = 65    4.2 / 4.8    4.5 / 5.3      FP32 k = 5     5.1 / 4.6    5.5 / 5.0
+//        k = 129   5.0 / 5.3    5.5 / 5.9           k = 17    5.3 / 4.8    5.7 / 5.2
+//        k = 257   7.6 / 6.3    8.0 / 7.0           k = 65    5.7 / 5.3    6.0 / 5.8
+//        k = 1025 18.8 / 14.0  19.5 / 15.6          k = 1025 24.8 / 17.3  25.2 / 18.4
+// and past them (FP64 782 tiles, k = 257 and 1025) 8.4 / 8.9 and 21.6 / 22.2.
+static int conv_sub(int prec, const ConvLaunch& c) { return c.ntiles <= 512 && c.kc >= (prec == 0 ? 160 : 8) ? 2 : 1; }
+// Workgroups per initialisation tile: more where the launch is short
+static int conv_init_parts(const ConvLaunch& c) { return c.ntiles <= 512 ? 8 : 2; }
 
 void launch_conv(int prec, const Tables& t, const ConvLaunch& c, int adj, int out, int in, int base,
                  double sigma, int gate, hipStream_t st) {
-    const int sub = conv_sub(c.ntiles);
-    const int grid = c.ntiles * sub + c.ninit * conv_init_parts(sub);
+    const int sub = conv_sub(prec, c), parts = conv_init_parts(c);
+    const int grid = c.ntiles * sub + c.ninit * parts;
     if (grid <= 0) return;
+    ConvLaunch cl = c;
+    if (sub == 1) cl.kc = std::min(c.kc, prec == 0 ? CONV_KC_MAX_F64 : CONV_KC_MAX_F32);
     // taps and window (at the larger R)
-    const size_t lds = (size_t)(2 * c.kc + (prec == 0 ? CONV_TILE_F64 : CONV_TILE_F32)) * (prec == 0 ? 8 : 4);
-#define CGS_CONV(T, R) k_conv<T, R><<<grid, CONV_NT, lds, st>>>(t, c, sub, adj, out, in, base, sigma, gate)
+    const size_t lds = (size_t)(2 * cl.kc + (prec == 0 ? CONV_TILE_F64 + 2 * CONV_R_F64 : CONV_TILE_F32 + 2 * CONV_R_F32)) *
+                       (prec == 0 ? 8 : 4);
+#define CGS_CONV(T, R) k_conv<T, R><<<grid, CONV_NT, lds, st>>>(t, cl, sub, parts, adj, out, in, base, sigma, gate)
     if (prec == 0) {
         if (sub == 2) CGS_CONV(double, 2);
         else CGS_CONV(double, 4);

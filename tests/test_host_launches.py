@@ -159,7 +159,19 @@ def product_gates(f, cg_per_step):
     return steps
 
 
-SCENARIOS = {v.__name__: v for v in (lds_by_current_device, launches_of_creation, steps_of_launches, timed_steps,
+def direct_convolution(f, n, k, precision):
+    """Grid and LDS of the direct convolution's launch for A x."""
+    n, k = int(n), int(k)
+    op = f.P.Operator(n + k - 1, n).add_conv(0, 0, np.ones(k), n)
+    pr = types.SimpleNamespace(op=op, l=n + k - 1, q=[], b=np.ones(n + k - 1), c=np.ones(n))
+    h = f.solver(pr, precision=int(precision), conv_mfma=0, fused_max=0)
+    f.launches.clear()
+    x, y = np.ones(n), np.ones(n + k - 1)
+    f.ok(f.P.lib().cgs_solver_apply(h, 0, *(v.ctypes.data_as(C.POINTER(C.c_double)) for v in (x, y))))
+    return [(v["grid"][0], v["lds"]) for v in f.launches if v["name"] == "k_conv"]
+
+
+SCENARIOS = {v.__name__: v for v in (direct_convolution, lds_by_current_device, launches_of_creation, steps_of_launches, timed_steps,
                                      product_gates)}
 
 
@@ -213,6 +225,19 @@ def test_every_timed_step_ends_its_cg(fake, family, precision):
     the autotuner times is at the iteration limit or may suspend the instance."""
     steps = fake(timed_steps, family, precision)
     assert steps and all(it + 1 == limit or last for it, limit, last in steps)
+
+
+# workgroups per tile of 256 (FP64) or 512 outputs, and bytes of LDS (taps and window)
+@pytest.mark.parametrize("n,k,precision,per,lds", [
+    (5000, 33, 0, 1, (2 * 36 + 264) * 8), (5000, 156, 0, 1, (2 * 156 + 264) * 8), (5000, 160, 0, 2, (2 * 160 + 264) * 8),
+    (130000, 257, 0, 2, (2 * 260 + 264) * 8), (140000, 257, 0, 1, (2 * 260 + 264) * 8),
+    (140000, 2047, 0, 1, (2 * 1024 + 264) * 8), (5000, 5, 1, 2, (2 * 8 + 528) * 4), (300000, 5, 1, 1, (2 * 8 + 528) * 4),
+    (300000, 2047, 1, 1, (2 * 2048 + 528) * 4)])
+def test_form_of_the_direct_convolution(fake, n, k, precision, per, lds):
+    """Narrow form (two workgroups per tile) up to 512 tiles and from the kernel lengths where
+    it is the faster one; the wide form's chunks of taps leave the LDS for eight waves."""
+    tile = 256 if precision == 0 else 512
+    assert fake(direct_convolution, n, k, precision) == [[per * -(-(n + k - 1) // tile), lds]]
 
 
 G_ADMM, G_ADMM_CG = 3, 4      # enum Gate
