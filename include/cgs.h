@@ -331,8 +331,10 @@ int cgs_solver_normal_solve(cgs_solver* s, const double* rhs, const double* z0, 
  * vectors: kernel 0 = convolution (A), 1 = convolution adjoint (A^T),
  * 2 = dense block (A), 3 = dense block (A^T) (for a CGS_BF16 batch: the
  * pack + MFMA GEMM + reduce of all instances), 4 = the whole normal-operator
- * application p + A^T A p.  *avg_ms receives the mean time per launch (per
- * operator block, for 0-3); CGS_ENOTFOUND if the operator has no such block. */
+ * application p + A^T A p.  The launches are those of an operator application: a
+ * dense block that owns its output range is timed writing it, base and identity
+ * blocks and (with the first block) the elements outside included.  *avg_ms receives
+ * the mean time per launch (per operator block, for 0-3); CGS_ENOTFOUND if the operator has no such block. */
 int cgs_solver_kernel_time(cgs_solver* s, int32_t kernel, int32_t reps, double* avg_ms);
 /* Autotuner: picks, for this solver's own operator and instances, the FP32
  * convolution engine (vector ALU, matrix cores, or FFT when the kernels are

@@ -470,19 +470,10 @@ int cgs_solver_kernel_time(cgs_solver* s, int32_t kernel, int32_t reps, double* 
                 e.conv(c, kernel, kernel ? cgs::XT : cgs::YT, kernel ? cgs::YU : cgs::XU, -1, 1.0, cgs::G_ALL),
                     ++launches;
         } else if (kernel <= 3) {
+            // what an apply launches (a batch's: pack + BF16 MFMA GEMM + reduce per block)
             const int adj = kernel == 3;
-            if (e.use_gemm) {
-                // the batch's dense applies: pack + BF16 MFMA GEMM + reduce
-                for (const cgs::DenseBlock& db : s->opdev.dense)
-                    cgs::launch_gemm_apply(e.T, db, adj, adj ? cgs::XT : cgs::YT, adj ? cgs::YU : cgs::XU, 1.0,
-                                           cgs::G_ALL, e.gemm_corr, e.panel, e.panel_stride, e.gemm_part,
-                                           e.gemm_target, e.stream),
-                        ++launches;
-            } else {
-                for (const auto& d : dl)
-                    cgs::launch_gemv(e.prec, e.T, d, adj, adj ? cgs::XT : cgs::YT, adj ? cgs::YU : cgs::XU, -1,
-                                     1.0, cgs::G_ALL, 0, e.stream), ++launches;
-            }
+            e.dense(adj, adj ? cgs::XT : cgs::YT, adj ? cgs::YU : cgs::XU, -1, 1.0, cgs::G_ALL, e.pack_init(adj));
+            launches += e.use_gemm ? (int)s->opdev.dense.size() : (int)dl.size();
         } else {
             e.apply(0, cgs::YT, cgs::XP, -1, 1.0, cgs::G_ALL);
             e.apply(1, cgs::XT, cgs::YT, cgs::XP, 1.0, cgs::G_ALL);

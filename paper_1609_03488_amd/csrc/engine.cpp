@@ -912,12 +912,15 @@ void Engine::conv(const ConvLaunch& c, int adj, int out, int in, int base, doubl
 
 void Engine::apply(int adj, int out, int in, int base, double sigma, int gate) {
     const auto& cl = adj ? ca : cf;
-    // with no convolution launch in between, the first GEMM's packing launch
-    // also writes the output's initial value
-    const bool init_in_pack = use_gemm && cl.empty() && !fold_init[adj] && !recs[0].op->dense.empty();
+    const bool init_in_pack = pack_init(adj);
     const int own = own_dense[adj];   // (the dense launches write base and identity blocks)
     if (!fold_init[adj] && !init_in_pack && !own) launch_apply_init(prec, T, adj, out, in, base, sigma, gate, stream);
     for (const auto& c : cl) conv(c, adj, out, in, base, sigma, gate);
+    dense(adj, out, in, base, sigma, gate, init_in_pack);
+}
+
+void Engine::dense(int adj, int out, int in, int base, double sigma, int gate, bool init_in_pack) {
+    const int own = own_dense[adj];
     if (use_gemm) {
         // every instance shares the dense blocks: one MFMA GEMM per block
         bool first = true;

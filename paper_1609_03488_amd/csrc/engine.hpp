@@ -252,6 +252,12 @@ class Engine {
     // ---- device work (enqueue only)
     void apply(int adj, int out, int in, int base, double sigma, int gate);
     void conv(const ConvLaunch& c, int adj, int out, int in, int base, double sigma, int gate);
+    // the dense launches of an apply; init_in_pack: the first GEMM's packing launch writes the
+    // output's initial value (pack_init: when no convolution launch comes in between)
+    void dense(int adj, int out, int in, int base, double sigma, int gate, bool init_in_pack);
+    bool pack_init(int adj) const {
+        return use_gemm && (adj ? ca : cf).empty() && !fold_init[adj] && !recs[0].op->dense.empty();
+    }
     // last = 1: the step's last CG launch (records a step that needed more);
     // start = 1: the first iteration of a step on the folded path (ungated
     // products, the update takes the CG start test)

@@ -171,7 +171,32 @@ def direct_convolution(f, n, k, precision):
     return [(v["grid"][0], v["lds"]) for v in f.launches if v["name"] == "k_conv"]
 
 
-SCENARIOS = {v.__name__: v for v in (direct_convolution, lds_by_current_device, launches_of_creation, steps_of_launches, timed_steps,
+def dense_launches(f, precision, adj):
+    """Launches of the dense products (name, grid, own) as an apply makes them and as the
+    timing call does."""
+    rec = []
+
+    def seen(launch, args):
+        own = {"k_gemv": 8, "k_gemm_reduce": 15}.get(launch["name"])
+        if launch["name"] in ("k_gemv", "k_gemm_pack", "k_gemm_bf16", "k_gemm_reduce"):
+            rec.append((launch["name"], launch["grid"], C.cast(args[own], C.POINTER(C.c_int))[0] if own else None))
+
+    P, adj, dp = f.P, int(adj), C.POINTER(C.c_double)
+    A = np.ones((300, 500))
+    op = P.Operator(700, 900).add_identity(0, 0, 400).add_dense(30, 40, A).add_dense(350, 600, A[:200, :300])
+    pr = types.SimpleNamespace(op=op, l=700, q=[], b=np.ones(700), c=np.ones(900))
+    h = f.solver(pr, precision=int(precision), fused_max=0, batch=3)
+    f.on_launch = seen
+    x, y = np.ones(900), np.ones(700)
+    x, y = (v.ctypes.data_as(dp) for v in (x, y))
+    f.ok(P.lib().cgs_solver_apply(h, adj, y if adj else x, x if adj else y))
+    apply = list(rec)
+    rec.clear()
+    f.ok(P.lib().cgs_solver_kernel_time(h, 2 + adj, 1, C.byref(C.c_double())))
+    return apply, rec
+
+
+SCENARIOS = {v.__name__: v for v in (dense_launches, direct_convolution, lds_by_current_device, launches_of_creation, steps_of_launches, timed_steps,
                                      product_gates)}
 
 
@@ -238,6 +263,16 @@ def test_form_of_the_direct_convolution(fake, n, k, precision, per, lds):
     it is the faster one; the wide form's chunks of taps leave the LDS for eight waves."""
     tile = 256 if precision == 0 else 512
     assert fake(direct_convolution, n, k, precision) == [[per * -(-(n + k - 1) // tile), lds]]
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("adj", [0, 1])
+def test_timed_dense_products_are_an_applys(fake, precision, adj):
+    """Two dense blocks that own their ranges: the timing call launches what an apply does,
+    initialisation and the written base and identity blocks included."""
+    apply, timed = fake(dense_launches, precision, adj)
+    assert len(apply) == (6 if precision == 2 else 2) and timed == apply
+    assert all(own == 1 for _, _, own in apply if own is not None)
 
 
 G_ADMM, G_ADMM_CG = 3, 4      # enum Gate
