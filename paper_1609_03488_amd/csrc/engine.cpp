@@ -716,7 +716,7 @@ int Engine::build(const std::vector<InstRec>& r) {
             d.fused = FUSED_REG + v;
             fused_reg = std::max(fused_reg, std::min(lds, fused_reg_bytes(prec, d.n, d.m, im.cblk[d.cb0],
                                                                           kRegVariants[v].r, true)));
-            if (prec == 0 && setup_cg_takes(d, im.cblk[d.cb0], lds))
+            if (prec == 0 && setup_cg_takes(d, im.cblk[d.cb0], lds, st.setup_max_iters))
                 setup_lds = std::max(setup_lds, setup_cg_bytes(d, im.cblk[d.cb0]));
         } else {
             fused_general = 1;
@@ -1281,11 +1281,11 @@ int Engine::setup() {
                    G_SETUP, stream);
     int it = 0;
     // instances whose whole loop runs in one launch; the others' runs launch by launch
-    bool rest = setup_lds == 0 || st.setup_max_iters > SETUP_CG_ITERS;
+    bool rest = setup_lds == 0;
     if (!rest) {
         launch_setup_cg(T, setup_lds, st.setup_max_iters, stream);
         for (const InstDesc& d : im.inst)
-            rest = rest || d.fused < FUSED_REG || !setup_cg_takes(d, im.cblk[d.cb0], setup_lds);
+            rest = rest || d.fused < FUSED_REG || !setup_cg_takes(d, im.cblk[d.cb0], setup_lds, st.setup_max_iters);
     }
     while (it < st.setup_max_iters) {
         const int nb = rest ? std::min(8, st.setup_max_iters - it) : 0;

@@ -1079,7 +1079,7 @@ __global__ __launch_bounds__(FNT) void k_setup_cg(Tables tb, int cg_max, int64_t
     extern __shared__ __align__(16) unsigned char fsmem[];
     __shared__ double sh[4 * (DOT_NT / 64)];
     const InstDesc d = tb.inst[blockIdx.x];
-    if (d.fused < FUSED_REG || !setup_cg_takes(d, tb.cblk[d.cb0], lds_bytes) || !gate_ok(scal(d), G_SETUP_CG)) return;
+    if (d.fused < FUSED_REG || !setup_cg_takes(d, tb.cblk[d.cb0], lds_bytes, cg_max) || !gate_ok(scal(d), G_SETUP_CG)) return;
     double* lds = reinterpret_cast<double*>(fsmem);
     switch (d.fused - FUSED_REG) {
 #define CGS_SETUP(V) \

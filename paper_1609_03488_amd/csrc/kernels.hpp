@@ -225,13 +225,16 @@ constexpr RegVariant kRegVariants[] = {{1, 2, 3}, {1, 3, 4}, {2, 3, 5}, {2, 5, 7
 constexpr int kNumRegVariants = 8;
 constexpr int FUSED_THREADS = 512, FUSED_REG = 16, FUSED_REG_IDS = 16;
 // The CG loop of the FP64 setup solve in one launch (k_setup_cg), for instances of the
-// register form (d.fused >= FUSED_REG) with one X tile whose vectors fit the LDS; iteration
-// limits up to SETUP_CG_ITERS, so that a launch ends within about 0.1 s (6 us an iteration)
-// and a larger limit, which only a tolerance below rounding reaches, stays with the host's loop.
-constexpr int SETUP_CG_ITERS = 16384;
+// register form (d.fused >= FUSED_REG) with one X tile whose vectors fit the LDS, as long as
+// the launch ends within about 0.1 s at its iteration limit: an iteration takes at most
+// 10 us + 16 ns per tap and output of a thread (n = 1000: k = 25 5.5, k = 101 8.1, k = 1000
+// 51 us; n = 2000, k = 49 12).  A larger limit, which only a tolerance below rounding
+// reaches, stays with the host's loop.
+constexpr int64_t SETUP_CG_BASE = 640, SETUP_CG_WORK = 6400000;   // in those 16 ns
 __host__ __device__ int64_t setup_cg_bytes(const InstDesc& d, const ConvBlock& cb);
-__host__ __device__ inline bool setup_cg_takes(const InstDesc& d, const ConvBlock& cb, int64_t lds) {
-    return d.xt1 - d.xt0 == 1 && setup_cg_bytes(d, cb) <= lds;
+__host__ __device__ inline bool setup_cg_takes(const InstDesc& d, const ConvBlock& cb, int64_t lds, int cg_max) {
+    return d.xt1 - d.xt0 == 1 && setup_cg_bytes(d, cb) <= lds &&
+           (SETUP_CG_BASE + kRegVariants[d.fused - FUSED_REG].r * cb.kpad) * cg_max <= SETUP_CG_WORK;
 }
 void launch_setup_cg(const Tables& t, int64_t lds, int cg_max, hipStream_t st);
 // LDS bytes an instance needs, with the step's vectors (used where they fit) or without

@@ -196,7 +196,16 @@ def dense_launches(f, precision, adj):
     return apply, rec
 
 
-SCENARIOS = {v.__name__: v for v in (dense_launches, direct_convolution, lds_by_current_device, launches_of_creation, steps_of_launches, timed_steps,
+def setup_launches(f, n, k, limit):
+    """CG launches of the FP64 setup solve of one instance that needs no iteration."""
+    f.scalars = dict(SC_ACTIVE=1.0, SC_PHASE=0.0)
+    h = f.solver(f.deconv(int(n), int(k)), precision=f.P.FP64, fused_lone_max=0, setup_max_iters=int(limit))
+    f.launches.clear()
+    f.ok(f.P.lib().cgs_solver_iterate(h, 0))
+    return sorted({v["name"] for v in f.launches} & {"k_setup_cg", "k_cg_update"})
+
+
+SCENARIOS = {v.__name__: v for v in (setup_launches, dense_launches, direct_convolution, lds_by_current_device, launches_of_creation, steps_of_launches, timed_steps,
                                      product_gates)}
 
 
@@ -273,6 +282,16 @@ def test_timed_dense_products_are_an_applys(fake, precision, adj):
     apply, timed = fake(dense_launches, precision, adj)
     assert len(apply) == (6 if precision == 2 else 2) and timed == apply
     assert all(own == 1 for _, _, own in apply if own is not None)
+
+
+# 640 units and one per padded tap (28, 104, 1000) and output of a thread (2, 3, 4) an iteration
+@pytest.mark.parametrize("n,k,limit,alone", [(600, 25, 500, True), (600, 25, 9195, True), (600, 25, 9196, False),
+                                             (1000, 101, 6722, True), (1000, 101, 6723, False),
+                                             (1000, 1000, 1379, True), (1000, 1000, 1380, False)])
+def test_setup_launch_is_bounded_by_its_work(fake, n, k, limit, alone):
+    """The setup solve runs in one launch where its iteration limit keeps that within 6.4
+    million units (0.1 s at 16 ns), else launch by launch."""
+    assert fake(setup_launches, n, k, limit) == (["k_setup_cg"] if alone else ["k_cg_update"])
 
 
 G_ADMM, G_ADMM_CG = 3, 4      # enum Gate
