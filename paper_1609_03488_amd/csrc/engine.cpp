@@ -1073,8 +1073,7 @@ void Engine::refresh() {
         fa.refresh = 1;
         fa.general = 1;   // (in the general form: the two forms' products are the same)
         fa.kc = fused_kc;
-        fa.lds_cap = fused_lds;
-        launch_fused(prec, T, fa, stream);
+        launch_fused(prec, T, fa, fused_lds, stream);
     }
     if (n_multi) {
         launch_wy(prec, T, G_ADMM, stream);                      // w_y = u_y + v_s
@@ -1096,11 +1095,10 @@ void Engine::fused_steps(int nsteps, int check) {
     fa.cg_max = st.cg_max_iters;
     fa.max_iters = st.max_iters;
     fa.kc = fused_kc;
-    fa.lds_cap = fused_lds;
     fa.res_want = fused_res;
     fa.general = fused_general;
     fa.reg_want = fused_reg;
-    launch_fused(prec, T, fa, stream);
+    launch_fused(prec, T, fa, fused_lds, stream);
 }
 
 // nsteps steps of the fused instances with a test after every check_every of them: a launch

@@ -266,6 +266,10 @@ DEVI void record_state(gptr<double> sc, const FusedArgs& fa, double tau, double 
 // the test ends an instance inside it.  Arithmetic and order of every sum are those of
 // the general form: identical results.
 
+// Dynamic LDS behind the form's own: the cone's tail partials (static LDS the general form
+// would lose as well)
+constexpr int REG_SCRATCH = FNT * (int)sizeof(double);
+
 template <typename T> using cptr = const __attribute__((address_space(4))) T*;
 
 // N sums over the workgroup, each in the order of bsum, with one barrier; sh: two
@@ -361,7 +365,8 @@ __host__ __device__ inline RegLds reg_lds(int n, int m, int n_in, int k, int kpa
 
 // R: convolution outputs per thread; NX, NY: a thread's most elements of an X / Y vector
 template <typename T, int R, int NX, int NY>
-DEVI void fused_reg(const Tables& tb, const FusedArgs& fa, const InstDesc& d, T* lds, double* sh, double* idw) {
+DEVI void fused_reg(const Tables& tb, const FusedArgs& fa, const InstDesc& d, T* lds, double* sh, double* idw,
+                    double* tails) {
     gptr<double> sc = scal(d);
     const int tid = threadIdx.x;
     const ConvBlock& cbr = tb.cblk[d.cb0];
@@ -586,10 +591,10 @@ DEVI void fused_reg(const Tables& tb, const FusedArgs& fa, const InstDesc& d, T*
                 if (i == s0) sh[2 * 6 * (FNT / 64)] = pv;
                 else s4[0] = fma(pv, pv, s4[0]);
             });
-            sh[2 * 6 * (FNT / 64) + 1 + ((tid - s0 - 1) & (FNT - 1))] = s4[0];
+            tails[(tid - s0 - 1) & (FNT - 1)] = s4[0];
             __syncthreads();
             const double t = sh[2 * 6 * (FNT / 64)];
-            s4[0] = sh[2 * 6 * (FNT / 64) + 1 + tid];
+            s4[0] = tails[tid];
             rsum<1>(s4, sh, turn);
             nz = sqrt(s4[0]);
             if (nz <= t) mode = 0;
@@ -670,16 +675,18 @@ DEVI void fused_reg(const Tables& tb, const FusedArgs& fa, const InstDesc& d, T*
 template <typename T>
 __global__ __launch_bounds__(FNT) void k_fused(Tables tb, FusedArgs fa) {
     extern __shared__ __align__(16) unsigned char fsmem[];
-    __shared__ double sh[2 * 6 * (FNT / 64) + 1 + FNT];   // (register form: sums, cone head, tail partials)
+    __shared__ double sh[2 * 6 * (FNT / 64) + 1];   // (register form: sums, cone head)
     __shared__ double idw[FUSED_REG_IDS];
+    static_assert(sizeof sh + sizeof idw <= FUSED_STATIC_LDS, "declared LDS");
     const InstDesc d = tb.inst[blockIdx.x];
     gptr<double> sc = scal(d);
     if (!(sc[SC_ACTIVE] != 0.0 && sc[SC_PHASE] == 2.0)) return;
     if (d.fused >= FUSED_REG && !fa.refresh) {
         T* lds = reinterpret_cast<T*>(fsmem);
+        double* tails = reinterpret_cast<double*>(fsmem + fa.lds_reg);
         switch (d.fused - FUSED_REG) {
 #define CGS_REG(V) \
-    case V: fused_reg<T, kRegVariants[V].r, kRegVariants[V].nx, kRegVariants[V].ny>(tb, fa, d, lds, sh, idw); break
+    case V: fused_reg<T, kRegVariants[V].r, kRegVariants[V].nx, kRegVariants[V].ny>(tb, fa, d, lds, sh, idw, tails); break
             CGS_REG(0);
             CGS_REG(1);
             CGS_REG(2);
@@ -690,7 +697,7 @@ __global__ __launch_bounds__(FNT) void k_fused(Tables tb, FusedArgs fa) {
 #undef CGS_REG
             default:
                 if constexpr (sizeof(T) == 4)
-                    fused_reg<T, kRegVariants[7].r, kRegVariants[7].nx, kRegVariants[7].ny>(tb, fa, d, lds, sh, idw);
+                    fused_reg<T, kRegVariants[7].r, kRegVariants[7].nx, kRegVariants[7].ny>(tb, fa, d, lds, sh, idw, tails);
         }
         return;
     }
@@ -1104,7 +1111,7 @@ int64_t fused_reg_bytes(int prec, int64_t n, int64_t m, const ConvBlock& cb, int
     const int64_t es = prec == 0 ? 8 : 4;
     int64_t e = reg_lds((int)n, (int)m, (int)cb.n_in, (int)cb.k, (int)cb.kpad, R).total;
     if (vectors) e += 3 * ((n + 3) & ~int64_t(3)) + 4 * ((m + 3) & ~int64_t(3));
-    return e * es;
+    return REG_SCRATCH + ((e * es + 15) & ~int64_t(15));
 }
 
 size_t fused_smem_bytes(int prec, int kc) {
@@ -1123,22 +1130,14 @@ int64_t fused_resident_bytes(int prec, int64_t n, int64_t m) {
 // Dynamic LDS per workgroup that the fused kernels may take on each device (0: not yet queried)
 static std::atomic<int> g_fused_lds[64];   // (zero-initialised: static storage)
 
-static int fused_static_lds() {
-    int b = 0;
-    hipFuncAttributes a;
-    if (hipFuncGetAttributes(&a, (const void*)k_fused<double>) == hipSuccess) b = std::max(b, (int)a.sharedSizeBytes);
-    if (hipFuncGetAttributes(&a, (const void*)k_fused<float>) == hipSuccess) b = std::max(b, (int)a.sharedSizeBytes);
-    return b > 0 ? b : 1024;
-}
-
 // (the kernels' attributes belong to the calling thread's current device)
 int fused_prepare(int dev) {
-    if (dev < 0 || dev >= 64) return 65536 - 1024;
+    if (dev < 0 || dev >= 64) return 65536 - FUSED_STATIC_LDS;
     if (g_fused_lds[dev].load() == 0) {
         int cur = dev;
         (void)hipGetDevice(&cur);
-        if (cur != dev && hipSetDevice(dev) != hipSuccess) return 65536 - 1024;
-        const int fixed = fused_static_lds();   // the kernels' own __shared__ arrays
+        if (cur != dev && hipSetDevice(dev) != hipSuccess) return 65536 - FUSED_STATIC_LDS;
+        const int fixed = FUSED_STATIC_LDS;
         int v = 0;
         if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || v <= 0)
             v = 65536;
@@ -1157,14 +1156,14 @@ int fused_prepare(int dev) {
     return g_fused_lds[dev].load();
 }
 
-void launch_fused(int prec, const Tables& t, FusedArgs fa, hipStream_t st) {
+void launch_fused(int prec, const Tables& t, FusedArgs fa, int64_t lds_cap, hipStream_t st) {
     if (t.ninst <= 0) return;
-    const int64_t cap = fa.lds_cap;
     fa.lds_conv = ((int64_t)fused_smem_bytes(prec, fa.kc) + 15) & ~int64_t(15);
     if (!fa.general) fa.lds_conv = 0;
-    fa.lds_res = std::max<int64_t>(0, std::min<int64_t>(fa.res_want, cap - fa.lds_conv));
-    fa.lds_reg = std::min(std::max(fa.reg_want, fa.lds_conv + fa.lds_res), cap);
-    const size_t lds = (size_t)std::max(fa.lds_conv + fa.lds_res, fa.lds_reg);
+    fa.lds_res = std::max<int64_t>(0, std::min<int64_t>(fa.res_want, lds_cap - fa.lds_conv));
+    const int64_t reg = std::min(std::max(fa.reg_want, fa.lds_conv + fa.lds_res), lds_cap);
+    fa.lds_reg = (reg - REG_SCRATCH) & ~int64_t(15);
+    const size_t lds = (size_t)std::max(fa.lds_conv + fa.lds_res, reg);
     if (prec == 0) k_fused<double><<<t.ninst, FNT, lds, st>>>(t, fa);
     else k_fused<float><<<t.ninst, FNT, lds, st>>>(t, fa);
 }

@@ -205,11 +205,10 @@ struct FusedArgs {
     // set by launch_fused: LDS bytes of the convolution's staging area, and
     // the bytes after it that hold an instance's most used vectors
     int64_t lds_conv, lds_res;
-    int64_t lds_cap;    // dynamic LDS bytes a workgroup may take on the stream's device (fused_prepare)
     int64_t res_want;   // bytes those vectors of the largest instance take (0: none)
     int general;        // some instance takes the general form
     int64_t reg_want;   // LDS bytes of the largest instance of the register form (0: none)
-    int64_t lds_reg;    // set by launch_fused: LDS bytes an instance of that form may use
+    int64_t lds_reg;    // set by launch_fused: LDS bytes an instance of that form may use ahead of the tail partials
 };
 // Register form of the fused steps: InstDesc::fused = FUSED_REG + the variant, which
 // takes r convolution outputs and at most nx / ny elements of an X / Y vector to each
@@ -224,6 +223,7 @@ constexpr RegVariant kRegVariants[] = {{1, 2, 3}, {1, 3, 4}, {2, 3, 5}, {2, 5, 7
                                        {3, 4, 7}, {4, 5, 9}, {4, 9, 13}, {8, 9, 17}};
 constexpr int kNumRegVariants = 8;
 constexpr int FUSED_THREADS = 512, FUSED_REG = 16, FUSED_REG_IDS = 16;
+constexpr int FUSED_STATIC_LDS = 912;   // __shared__ bytes of k_fused and k_setup_cg, each at most
 // The CG loop of the FP64 setup solve in one launch (k_setup_cg), for instances of the
 // register form (d.fused >= FUSED_REG) with one X tile whose vectors fit the LDS, as long as
 // the launch ends within about 0.1 s at its iteration limit: an iteration takes at most
@@ -245,9 +245,9 @@ size_t fused_smem_bytes(int prec, int kc);
 int64_t fused_resident_bytes(int prec, int64_t n, int64_t m);
 // queries the LDS per workgroup of device dev (whatever device is current) and lets the
 // fused kernels take it (once per device, outside any stream capture); returns that limit,
-// by which an instance's form is chosen and which every launch gets as FusedArgs::lds_cap
+// by which an instance's form is chosen and which every launch gets (lds_cap)
 int fused_prepare(int dev);
-void launch_fused(int prec, const Tables& t, FusedArgs fa, hipStream_t st);
+void launch_fused(int prec, const Tables& t, FusedArgs fa, int64_t lds_cap, hipStream_t st);
 
 // ---- batched dense applies as BF16 MFMA GEMMs (gemm.hip)
 struct GemmPlan {

@@ -205,7 +205,32 @@ def setup_launches(f, n, k, limit):
     return sorted({v["name"] for v in f.launches} & {"k_setup_cg", "k_cg_update"})
 
 
-SCENARIOS = {v.__name__: v for v in (setup_launches, dense_launches, direct_convolution, lds_by_current_device, launches_of_creation, steps_of_launches, timed_steps,
+def general_form_lds(f, attributes):
+    """Dynamic LDS of the fused steps of an instance of the general form (two convolutions)
+    that could use more than there is; attributes = 0: the runtime does not tell a kernel's
+    attributes."""
+    f.hip.fake_func_attributes(int(attributes))
+    op = f.P.Operator(8000, 7000).add_conv(0, 0, np.ones(101), 3000).add_conv(4000, 3500, np.ones(31), 3000)
+    pr = types.SimpleNamespace(op=op, l=8000, q=[], b=np.ones(8000), c=np.ones(7000))
+    h = f.solver(pr, precision=f.P.FP64, fused_lone_max=0)
+    f.launches.clear()
+    f.ok(f.P.lib().cgs_solver_iterate(h, 3))
+    return max(v["lds"] for v in f.launches if v["name"] == "k_fused")
+
+
+def static_lds(obj, tmp):
+    """Static LDS bytes of the kernels of an object file compiled for gfx950."""
+    llvm = "/opt/rocm/llvm/bin/"
+    fat, code = os.path.join(tmp, "fat"), os.path.join(tmp, "code")
+    subprocess.run([llvm + "llvm-objcopy", f"--dump-section=.hip_fatbin={fat}", obj, os.path.join(tmp, "out")], check=True)
+    subprocess.run([llvm + "clang-offload-bundler", "--unbundle", "--type=o", f"--input={fat}", f"--output={code}",
+                    "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"], check=True)
+    notes = subprocess.run([llvm + "llvm-readelf", "--notes", code], check=True, capture_output=True, text=True).stdout
+    return dict(zip(re.findall(r"^ +\.name: +_\S*?(k_[a-z_]+I?[df]?)\S*$", notes, re.M),
+                    map(int, re.findall(r"\.group_segment_fixed_size: (\d+)", notes))))
+
+
+SCENARIOS = {v.__name__: v for v in (general_form_lds, setup_launches, dense_launches, direct_convolution, lds_by_current_device, launches_of_creation, steps_of_launches, timed_steps,
                                      product_gates)}
 
 
@@ -292,6 +317,19 @@ def test_setup_launch_is_bounded_by_its_work(fake, n, k, limit, alone):
     """The setup solve runs in one launch where its iteration limit keeps that within 6.4
     million units (0.1 s at 16 ns), else launch by launch."""
     assert fake(setup_launches, n, k, limit) == (["k_setup_cg"] if alone else ["k_cg_update"])
+
+
+@pytest.mark.parametrize("attributes", [0, 1])
+def test_general_form_takes_the_lds_there_is(fake, tmp_path, attributes):
+    """Static and dynamic LDS together are the workgroup's 160 KB, whether or not the runtime
+    tells the kernels' attributes, and nearly all of it is dynamic."""
+    obj = os.path.join(ROOT, "paper_1609_03488_amd", "_build", "fused_hip.o")
+    if not os.path.exists(obj):
+        pytest.skip("objects of the build are not there")
+    static = static_lds(obj, str(tmp_path))
+    dynamic = fake(general_form_lds, attributes)
+    assert set(static) == {"k_fusedId", "k_fusedIf", "k_setup_cg"}
+    assert dynamic + max(static.values()) <= 160 << 10 and dynamic >= (160 << 10) - 1024
 
 
 G_ADMM, G_ADMM_CG = 3, 4      # enum Gate
