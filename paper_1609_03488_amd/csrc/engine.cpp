@@ -1240,18 +1240,25 @@ int Engine::get_point(int i, double* x, double* y, double* sl) {
     const int64_t n = im.inst[(size_t)i].n, m = im.inst[(size_t)i].m;
     double* outs[3] = {x, y, sl};
     const int64_t lens[3] = {n, m, m};
-    if (n + 2 * m <= std::max(stg.cap, stg.host_cap)) {
+    int want = 0;
+    int64_t total = 0;
+    for (int w = 0; w < 3; ++w)
+        if (outs[w]) want |= 1 << w, total += lens[w];
+    if (want == 0) return CGS_OK;
+    if (total <= std::max(stg.cap, stg.host_cap)) {
         // one launch, one wait (a copy and a wait for each vector took 75 us)
         const bool direct = stg.host_cap > 0;
-        launch_extract_point(prec, inst_dev, i, n, m, direct ? stg.host : stg.dev, stream);
+        launch_extract_point(prec, inst_dev, i, want, n, m, direct ? stg.host : stg.dev, stream);
         CGS_HIP(hipGetLastError());
         if (!direct)
-            CGS_HIP(hipMemcpyAsync(stg.host, stg.dev, (size_t)(n + 2 * m) * sizeof(double), hipMemcpyDeviceToHost,
-                                   stream));
+            CGS_HIP(hipMemcpyAsync(stg.host, stg.dev, (size_t)total * sizeof(double), hipMemcpyDeviceToHost, stream));
         CGS_HIP(hipStreamSynchronize(stream));
         const double* h = stg.host;
-        for (int w = 0; w < 3; h += lens[w], ++w)
-            if (outs[w]) std::memcpy(outs[w], h, (size_t)lens[w] * sizeof(double));
+        for (int w = 0; w < 3; ++w) {
+            if (!outs[w]) continue;
+            std::memcpy(outs[w], h, (size_t)lens[w] * sizeof(double));
+            h += lens[w];
+        }
         return CGS_OK;
     }
     for (int w = 0; w < 3; ++w) {

@@ -1088,16 +1088,22 @@ __global__ void k_extract(const InstDesc* insts, int inst, int what, int64_t off
          i += (int64_t)gridDim.x * blockDim.x)
         out[i] = x.at(off + i);
 }
-// x, y and s of an instance one after the other (gridDim.y = 3)
+// those of x, y and s (bits 0 to 2 of want) of an instance one after the other, one to
+// each blockIdx.y
 template <typename T>
-__global__ void k_extract_point(const InstDesc* insts, int inst, double* out) {
+__global__ void k_extract_point(const InstDesc* insts, int inst, int want, double* out) {
     const InstDesc d = insts[inst];
-    const Extract<T> x(d, blockIdx.y);
-    const int64_t len = blockIdx.y == 0 ? d.n : d.m;
-    double* o = out + (blockIdx.y == 0 ? 0 : d.n + (blockIdx.y - 1) * d.m);
+    int what = 0;
+    for (int left = blockIdx.y;; ++what) {
+        if (!((want >> what) & 1)) continue;
+        if (left-- == 0) break;
+        out += what == 0 ? d.n : d.m;
+    }
+    const Extract<T> x(d, what);
+    const int64_t len = what == 0 ? d.n : d.m;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < len;
          i += (int64_t)gridDim.x * blockDim.x)
-        o[i] = x.at(i);
+        out[i] = x.at(i);
 }
 // an instance's scaled data, FP64 [b^ (m) | D (m) | c^ (n) | E (n) | sb, sc], into its region
 template <typename T>
@@ -1325,11 +1331,12 @@ void launch_extract(int prec, const InstDesc* inst_dev, int inst, int what, int6
     CGS_DISPATCH(prec, k_extract, flat_grid(len, 256), 256, st, inst_dev, inst, what, off, len,
                  out64);
 }
-void launch_extract_point(int prec, const InstDesc* inst_dev, int inst, int64_t n, int64_t m, double* out,
+void launch_extract_point(int prec, const InstDesc* inst_dev, int inst, int want, int64_t n, int64_t m, double* out,
                           hipStream_t st) {
-    const dim3 g((unsigned)flat_grid(std::max(n, m), 256), 3);
-    if (prec == 0) k_extract_point<double><<<g, 256, 0, st>>>(inst_dev, inst, out);
-    else k_extract_point<float><<<g, 256, 0, st>>>(inst_dev, inst, out);
+    const int64_t len = (want & 1) ? std::max(n, (want & 6) ? m : 0) : m;
+    const dim3 g((unsigned)flat_grid(len, 256), (unsigned)((want & 1) + ((want >> 1) & 1) + ((want >> 2) & 1)));
+    if (prec == 0) k_extract_point<double><<<g, 256, 0, st>>>(inst_dev, inst, want, out);
+    else k_extract_point<float><<<g, 256, 0, st>>>(inst_dev, inst, want, out);
 }
 void launch_put_data(int prec, const double* src, char* base, int64_t n, int64_t m, int64_t nxs, int64_t nys,
                      hipStream_t st) {

@@ -161,9 +161,9 @@ void launch_copy(int prec, const Tables& t, int is_y, int dst, int src, int gate
 //   scales x, s by 1/(-c^T u_x).
 void launch_extract(int prec, const InstDesc* inst_dev, int inst, int what, int64_t off,
                     int64_t len, double* out64, hipStream_t st);
-// x, y, s (what 0, 1, 2) of an instance, one after the other: n + 2 m doubles (device
-// memory or pinned host memory)
-void launch_extract_point(int prec, const InstDesc* inst_dev, int inst, int64_t n, int64_t m, double* out,
+// those of x, y, s (bits 0, 1, 2 of want, not 0) of an instance, one after the other, into
+// device memory or pinned host memory
+void launch_extract_point(int prec, const InstDesc* inst_dev, int inst, int want, int64_t n, int64_t m, double* out,
                           hipStream_t st);
 // scaled data [b^ (m) | D (m) | c^ (n) | E (n) | sb, sc] (FP64) into the region at `base`
 void launch_put_data(int prec, const double* src, char* base, int64_t n, int64_t m, int64_t nxs, int64_t nys,

@@ -329,3 +329,25 @@ def test_start_test_ahead_of_the_products(family, prec, batch, cg_tol):
 def test_direct_convolution_forms(n, k, prec):
     """The bound of test_direct_convolution_edges, at the edges of the rule on kernel lengths."""
     test_direct_convolution_edges(n, k, prec)
+
+
+@pytest.mark.parametrize("n", [1, 300, 3000, 200000])
+@pytest.mark.parametrize("prec", [P.FP64, P.FP32], ids=["fp64", "fp32"])
+def test_parts_of_a_solution(n, prec):
+    """x, y or s alone, and any two, are the parts of the whole solution, bit for bit: in one
+    piece, and (n = 200000: more than 2^20 doubles of data, more than 65536 of a vector) piece by piece."""
+    import ctypes as C
+    print("[case] parts of a solution", n, prec, flush=True)
+    rng = np.random.default_rng(n)
+    op = P.Operator(2 * n, n).add_identity(0, 0, n).add_identity(n, 0, n, -0.5)
+    s = P.Solver(op, 2 * n, [], P.Settings.make(precision=prec, max_iters=20, fused_max=0))
+    s.set_data(0, np.abs(rng.standard_normal(2 * n)), rng.standard_normal(n))
+    s.solve()
+    whole = s.solution(0)
+    for want in range(1, 8):
+        out = [np.full(v.size, np.pi) for v in whole]
+        rc = P.lib().cgs_solver_get_solution(s._h, 0, *((v.ctypes.data_as(C.POINTER(C.c_double)) if want >> i & 1
+                                                         else None) for i, v in enumerate(out)))
+        assert rc == 0
+        for i in range(3):
+            np.testing.assert_array_equal(out[i], whole[i] if want >> i & 1 else np.full(whole[i].size, np.pi))

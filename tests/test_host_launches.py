@@ -230,7 +230,19 @@ def static_lds(obj, tmp):
                     map(int, re.findall(r"\.group_segment_fixed_size: (\d+)", notes))))
 
 
-SCENARIOS = {v.__name__: v for v in (general_form_lds, setup_launches, dense_launches, direct_convolution, lds_by_current_device, launches_of_creation, steps_of_launches, timed_steps,
+def vectors_moved(f, want):
+    """Vectors the device hands over for a solution call with x, y and s (bits of want)."""
+    want = int(want)
+    h = f.solver(f.deconv(3000, 31))
+    out = [np.full(n, 7.0) for n in (3001, 6031, 6031)]
+    f.launches.clear()
+    f.ok(f.P.lib().cgs_solver_get_solution(h, 0, *((v.ctypes.data_as(C.POINTER(C.c_double)) if want >> i & 1 else None)
+                                                   for i, v in enumerate(out))))
+    assert [bool((v != 7.0).all()) for v in out] == [bool(want >> i & 1) for i in range(3)]
+    return sum(v["grid"][1] for v in f.launches if v["name"].startswith("k_extract"))
+
+
+SCENARIOS = {v.__name__: v for v in (vectors_moved, general_form_lds, setup_launches, dense_launches, direct_convolution, lds_by_current_device, launches_of_creation, steps_of_launches, timed_steps,
                                      product_gates)}
 
 
@@ -330,6 +342,11 @@ def test_general_form_takes_the_lds_there_is(fake, tmp_path, attributes):
     dynamic = fake(general_form_lds, attributes)
     assert set(static) == {"k_fusedId", "k_fusedIf", "k_setup_cg"}
     assert dynamic + max(static.values()) <= 160 << 10 and dynamic >= (160 << 10) - 1024
+
+
+@pytest.mark.parametrize("want", range(8))
+def test_solution_moves_what_is_asked_for(fake, want):
+    assert fake(vectors_moved, want) == bin(want).count("1")
 
 
 G_ADMM, G_ADMM_CG = 3, 4      # enum Gate
