@@ -70,7 +70,7 @@ int solver_layout(const cgs_op* op, int64_t l, const int64_t* q, int64_t nq, con
     if (st->precision == CGS_BF16) {
         for (const cgs::DenseBlock& db : shape.dense) {
             for (int adj = 0; adj < 2; ++adj) {
-                const int64_t N = adj ? db.cols : db.rows, kpad = adj ? db.ldt : db.ld;
+                const int64_t N = adj ? db.cols : db.rows, kpad = adj ? db.ldt() : db.ld();
                 for (int target = 128; target <= cgs::GEMM_TARGET_MAX; target *= 2) {
                     const cgs::GemmPlan g = cgs::gemm_plan(N, kpad, (int)batch, target);
                     L->panel = std::max(L->panel, cgs::align256((size_t)g.mpad * kpad * 2));

@@ -138,7 +138,7 @@ struct VecTile {
 
 // A piece of a vector tile outside every owned output range (an initialisation tile that
 // rides on a product's launch), in half a VecTile's bytes: a range inside a tile leaves
-// two, and the tables stay within the bytes of the whole tiles.
+// two, and the tables stay within the bytes of the whole tiles (build_image).
 struct InitPiece {
     int32_t inst;
     uint32_t start_lo;
@@ -187,7 +187,9 @@ struct ConvTile {        // CONV_TILE outputs starting at block-local `start`
 
 struct DenseBlock {      // rows x cols block
     int64_t row0, col0, rows, cols;
-    int64_t ld, ldt;     // leading dimensions of a (rows x ld) and at (cols x ldt)
+    // leading dimensions of a (rows x ld) and at (cols x ldt): whole K steps of the MFMA kernels
+    __host__ __device__ int64_t ld() const { return (cols + 15) & ~int64_t(15); }
+    __host__ __device__ int64_t ldt() const { return (rows + 15) & ~int64_t(15); }
     const void* a;       // working precision, row-major
     const void* at;      // its transpose, row-major
     const void* a16;     // BF16 (round to nearest even) copies in the GEMM's packed
@@ -221,7 +223,7 @@ struct Tables {
     double* xpart;       // 4 per X tile
     double* ypart;       // 4 per Y tile
     double* cpart;       // CG products: 4 per workgroup of the folded A^T launch, or per X tile (k_cg_dot)
-    double* spart;       // CG start: the same for the right-hand side's A^T launch, or k_cg_init's
+    double* spart;       // CG start: 2 per workgroup of the right-hand side's A^T launch, or per X tile (k_cg_init)
     // slot-major partials of the update that ends CG for the projection that
     // follows (CgStart::cone): slot 0 (tau products) of the X tiles, then slots 0 to 3
     // of the Y tiles, tpart[nx_tiles + j * ny_tiles + tile]

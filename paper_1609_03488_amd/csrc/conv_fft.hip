@@ -228,13 +228,14 @@ DEVI void out4u(gptr<float> p, int o, int lo, int hi, const f32x4& v) { out4_as<
 struct Fold4 {
     double a, b, c, d;
 };
-// The workgroup's partials of a folded CG step (every thread calls this).
+// The workgroup's partials of a folded CG step (every thread calls this): two or four.
+template <int FOLD>
 DEVI void fold_partials(double* part, const Fold4& f, double* red) {
     double v[4] = {f.a, f.b, f.c, f.d};
     block_sum4<FT>(v, red);
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) part[4 * (int64_t)blockIdx.x + j] = v[j];
+        for (int j = 0; j < 2 * FOLD; ++j) part[2 * FOLD * (int64_t)blockIdx.x + j] = v[j];
     }
 }
 
@@ -499,7 +500,7 @@ __global__ __launch_bounds__(FT) void k_conv_fft(Tables tb, ConvLaunch cl, int a
             }
         }
     }
-    if (FOLD) fold_partials(cl.part, f, red);
+    if constexpr (FOLD != 0) fold_partials<FOLD>(cl.part, f, red);
 }
 
 void launch_conv_spectrum(const void* w, int64_t k, void* spec, hipStream_t st) {

@@ -185,7 +185,7 @@ DEVI void inst_xsum4(const Tables& tb, const InstDesc& d, double (&s)[4], bool s
 #pragma unroll
     for (int j = 0; j < 4; ++j) a[j] = thread_sum<VEC_NT, 4>(tb.cpart + j, d.xt0, d.xt1, 4);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) a[4 + j] = start ? thread_sum<VEC_NT, 4>(tb.spart + j, d.xt0, d.xt1, 4) : 0.0;
+    for (int j = 0; j < 2; ++j) a[4 + j] = start ? thread_sum<VEC_NT, 4>(tb.spart + j, d.xt0, d.xt1, 2) : 0.0;
     block_sumN<VEC_NT, 6>(a, sh);
 #pragma unroll
     for (int j = 0; j < 4; ++j) s[j] = a[j];
@@ -216,7 +216,7 @@ DEVI void inst_csum4(const Tables& tb, const InstDesc& d, double (&s)[4], bool s
                 const f64x2* pc = reinterpret_cast<const f64x2*>(tb.cpart + 4 * (int64_t)k);
                 c[u][0] = pc[0];
                 c[u][1] = pc[1];
-                if (start) q[u] = *reinterpret_cast<const f64x2*>(tb.spart + 4 * (int64_t)k);
+                if (start) q[u] = *reinterpret_cast<const f64x2*>(tb.spart + 2 * (int64_t)k);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {

@@ -242,8 +242,6 @@ void op_dev_shape(const cgs_op& op, int precision, OpDev* out, const double* mul
             db.col0 = b.col0;
             db.rows = b.rows;
             db.cols = b.cols;
-            db.ld = dense_ld(b.cols);
-            db.ldt = dense_ld(b.rows);
             db.scale = scale;
             out->dense.push_back(db);
         }
@@ -318,7 +316,7 @@ int op_upload(const cgs_op& op, int precision, char* dst, const Staging& stg, hi
             CGS_HIP(hipStreamSynchronize(st));
         } else if (b.kind == CGS_BLOCK_DENSE) {
             DenseBlock& db = out->dense[di++];
-            const int64_t rows = db.rows, cols = db.cols, ld = db.ld, ldt = db.ldt;
+            const int64_t rows = db.rows, cols = db.cols, ld = db.ld(), ldt = db.ldt();
             db.a = p;
             p += align256(rows * ld * sz);
             db.at = p;
@@ -400,6 +398,13 @@ int download_f64(const Staging& stg, hipStream_t st, int prec, const void* src, 
 }
 
 // ---------------------------------------------------------------- tables
+template <typename V>
+static size_t vbytes(const std::vector<V>& v) { return align256(v.size() * sizeof(V)); }
+
+static size_t pieces_bytes(const TableImage& im) {
+    return align256((im.init[0].size() + im.init[1].size()) * sizeof(InitPiece));
+}
+
 void build_image(const std::vector<InstRec>& recs, int precision, TableImage& im, int vec_tile) {
     im = TableImage{};
     const int64_t ct = conv_tile(precision);
@@ -531,10 +536,19 @@ void build_image(const std::vector<InstRec>& recs, int precision, TableImage& im
         }
         im.all_own[adj] = 1;
     }
+    // The pieces may take the bytes that whole tiles would (and 256), no more, so that the
+    // tables never outgrow those: where many ranges lie inside tiles they do, and the outputs
+    // are initialised in a launch of their own.  (One range in a direction always fits: no
+    // instance of a table whose CG steps fold takes its neighbours' launches out of the fold.)
+    if (pieces_bytes(im) > vbytes(im.xt) + vbytes(im.yt) + 256)
+        for (int adj = 0; adj < 2; ++adj) im.all_own[adj] = 0, im.init[adj].clear();
+    // CG steps fold into the FFT engine's A^T launch when that launch (its transform
+    // workgroups and its initialisation workgroups) writes every X element: one convolution
+    // slot, all blocks owned and with spectra, no dense block.
+    im.fold = im.all_own[1] && im.cadj.size() == 1 && im.dadj.empty() && work_prec(precision) == 1 ? 1 : 0;
+    for (const ConvBlock& cb : im.cblk)
+        if (cb.k > FFT_KMAX) im.fold = 0;
 }
-
-template <typename V>
-static size_t vbytes(const std::vector<V>& v) { return align256(v.size() * sizeof(V)); }
 
 size_t image_table_bytes(const TableImage& im) {
     size_t t = vbytes(im.inst) + vbytes(im.xt) + vbytes(im.yt) + vbytes(im.seg) + vbytes(im.ids) +
@@ -545,19 +559,19 @@ size_t image_table_bytes(const TableImage& im) {
     for (const auto& v : im.fadj) t += vbytes(v);
     for (const auto& v : im.dfwd) t += vbytes(v);
     for (const auto& v : im.dadj) t += vbytes(v);
-    return t + vbytes(im.init[0]) + vbytes(im.init[1]);
+    return t + pieces_bytes(im);
 }
 
-// most workgroups of a folded A^T launch: transforms and initialisation tiles
-static size_t folded_wgs(const TableImage& im) {
-    return (im.fadj.empty() ? 0 : im.fadj[0].size()) + std::max(im.xt.size(), im.init[1].size());
+// records of the CG partials: workgroups of the folded A^T launch (transforms and
+// initialisation tiles) or, without it, X tiles
+static size_t cg_records(const TableImage& im) {
+    return im.fold ? std::max(im.xt.size(), im.fadj[0].size() + im.init[1].size()) : im.xt.size();
 }
 
 size_t image_work_bytes(const TableImage& im) {
-    const size_t nfa = folded_wgs(im);
     return align256(4 * im.xt.size() * 8) + align256(4 * im.yt.size() * 8) +
            align256(2 * im.seg.size() * 8) + align256(im.seg.size() * 4) +
-           2 * align256(4 * nfa * 8) + align256((im.xt.size() + 4 * im.yt.size()) * 8) +
+           align256((6 * cg_records(im) + im.xt.size() + 4 * im.yt.size()) * 8) +
            align256(im.inst.size() * NSC * 8);
 }
 
@@ -728,17 +742,9 @@ int Engine::build(const std::vector<InstRec>& r) {
         fold_init[adj] = conv && im.all_own[adj];
         own_dense[adj] = !conv && im.all_own[adj];
     }
-    // CG steps fold into the FFT engine's A^T launch when that launch (its
-    // transform workgroups and its initialisation workgroups) writes every X
-    // element: one convolution slot, all blocks owned and with spectra, no
-    // dense block.  Each instance's partials are then those of its transform
-    // workgroups and of its initialisation workgroups.
-    fold_cg = 0;
-    if (fold_init[1] && im.cadj.size() == 1 && im.dadj.empty() && !use_gemm && work_prec(precision) == 1) {
-        bool fft = !im.cadj[0].empty();
-        for (const ConvTile& t : im.cadj[0]) fft = fft && im.cblk[t.blk].k <= FFT_KMAX;
-        fold_cg = fft && !im.fadj.empty() ? 1 : 0;
-    }
+    // Each instance's partials are then those of its transform workgroups and of its
+    // initialisation workgroups.
+    fold_cg = im.fold && !use_gemm ? 1 : 0;
     // The right-hand side launch can also write the identity rows of A p (the
     // first CG product, p = r): possible when, in every instance on this
     // path, the convolution rows and rows reached by exactly one identity
@@ -850,11 +856,16 @@ int Engine::build(const std::vector<InstRec>& r) {
                                 fft ? (const ConvTile*)put(fv.data(), fv.size() * sizeof(ConvTile)) : nullptr,
                                 fft ? (int)fv.size() : 0, fft});
     }
+    std::vector<InitPiece> pieces(im.init[0]);
+    pieces.insert(pieces.end(), im.init[1].begin(), im.init[1].end());
+    const InitPiece* pieces_dev = (const InitPiece*)put(pieces.data(), pieces.size() * sizeof(InitPiece));
+    auto ride = [&](int adj, auto& launches) {
+        launches[0].init = pieces_dev + (adj ? im.init[0].size() : 0);
+        launches[0].ninit = (int)im.init[adj].size();
+    };
     for (int adj = 0; adj < 2; ++adj) {
         std::vector<ConvLaunch>& cl = adj ? ca : cf;
-        if (!fold_init[adj] || cl.empty()) continue;
-        cl[0].init = (const InitPiece*)put(im.init[adj].data(), im.init[adj].size() * sizeof(InitPiece));
-        cl[0].ninit = (int)im.init[adj].size();
+        if (fold_init[adj] && !cl.empty()) ride(adj, cl);
     }
     for (int adj = 0; adj < 2; ++adj) {
         const int64_t w = precision == CGS_FP64 ? 2 : 4;   // elements of a 16-byte vector
@@ -865,9 +876,7 @@ int Engine::build(const std::vector<InstRec>& r) {
                                                   (int)v.size(), vecs, nullptr, 0});
         }
         std::vector<DenseLaunch>& dl = adj ? da : df;
-        if (!own_dense[adj] || dl.empty()) continue;
-        dl[0].init = (const InitPiece*)put(im.init[adj].data(), im.init[adj].size() * sizeof(InitPiece));
-        dl[0].ninit = (int)im.init[adj].size();
+        if (own_dense[adj] && !dl.empty()) ride(adj, dl);
     }
     if (off > tab_cap) return fail(CGS_ENOMEM, "table overflow");
     CGS_HIP(hipMemcpyAsync(tab_dev, tab_host, off, hipMemcpyHostToDevice, stream));
@@ -876,9 +885,10 @@ int Engine::build(const std::vector<InstRec>& r) {
     T.ypart = (double*)w; w += align256(4 * im.yt.size() * 8);
     T.seg_val = (double*)w; w += align256(2 * im.seg.size() * 8);
     T.seg_cnt = (int*)w; w += align256(im.seg.size() * 4);
-    T.cpart = (double*)w; w += align256(4 * folded_wgs(im) * 8);
-    T.spart = (double*)w; w += align256(4 * folded_wgs(im) * 8);
-    T.tpart = (double*)w; w += align256((im.xt.size() + 4 * im.yt.size()) * 8);
+    T.cpart = (double*)w;
+    T.spart = T.cpart + 4 * cg_records(im);
+    T.tpart = T.spart + 2 * cg_records(im);
+    w += align256((6 * cg_records(im) + im.xt.size() + 4 * im.yt.size()) * 8);
     gather_dev = (double*)w;
     if (!im.seg.empty()) CGS_HIP(hipMemsetAsync(T.seg_cnt, 0, im.seg.size() * 4, stream));
     T.nx_tiles = (int)im.xt.size();

@@ -151,6 +151,7 @@ struct TableImage {
     // per direction: the blocks own their output ranges, and the pieces outside them
     int all_own[2] = {0, 0};
     std::vector<InitPiece> init[2];
+    int fold = 0;        // CG steps may fold into the FFT engine's A^T launch
 };
 // vec_tile: elements per X/Y vector tile, VEC_TILE_MIN..VEC_TILE
 void build_image(const std::vector<InstRec>& recs, int precision, TableImage& im, int vec_tile = VEC_TILE);

@@ -116,7 +116,7 @@ DEVI void fv_copy(const InstDesc& d, FVecs<T>& fv, bool in) {
 template <typename T>
 DEVI void dense_rows(const DenseBlock& db, int adj, T* out, const T* in, double sigma) {
     gptr<const T> a = (gptr<const T>)(adj ? db.at : db.a);
-    const int64_t ld = adj ? db.ldt : db.ld;
+    const int64_t ld = adj ? db.ldt() : db.ld();
     const int64_t nrows = adj ? db.cols : db.rows, ncols = adj ? db.rows : db.cols;
     T* o = out + (adj ? db.col0 : db.row0);
     const T* x = in + (adj ? db.row0 : db.col0);

@@ -334,7 +334,7 @@ void launch_gemm_apply(const Tables& tb, const DenseBlock& db, int adj, int out,
     uint16_t* panel_lo = panel + 2 * panel_stride;
     const int64_t N = adj ? db.cols : db.rows;        // outputs
     const int64_t K = adj ? db.rows : db.cols;        // inputs
-    const int64_t kpad = adj ? db.ldt : db.ld;
+    const int64_t kpad = adj ? db.ldt() : db.ld();
     const uint16_t* w_hi = (const uint16_t*)(adj ? db.at16 : db.a16);
     const uint16_t* w_lo = (const uint16_t*)(adj ? db.at16lo : db.a16lo);
     const int64_t off_in = adj ? db.row0 : db.col0;

@@ -255,7 +255,7 @@ __global__ __launch_bounds__(GEMV_NT) void k_gemv(Tables tb, DenseLaunch dl, int
     const DenseBlock db = dl.blocks[tl.blk];
     if (!gate_ok(scal(d), gate)) return;
     const int tid = threadIdx.x, wave = tid >> 6;
-    const int64_t ld = adj ? db.ldt : db.ld, ncols = adj ? db.rows : db.cols;
+    const int64_t ld = adj ? db.ldt() : db.ld(), ncols = adj ? db.rows : db.cols;
     const int64_t rows = adj ? db.cols : db.rows, per = dense_tile_rows(rows), r0 = (int64_t)tl.t * per;
     const int64_t g0 = (adj ? db.col0 : db.row0) + r0;   // the tile's first output
     gptr<const T> arow = (gptr<const T>)(adj ? db.at : db.a) + r0 * ld;
@@ -336,7 +336,7 @@ __global__ __launch_bounds__(GEMV_NT) void k_gemv(Tables tb, DenseLaunch dl, int
 // ---------------------------------------------------------------- CG
 template <typename T>
 __global__ __launch_bounds__(VEC_NT) void k_cg_init(Tables tb, int z, int r, int p, int q, int h,
-                                                    int have_q, int gate, double* parts) {
+                                                    int have_q, int gate, double* parts, int stride) {
     __shared__ double sh[VEC_NT / 64];
     const VecTile tl = tb.xt[blockIdx.x];
     const InstDesc d = tb.inst[tl.inst];
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(VEC_NT) void k_cg_init(Tables tb, int z, int r, int
     }
     s0 = block_sum<VEC_NT>(s0, sh);
     s1 = block_sum<VEC_NT>(s1, sh);
-    double* part = parts + 4 * (int64_t)blockIdx.x;
+    double* part = parts + stride * (int64_t)blockIdx.x;
     if (threadIdx.x == 0) {
         part[0] = s0;
         part[1] = s1;
@@ -1279,11 +1279,11 @@ void launch_gemv(int prec, const Tables& t, const DenseLaunch& d, int adj, int o
 }
 void launch_cg_init(int prec, const Tables& t, int z, int r, int p, int q, int h, int have_q,
                     double zeta, double rate, double floor_, int cg_max, int gate, hipStream_t st) {
-    CGS_DISPATCH(prec, k_cg_init, t.nx_tiles, VEC_NT, st, t, z, r, p, q, h, have_q, gate, t.xpart);
+    CGS_DISPATCH(prec, k_cg_init, t.nx_tiles, VEC_NT, st, t, z, r, p, q, h, have_q, gate, t.xpart, 4);
     k_finalize<<<t.ninst, VEC_NT, 0, st>>>(t, FIN_CG_INIT, gate, FinArgs{zeta, rate, floor_, cg_max, 0});
 }
 void launch_cg_start(int prec, const Tables& t, int z, int r, int p, int q, int h, int gate, hipStream_t st) {
-    CGS_DISPATCH(prec, k_cg_init, t.nx_tiles, VEC_NT, st, t, z, r, p, q, h, 1, gate, t.spart);
+    CGS_DISPATCH(prec, k_cg_init, t.nx_tiles, VEC_NT, st, t, z, r, p, q, h, 1, gate, t.spart, 2);
 }
 void launch_cg_dot(int prec, const Tables& t, int p, int q, int r, int it, int gate, hipStream_t st) {
     CGS_DISPATCH(prec, k_cg_dot, t.nx_tiles, VEC_NT, st, t, p, q, r, it, gate);

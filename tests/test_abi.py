@@ -188,3 +188,40 @@ def test_typed_dense_blocks():
         d64, e64, _ = op64.equilibrate(9, [], level=level)
         d32, e32, _ = op32.equilibrate(9, [], level=level)
         assert np.array_equal(d64, d32) and np.array_equal(e64, e32)
+
+
+# bytes of a workspace that held each operator when the tables had whole initialisation tiles:
+# batches of 1, 7 and 64, FP64 and FP32 of each.  Ranges inside a vector's one tile split it;
+# many of them must not make the tables or the partials outgrow that.
+@pytest.mark.parametrize("name,held", [
+    ("conv inside", [680448, 638720, 1560064, 1084160, 9933056, 5331712]),
+    ("conv at an end", [604928, 600832, 1051392, 829696, 5308672, 3017984]),
+    ("four convs inside", [960512, 880384, 3532800, 2173696, 27986688, 14482176]),
+    ("two dense inside", [4645632, 2929664, 5672704, 3471360, 15438848, 8626432]),
+    ("dense and conv", [1131776, 865280, 4338176, 2478336, 34806784, 17812992]),
+    ("long conv", [13519616, 7086848, 91234816, 46016256, 829531904, 415852288])])
+def test_workspace_of_split_tiles(name, held):
+    if name == "conv inside":
+        op = P.Operator(1307, 198).add_conv(400, 20, np.ones(301), 150).add_identity(0, 0, 198)
+    elif name == "conv at an end":
+        op = P.Operator(400, 300).add_conv(0, 0, np.ones(101), 300)
+    elif name == "four convs inside":
+        op = P.Operator(3663, 900)
+        for j in range(4):
+            op.add_conv(100 + 800 * j, 30 + 200 * j, np.ones(31), 150)
+    elif name == "two dense inside":
+        op = P.Operator(700, 900).add_dense(30, 40, np.ones((300, 500))).add_dense(350, 600, np.ones((200, 250)))
+    elif name == "dense and conv":
+        op = P.Operator(3000, 2500).add_dense(10, 10, np.ones((50, 70))).add_conv(700, 500, np.ones(65), 1800)
+    else:
+        op = P.Operator(70000, 65001).add_conv(200, 100, np.ones(257), 64000).add_identity(0, 0, 65001)
+    q = np.array([op.m // 2], dtype=np.int64)
+    need = []
+    for batch in (1, 7, 64):
+        for prec in (P.FP64, P.FP32):
+            nb = C.c_size_t()
+            st = P.Settings.make(precision=prec)
+            assert P.lib().cgs_workspace_bytes(op._h, op.m - op.m // 2, q.ctypes.data_as(C.POINTER(C.c_int64)), 1,
+                                               C.byref(st), batch, C.byref(nb)) == 0
+            need.append(nb.value)
+    assert all(n <= h for n, h in zip(need, held)), (need, held)
