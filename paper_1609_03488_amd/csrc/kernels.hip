@@ -575,24 +575,22 @@ __global__ __launch_bounds__(VEC_NT) void k_cg_update(Tables tb, int z, int r, i
     gptr<double> sc = scal(d);
     const double run = sc[SC_CGRUN];
     if (!gate_ok(sc, gate)) return;
-    if (run != (double)it) {
-        // the start test ahead of the products ended the step's CG
-        if (cs.tested && run < 0.0)
-            cg_elems<T>(tb, d, xt, sc, cs, false, 0.0, 0.0, false, false, true, z, r, p, q, sh);
-        return;
-    }
+    bool act = run == (double)it;
+    if (!act && !(cs.tested && run < 0.0)) return;   // (tested, < 0: the start test ahead of the products ended CG)
     const bool rec = !xt.is_y && xt.index == d.xt0 && threadIdx.x == 0;
-    double s[4];
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
     double h0 = 0.0, h1 = 0.0;
-    if (folded) inst_csum4(tb, d, s, cs.on != 0, h0, h1, sh);   // partials of the A^T launch(es)
-    else inst_xsum4(tb, d, s, cs.on != 0, h0, h1, sh);          // partials of k_cg_dot
+    if (act) {
+        if (folded) inst_csum4(tb, d, s, cs.on != 0, h0, h1, sh);   // partials of the A^T launch(es)
+        else inst_xsum4(tb, d, s, cs.on != 0, h0, h1, sh);          // partials of k_cg_dot
+    }
     double tol;
     if (cs.on) {
         // the step's CG start test, from the right-hand side launch's partials
         // ||r||^2, ||h||^2 (the products of this first iteration ran whatever
         // its outcome); every workgroup evaluates it
         tol = cg_tolerance(sc[SC_ITER], h1, cs.zeta, cs.rate, cs.floor_);
-        const bool act = cg_max > 0 && sqrt(h0) > tol && std::isfinite(h0);
+        act = cg_max > 0 && sqrt(h0) > tol && std::isfinite(h0);
         if (rec) {
             sc[SC_RR] = h0;
             sc[SC_HN] = sqrt(h1);
@@ -600,12 +598,12 @@ __global__ __launch_bounds__(VEC_NT) void k_cg_update(Tables tb, int z, int r, i
             sc[SC_CGIT] = 0.0;
             sc[SC_CGACT] = act ? 1.0 : 0.0;
         }
-        if (!act) {
-            if (cs.tau) cg_elems<T>(tb, d, xt, sc, cs, false, 0.0, 0.0, false, false, true, z, r, p, q, sh);
-            return;
-        }
     } else {
         tol = sc[SC_CGTOL];
+    }
+    if (!act) {
+        if (cs.tau) cg_elems<T>(tb, d, xt, sc, cs, false, 0.0, 0.0, false, false, true, z, r, p, q, sh);
+        return;
     }
     const double pq = s[0], rr = s[1], rq = s[2], qq = s[3];
     const double al = rr / pq;
