@@ -85,8 +85,8 @@ DEVI int tw_index(int e) {   // entry -> m
     return (((e - TW512) / 512 + 1) * ((e - TW512) % 512)) & (FFT_L - 1);
 }
 // The table's values, in device memory (one copy per GPU).  k_conv_spectrum, which an
-// operator's upload runs on its device ahead of every product, computes them and stores
-// those that are not there yet (once there, no entry is written again).  A workgroup of
+// operator's upload runs on its device ahead of every product, computes and stores those
+// that are not there yet (still zero: once there, no entry is written again).  A workgroup of
 // a product copies them to LDS beside its window loads; computing them there (eight
 // sincospi per thread) took about 0.6 us of every launch.
 __device__ float2 g_twiddles[TW_N];
@@ -246,14 +246,18 @@ __global__ __launch_bounds__(FT) void k_conv_spectrum(const float* w, int k, flo
     __shared__ cf lds[LDS_L];
     __shared__ cf tw[TW_N];
     const int t = threadIdx.x;
-    for (int e = t; e < TW_N; e += FT) {
+    TwRegs twr;
+    twr.load();
+#pragma unroll
+    for (int r = 0; r < TW_PER; ++r) {
+        const int e = t + FT * r;
+        if (twr.v[r].x != 0.0f || twr.v[r].y != 0.0f) continue;   // (no root of unity is 0)
         float sn, cs;
-        sincospif(-2.0f * (float)tw_index(e) / (float)FFT_L, &sn, &cs);
-        tw[e] = {cs, sn};
-        const float2 have = g_twiddles[e];
-        if (__float_as_uint(have.x) != __float_as_uint(cs) || __float_as_uint(have.y) != __float_as_uint(sn))
-            g_twiddles[e] = make_float2(cs, sn);
+        sincospif(-2.0f * (float)tw_index(e < TW_N ? e : 0) / (float)FFT_L, &sn, &cs);
+        twr.v[r] = make_float2(cs, sn);
+        if (e < TW_N) g_twiddles[e] = twr.v[r];
     }
+    twr.store(tw);
     cf v[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
