@@ -225,7 +225,7 @@ struct Tables {
     double* cpart;       // CG products: 4 per workgroup of the folded A^T launch, or per X tile (k_cg_dot)
     double* spart;       // CG start: 2 per workgroup of the right-hand side's A^T launch, or per X tile (k_cg_init)
     // slot-major partials of the update that ends CG for the projection that
-    // follows (CgStart::cone): slot 0 (tau products) of the X tiles, then slots 0 to 3
+    // follows (CgStart::tau): slot 0 (tau products) of the X tiles, then slots 0 to 3
     // of the Y tiles, tpart[nx_tiles + j * ny_tiles + tile]
     double* tpart;
     int nx_tiles, ny_tiles, nseg, ninst;

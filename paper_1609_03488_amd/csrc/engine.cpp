@@ -972,7 +972,7 @@ void Engine::cg_iter(int z, int gate, int cg_max, int track, int it, int last, i
         c.fit = it;
         c.part = T.cpart;
         conv(c, 1, XQ, YT, XR, 1.0, G_ADMM);
-        CgStart cs{st.cg_tol, st.cg_rate, cg_floor(), 1, 1, 1, st.alpha};
+        CgStart cs{st.cg_tol, st.cg_rate, cg_floor(), 1, 1, st.alpha};
         cs.pn = XP;
         launch_cg_update(prec, T, z, XR, XR, XQ, it, cg_max, gate, track, stream, 1, last, cs);
         return;
@@ -995,12 +995,12 @@ void Engine::cg_iter(int z, int gate, int cg_max, int track, int it, int last, i
         c.part = T.cpart;
         conv(c, 1, XQ, YT, XP, 1.0, gate);
         launch_cg_update(prec, T, z, XR, XP, XQ, it, cg_max, gate, track, stream, 1, last,
-                         CgStart{0.0, 0.0, 0.0, 0, tau, tau, st.alpha});
+                         CgStart{0.0, 0.0, 0.0, 0, tau, st.alpha});
         return;
     }
     apply(1, XQ, YT, XP, 1.0, pgate);
     launch_cg_dot(prec, T, XP, XQ, XR, it, pgate, stream);
-    CgStart cs{st.cg_tol, st.cg_rate, cg_floor(), ungated ? 1 : 0, tau, tau, st.alpha};
+    CgStart cs{st.cg_tol, st.cg_rate, cg_floor(), ungated ? 1 : 0, tau, st.alpha};
     cs.tested = start && test_first ? 1 : 0;
     launch_cg_update(prec, T, z, XR, XP, XQ, it, cg_max, gate, track, stream, 0, last, cs);
 }

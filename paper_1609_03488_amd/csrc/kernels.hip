@@ -400,8 +400,8 @@ __global__ __launch_bounds__(VEC_NT) void k_cg_dot(Tables tb, int p, int q, int 
 // The scalar products of u~_tau for one tile (Section V-B: the tau component
 // of the subspace projection): c^T z_x over an X tile, or b^T z_y over a Y
 // tile with z_y = w_y + A z (the carried product) formed, not stored; FP64 partial in
-// slot 0 of the tile's X or Y partials.  With CgStart::cone the cone terms of
-// the projection that follows are formed as well (see CgStart).
+// slot 0 of the tile in Tables::tpart, and the cone terms of
+// the projection that follows (CgStart::tau).
 //
 // The element work of the update that ends an instance's CG, and of a CG
 // update that goes on, in one routine: `upd` = 0 leaves z and A z as they are
@@ -464,12 +464,11 @@ DEVI void cg_elems(const Tables& tb, const InstDesc& d, const XYTile& xt, gptr<c
         if (tw) {
             s0 = block_sum<VEC_NT>(s0, sh);
             if (threadIdx.x == 0) {
-                double* part = tb.xpart + 4 * (int64_t)xt.index;
-                if (cs.cone) tb.tpart[xt.index] = s0;
-                else part[0] = s0;
-                if (cs.cone && xt.index == d.xt0) {
+                tb.tpart[xt.index] = s0;
+                if (xt.index == d.xt0) {
                     // for the projection: the expansion point and tau + kappa
                     // (it rewrites tau and kappa while its workgroups run)
+                    double* part = tb.xpart + 4 * (int64_t)xt.index;
                     const double ex = sc[SC_UT];
                     part[1] = std::isfinite(ex) ? ex : 0.0;
                     part[2] = sc[SC_TAU] + sc[SC_KAPPA];
@@ -485,7 +484,7 @@ DEVI void cg_elems(const Tables& tb, const InstDesc& d, const XYTile& xt, gptr<c
     gptr<const T> uyp = yvec<T>(d, YU);
     gptr<const T> vsp = yvec<T>(d, YV);
     gptr<const T> gyp = yvec<T>(d, YG);
-    const bool cone = tw && cs.cone && xt.t.seg >= 0;
+    const bool cone = tw && xt.t.seg >= 0;
     double e_pt = 0.0;
     int64_t head = -1;
     if (cone) {
@@ -549,10 +548,7 @@ DEVI void cg_elems(const Tables& tb, const InstDesc& d, const XYTile& xt, gptr<c
         }
     } else {
         s[0] = block_sum<VEC_NT>(s[0], sh);
-        if (threadIdx.x == 0) {
-            if (cs.cone) tb.tpart[b] = s[0];
-            else tb.ypart[4 * (int64_t)xt.index] = s[0];
-        }
+        if (threadIdx.x == 0) tb.tpart[b] = s[0];
     }
 }
 
@@ -691,7 +687,7 @@ __global__ __launch_bounds__(VEC_NT) void k_project(Tables tb, double alpha) {
     {
         // u~_tau = (tau + kappa + c^T z_x + b^T z_y) / eta from the slot-0
         // partials (Tables::tpart) of every X and Y tile of the instance, and the cone's head
-        // value and tail norm from the cone terms (CgStart::cone), all summed
+        // value and tail norm from the cone terms (CgStart::tau), all summed
         // in one fixed order by every workgroup
         const double* xp0 = tb.xpart + 4 * (int64_t)d.xt0;
         const double e_pt = xp0[1], wtau = xp0[2];

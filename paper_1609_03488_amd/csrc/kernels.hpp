@@ -102,21 +102,18 @@ void launch_cg_dot(int prec, const Tables& t, int p, int q, int r, int it, int g
 struct CgStart {
     double zeta, rate, floor_;
     int on;
-    // 1: the update in which an instance's CG ends also does the work of
-    // the tau products c^T z_x and b^T z_y (z_y = w_y + A z) on the final z and A z
-    // (ADMM path, where some update of the loop always runs)
-    int tau;
-    // with tau: that update also forms the cone terms of the projection that
-    // follows (launch_project): relative to
-    // the expansion point e = the previous step's u~_tau, every second-order
-    // cone row has u_bar - v = a - (u~_tau - e) b with
+    // 1: the update in which an instance's CG ends also forms the tau products c^T z_x and
+    // b^T z_y (z_y = w_y + A z) on the final z and A z (ADMM path, where some update of the
+    // loop always runs), and the cone terms of the projection that follows
+    // (launch_project): relative to the expansion point e = the previous step's u~_tau, every
+    // second-order cone row has u_bar - v = a - (u~_tau - e) b with
     //   a = alpha z_y + (1 - alpha) u_y - v_s - alpha e g_y,   b = alpha g_y,
     // so the cone's tail norm is sum a^2 - 2 (u~_tau - e) sum a b
     // + (u~_tau - e)^2 sum b^2; the tau products go to slot 0 and the sums over
     // the tail to slots 1..3 of Tables::tpart, the head's a and b to seg_val,
     // and the first X tile's workgroup stores e and tau + kappa in its X
     // partial slots 1 and 2
-    int cone;
+    int tau;
     double alpha;
     // where the next direction p' = r' + beta p is written (-1: over p).  The
     // first CG iteration of a folded ADMM step reads p = r from r's vector
@@ -128,7 +125,7 @@ struct CgStart {
 };
 void launch_cg_update(int prec, const Tables& t, int z, int r, int p, int q, int it, int cg_max,
                       int gate, int track, hipStream_t st, int folded = 0, int last = 0,
-                      CgStart cs = CgStart{0.0, 0.0, 0.0, 0, 0, 0, 0.0});
+                      CgStart cs = CgStart{0.0, 0.0, 0.0, 0, 0, 0.0});
 // (folded = 1: the partials come from the A^T launch of ConvLaunch::fold = 2;
 // last = 1: the step's last CG launch of a round run from a snapshot; when CG
 // would go on the instance is suspended, phase 3, for the host to run the
@@ -142,7 +139,7 @@ void launch_snapshot(int prec, const Tables& t, int restore, hipStream_t st);
 void launch_wy(int prec, const Tables& t, int gate, hipStream_t st);
 // relaxation, projection onto K, dual update of every X/Y entry: every
 // workgroup forms u~_tau = (tau + kappa + c^T z_x + b^T z_y) / eta from the tau
-// products' partials and the cone norms from the cone terms (CgStart::cone)
+// products' partials and the cone norms from the cone terms (CgStart::tau)
 void launch_project(int prec, const Tables& t, double alpha, hipStream_t st);
 // termination quantities from A u_x (in YT) and A^T u_y (in XT)
 void launch_resid(int prec, const Tables& t, double eps, int max_iters, int gate, hipStream_t st);
