@@ -351,3 +351,158 @@ def test_parts_of_a_solution(n, prec):
         assert rc == 0
         for i in range(3):
             np.testing.assert_array_equal(out[i], whole[i] if want >> i & 1 else np.full(whole[i].size, np.pi))
+
+
+def _layout(name, rng):
+    """Blocks (kind, row0, col0, data) of a 700 x 720 operator; entries exact in BF16."""
+    def mat(m, n):
+        return rng.integers(-4, 5, (m, n)) / 4.0
+    taps = rng.integers(-4, 5, 33) / 4.0
+    return {"rows shared": [("dense", 5, 3, mat(300, 200)), ("dense", 100, 210, mat(350, 300))],
+            "columns shared": [("dense", 5, 3, mat(200, 300)), ("dense", 210, 100, mat(300, 350))],
+            "own ranges": [("dense", 5, 3, mat(300, 200)), ("dense", 310, 207, mat(130, 450)),
+                           ("dense", 445, 660, mat(40, 40))],
+            "same place": [("dense", 5, 3, mat(200, 300)), ("dense", 5, 3, mat(200, 300))],
+            "beside a convolution": [("dense", 5, 3, mat(200, 300)), ("conv", 210, 310, taps)],
+            "across a convolution": [("dense", 5, 3, mat(200, 300)), ("conv", 100, 100, taps)]}[name]
+
+
+# which blocks own their rows or columns, and so which launches write base and identity blocks:
+# two dense blocks that share one direction, both or none, several slots, a convolution beside
+@pytest.mark.parametrize("name", ["rows shared", "columns shared", "own ranges", "same place", "beside a convolution",
+                                  "across a convolution"])
+@pytest.mark.parametrize("prec", [P.FP64, P.FP32, P.BF16], ids=["fp64", "fp32", "bf16"])
+def test_blocks_that_share_ranges(name, prec):
+    """A x and A^T y of two vectors in turn against NumPy.  Dense sums accumulate in FP64 (a
+    BF16 batch: in FP32, 720 terms at most), convolutions fuse k multiply-adds in the working
+    precision, and every block and identity rounds the output once: within
+    (terms + blocks + 4) u sum |a||x|."""
+    print("[case] shared ranges", name, prec, flush=True)
+    rng = np.random.default_rng(len(name))
+    blocks = _layout(name, rng)
+    rows, cols, n_in = 700, 720, 400
+    op, A = P.Operator(rows, cols), np.zeros((rows, cols))
+    mag = np.zeros_like(A)
+    for kind, r0, c0, a in blocks:
+        if kind == "dense":
+            op.add_dense(r0, c0, a, 0.5)
+            A[r0:r0 + a.shape[0], c0:c0 + a.shape[1]] += 0.5 * a
+            mag[r0:r0 + a.shape[0], c0:c0 + a.shape[1]] += 0.5 * np.abs(a)
+        else:
+            op.add_conv(r0, c0, a, n_in, 0.5)
+            for t in range(a.size):
+                i = np.arange(n_in)
+                A[r0 + i + t, c0 + i] += 0.5 * a[t]
+                mag[r0 + i + t, c0 + i] += 0.5 * abs(a[t])
+    for r0, c0, ln, sc in ((0, 0, 690, -0.25), (9, 2, 691, 2.0)):
+        op.add_identity(r0, c0, ln, sc)
+        A[r0 + np.arange(ln), c0 + np.arange(ln)] += sc
+        mag[r0 + np.arange(ln), c0 + np.arange(ln)] += abs(sc)
+    s = P.Solver(op, rows, [], P.Settings.make(precision=prec, normalize=0, conv_mfma=0, fused_max=0),
+                 batch=3 if prec == P.BF16 else 1)
+    u = 2.0 ** -53 if prec == P.FP64 else 2.0 ** -24
+    terms = 720 if prec == P.BF16 else 33
+    for _ in range(2):
+        for adj in (False, True):
+            v = rng.standard_normal(rows if adj else cols).astype(np.float32).astype(np.float64)
+            M, G = (A.T, mag.T) if adj else (A, mag)
+            err = np.abs(s.apply(v, transpose=adj) - M @ v)
+            assert np.all(err <= ((terms + len(blocks) + 6) * u + 720 * 2.0 ** -52) * (G @ np.abs(v)))
+
+
+# one instance, whose pieces ride on the first convolution's launch, and a batch large enough
+# that they would outgrow the whole tiles and take a launch of their own
+@pytest.mark.parametrize("prec,engine", [(P.FP64, 0), (P.FP32, 0), (P.FP32, 1), (P.FP32, 2)])
+def test_many_ranges_inside_a_tile(prec, engine):
+    """The same problem alone and as members of a batch of 64: states equal, bit for bit, and
+    A x and A^T y against NumPy within the bounds of test_convolution_with_identity_blocks."""
+    print("[case] many ranges inside a tile", prec, engine, flush=True)
+    rng = np.random.default_rng(11)
+    rows, cols, n_in, k = 3663, 900, 150, 31
+    taps = [rng.standard_normal(k) for _ in range(4)]
+    op = P.Operator(rows, cols).add_identity(0, 0, cols, -1.0)
+    for j, t in enumerate(taps):
+        op.add_conv(1000 + 600 * j, 30 + 200 * j, t, n_in)
+    b, c = np.abs(rng.standard_normal(rows)) + 1.0, rng.standard_normal(cols)
+    st = P.Settings.make(precision=prec, conv_mfma=engine, fused_max=0)
+    out = []
+    for batch in (1, 64):
+        s = P.Solver(op, rows, [], st, batch=batch)
+        for i in range(batch):
+            s.set_data(i, b, c)
+        s.iterate(5)
+        out.append(s.state(0))
+        for x, y in zip(out[0], s.state(batch - 1)):
+            np.testing.assert_array_equal(x, y)
+    s = P.Solver(op, rows, [], P.Settings.make(precision=prec, conv_mfma=engine, fused_max=0, normalize=0), batch=64)
+    u = 2.0 ** -53 if prec == P.FP64 else 2.0 ** -24
+    for adj in (False, True):
+        v = rng.standard_normal(rows if adj else cols).astype(np.float32).astype(np.float64)
+        ref = np.zeros(cols if adj else rows)
+        ref[:cols] = -v[:cols]
+        mag, bound = np.abs(ref), np.zeros(ref.size)
+        for j, t in enumerate(taps):
+            src = v[1000 + 600 * j:][:n_in + k - 1] if adj else v[30 + 200 * j:][:n_in]
+            lo, m = (30 + 200 * j, n_in) if adj else (1000 + 600 * j, n_in + k - 1)
+            conv = (lambda a, w: np.correlate(a, w, "valid")) if adj else np.convolve
+            ref[lo:lo + m] += conv(src, t)
+            mag[lo:lo + m] += conv(np.abs(src), np.abs(t))
+            bound[lo:lo + m] = _fft_bound(t, src) if engine == 2 else k * u * conv(np.abs(src), np.abs(t))
+        err = np.abs(s.apply(v, transpose=adj) - ref)
+        assert np.all(err <= bound + 5 * u * mag)
+
+
+# the convolution and its columns off the vectors' starts, the cone's head on, before and
+# after the convolution's rows, rows and columns that no block reaches
+@pytest.mark.parametrize("n,k,r0,c0,cone", [(100, 7, 3, 5, 40), (470, 31, 17, 1, 300), (900, 64, 1, 130, 500),
+                                            (1300, 101, 250, 77, 2), (2000, 33, 5, 40, 0)])
+def test_fused_register_form_of_offset_blocks(n, k, r0, c0, cone):
+    """FP64, CG to 1e-13: 12 steps of the register form (tests inside the launch after 5 and 10)
+    leave the launch-by-launch path's embedding state to 1e-8, as its oracle test asks."""
+    print("[case] register form, offset blocks", n, k, r0, c0, cone, flush=True)
+    rng = np.random.default_rng(n)
+    rows, cols = r0 + n + k - 1 + 23, c0 + n + 9
+    op = P.Operator(rows, cols).add_conv(r0, c0, rng.standard_normal(k) / k, n, -1.5)
+    op.add_identity(2, 3, min(rows, cols) - 12, -1.0).add_identity(rows - 20, 0, 15, 0.5)
+    b, c = rng.standard_normal(rows), rng.standard_normal(cols)
+    q = [rows - cone] if cone < rows else []
+    out = []
+    for fused in (0, 65536):
+        s = P.Solver(op, cone if q else rows, q, P.Settings.make(
+            precision=P.FP64, cg_tol=0.0, cg_floor=1e-13, cg_max_iters=200, setup_tol=1e-14, setup_max_iters=2000,
+            eps=1e-300, max_iters=12, check_every=5, fused_max=fused, fused_lone_max=0))
+        s.set_data(0, b, c)
+        info = s.solve()[0]
+        assert info["iters"] == 12 and info["status"] == P.MAX_ITERS
+        out.append(s.state(0))
+    scale = max(1.0, *(np.abs(v).max() for v in (out[0][0], out[0][1], out[0][3])))
+    for a, b in zip(*out):
+        assert np.abs(np.asarray(a) - np.asarray(b)).max() <= 1e-8 * scale
+
+
+# 20 (one output a thread) to 2000 variables; a certificate inside a launch of many intervals
+@pytest.mark.parametrize("n,k", [(20, 3), (600, 5), (1500, 9), (2000, 17)])
+@pytest.mark.parametrize("prec", [P.FP64, P.FP32], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("kind", ["infeasible", "unbounded"])
+def test_certificates_in_the_register_form(kind, prec, n, k):
+    """x >= 1 with w * x <= -1 (w >= 0), and minimise -sum x with x >= 0, -w * x <= 1: the
+    certificate meets the header's conditions, recomputed in FP64: -b'y = 1 and ||A'y|| <= eps,
+    or -c'x = 1 and ||A x + s|| <= eps, to 10 % for FP32's rounding of the returned point."""
+    print("[case] certificate", kind, n, k, prec, flush=True)
+    w, rows, eps = np.ones(k) / k, 2 * n + k - 1, 1e-4
+    sign = 1.0 if kind == "infeasible" else -1.0
+    op = P.Operator(rows, n).add_identity(0, 0, n, -1.0).add_conv(n, 0, w, n, sign)
+    b, c = (np.full(rows, -1.0), np.ones(n)) if sign > 0 else (np.ones(rows), np.full(n, -1.0))
+    if sign < 0:
+        b[:n] = 0.0
+    s = P.Solver(op, rows, [], P.Settings.make(precision=prec, eps=eps, max_iters=20000, fused_lone_max=0))
+    s.set_data(0, b, c)
+    info = s.solve()[0]
+    assert info["status"] == (P.INFEASIBLE if sign > 0 else P.UNBOUNDED) and info["iters"] < 20000
+    x, y, sl = s.solution(0)
+    if sign > 0:
+        aty = -y[:n] + np.correlate(y[n:], w, "valid")
+        assert np.all(y >= 0) and abs(b @ y + 1.0) <= 1e-5 and np.linalg.norm(aty) <= 1.1 * eps
+    else:
+        ax = np.concatenate([-x, -np.convolve(x, w)])
+        assert np.all(sl >= 0) and abs(c @ x + 1.0) <= 1e-5 and np.linalg.norm(ax + sl) <= 1.1 * eps
