@@ -692,12 +692,10 @@ __global__ __launch_bounds__(FNT) void k_fused(Tables tb, FusedArgs fa) {
             CGS_REG(2);
             CGS_REG(3);
             CGS_REG(4);
-            CGS_REG(5);
-            CGS_REG(6);
 #undef CGS_REG
             default:
                 if constexpr (sizeof(T) == 4)
-                    fused_reg<T, kRegVariants[7].r, kRegVariants[7].nx, kRegVariants[7].ny>(tb, fa, d, lds, sh, idw, tails);
+                    fused_reg<T, kRegVariants[5].r, kRegVariants[5].nx, kRegVariants[5].ny>(tb, fa, d, lds, sh, idw, tails);
         }
         return;
     }
@@ -1096,8 +1094,6 @@ __global__ __launch_bounds__(FNT) void k_setup_cg(Tables tb, int cg_max, int64_t
         CGS_SETUP(2);
         CGS_SETUP(3);
         CGS_SETUP(4);
-        CGS_SETUP(5);
-        CGS_SETUP(6);
 #undef CGS_SETUP
         default: break;
     }

@@ -212,13 +212,18 @@ struct FusedArgs {
 // of FUSED_THREADS threads (nx = r + 1, ny = 2 r + 1 hold a deconvolution of n <= 512 r,
 // 2 r + 1 and 3 r + 1 a lasso); at most FUSED_REG_IDS identity blocks.  The first
 // variant that holds an instance is its own; the last one is FP32 only (the FP64 state
-// of eight outputs exceeds the registers).
+// of eight outputs exceeds the registers).  us per step with an instance's own variant,
+// the next one and the general form, FP64 / FP32 (d: deconvolution, l: lasso, n, k):
+//   r = 1  l 480, 31   16.8, 16.9, 45 / 17.1, 17.6, 50     r = 4   d 2000, 45   33.5, 35.8, 46 / 25.2, 28.9, 43
+//   r = 2  d 980, 41   16.9, 18.9, 32 / 16.2, 17.0, 34     4, 9    l 1900, 101  77.2, -, 110   / 54.6, 59.2, 102
+//   r = 3  d 1480, 51  22.9, 27.9, 41 / 20.0, 21.8, 40     r = 8   d 3900, 101                   58.5, -, 69
+// (a variant 2, 5, 7 for a lasso of n <= 1023 was slower than 3, 4, 7 in FP64: 34.9, 31.8 at
+// n = 960, k = 61; FP32 28.3, 28.2.)
 struct RegVariant {
     int r, nx, ny;
 };
-constexpr RegVariant kRegVariants[] = {{1, 2, 3}, {1, 3, 4}, {2, 3, 5}, {2, 5, 7},
-                                       {3, 4, 7}, {4, 5, 9}, {4, 9, 13}, {8, 9, 17}};
-constexpr int kNumRegVariants = 8;
+constexpr RegVariant kRegVariants[] = {{1, 2, 3}, {2, 3, 5}, {3, 4, 7}, {4, 5, 9}, {4, 9, 13}, {8, 9, 17}};
+constexpr int kNumRegVariants = 6;
 constexpr int FUSED_THREADS = 512, FUSED_REG = 16, FUSED_REG_IDS = 16;
 constexpr int FUSED_STATIC_LDS = 912;   // __shared__ bytes of k_fused and k_setup_cg, each at most
 // The CG loop of the FP64 setup solve in one launch (k_setup_cg), for instances of the
