@@ -859,6 +859,10 @@ int Engine::build(const std::vector<InstRec>& r) {
     std::vector<InitPiece> pieces(im.init[0]);
     pieces.insert(pieces.end(), im.init[1].begin(), im.init[1].end());
     const InitPiece* pieces_dev = (const InitPiece*)put(pieces.data(), pieces.size() * sizeof(InitPiece));
+    int nid = 0;
+    for (const InstDesc& d : im.inst) nid = std::max(nid, d.id1 - d.id0);
+    for (ConvLaunch& c : cf) c.nid = nid;
+    for (ConvLaunch& c : ca) c.nid = nid;
     auto ride = [&](int adj, auto& launches) {
         launches[0].init = pieces_dev + (adj ? im.init[0].size() : 0);
         launches[0].ninit = (int)im.init[adj].size();

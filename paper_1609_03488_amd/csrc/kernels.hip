@@ -1219,14 +1219,19 @@ void launch_apply_init(int prec, const Tables& t, int adj, int out, int in, int 
 }
 // Workgroups per tile of the tile tables: two, in the narrow form of k_conv, where a wave's
 // own chain bounds the launch: up to 512 tiles (at most two waves per SIMD in the other
-// form) and kernels long enough for the chain to outweigh the narrow form's longer start.
-// us per launch, wide / narrow, first at 20-30 tiles, then at 490-510:
-//   FP64 k = 65    4.2 / 4.8    4.5 / 5.3      FP32 k = 5     5.1 / 4.6    5.5 / 5.0
-//        k = 129   5.0 / 5.3    5.5 / 5.9           k = 17    5.3 / 4.8    5.7 / 5.2
-//        k = 257   7.6 / 6.3    8.0 / 7.0           k = 65    5.7 / 5.3    6.0 / 5.8
-//        k = 1025 18.8 / 14.0  19.5 / 15.6          k = 1025 24.8 / 17.3  25.2 / 18.4
-// and past them (FP64 782 tiles, k = 257 and 1025) 8.4 / 8.9 and 21.6 / 22.2.
-static int conv_sub(int prec, const ConvLaunch& c) { return c.ntiles <= 512 && c.kc >= (prec == 0 ? 160 : 8) ? 2 : 1; }
+// form) and, in FP64, kernels long enough for the chain to outweigh the narrow form's longer
+// start, or several identity blocks, whose loads it has in flight with the window's.
+// us, wide / narrow, first at 20-30 tiles, then at 490-510: a launch in FP32, A and A^T with
+// their initialisation in FP64, of a deconvolution (2 identity blocks) and a lasso (8)
+//   FP32 k = 5     5.1 / 4.6    5.5 / 5.0     FP64 deconvolution        FP64 lasso
+//        k = 17    5.3 / 4.8    5.7 / 5.2     k = 5     9.2 / 10.3  10.4 / 11.4  12.7 / 12.5  15.5 / 14.7
+//        k = 65    5.7 / 5.3    6.0 / 5.8     k = 65   10.6 / 11.2  12.0 / 12.6  14.1 / 13.2  16.2 / 16.1
+//        k = 1025 24.8 / 17.3  25.2 / 18.4    k = 129  12.3 / 12.1  13.7 / 13.8  16.0 / 14.3  18.1 / 17.7
+// (FP64 launches alone, k = 257 7.6 / 6.3, 8.0 / 7.0 and 782 tiles 8.4 / 8.9; k = 1025 18.8 / 14.0,
+// 19.5 / 15.6 and 21.6 / 22.2.)
+static int conv_sub(int prec, const ConvLaunch& c) {
+    return c.ntiles <= 512 && (prec == 0 ? c.kc >= 128 || c.nid > 4 : c.kc >= 8) ? 2 : 1;
+}
 // Workgroups per initialisation tile: more where the launch is short
 static int conv_init_parts(const ConvLaunch& c) { return c.ntiles <= 512 ? 8 : 2; }
 

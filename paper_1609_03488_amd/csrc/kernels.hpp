@@ -44,6 +44,8 @@ struct ConvLaunch {
     // rows of Y kind k that A p has there for p = r: (T)(scale * r), the value
     // the A launch's initialisation workgroups would write (0: none)
     int idrows;
+    // most identity blocks of an instance of the tables (conv_sub)
+    int nid;
 };
 struct DenseLaunch {
     const DenseTile* tiles;

@@ -320,10 +320,10 @@ def test_start_test_ahead_of_the_products(family, prec, batch, cg_tol):
             np.testing.assert_array_equal(a, b)
 
 
-# both sides of the kernel lengths where the narrow form takes over (padded taps: FP64 160,
+# both sides of the kernel lengths where a narrow form takes over (padded taps: FP64 128,
 # FP32 8), ends of a step of 16 taps, tile edges, a chunk of 1024 taps of the wide form and
 # more, and the 512 tiles from which every kernel takes the wide form
-@pytest.mark.parametrize("n,k", [(1, 156), (1, 157), (96, 161), (200, 172), (97, 160), (3000, 177), (130900, 160),
+@pytest.mark.parametrize("n,k", [(1, 124), (1, 125), (96, 161), (200, 140), (97, 128), (3000, 145), (130900, 160),
                                  (130914, 160), (131000, 1030), (131200, 2060), (300, 8), (300, 7)])
 @pytest.mark.parametrize("prec", [P.FP64, P.FP32], ids=["fp64", "fp32"])
 def test_direct_convolution_forms(n, k, prec):

@@ -159,10 +159,12 @@ def product_gates(f, cg_per_step):
     return steps
 
 
-def direct_convolution(f, n, k, precision):
+def direct_convolution(f, n, k, precision, ids):
     """Grid and LDS of the direct convolution's launch for A x."""
     n, k = int(n), int(k)
     op = f.P.Operator(n + k - 1, n).add_conv(0, 0, np.ones(k), n)
+    for _ in range(int(ids)):
+        op.add_identity(0, 0, 1)
     pr = types.SimpleNamespace(op=op, l=n + k - 1, q=[], b=np.ones(n + k - 1), c=np.ones(n))
     h = f.solver(pr, precision=int(precision), conv_mfma=0, fused_max=0)
     f.launches.clear()
@@ -299,16 +301,17 @@ def test_every_timed_step_ends_its_cg(fake, family, precision):
 
 
 # workgroups per tile of 256 (FP64) or 512 outputs, and bytes of LDS (taps and window)
-@pytest.mark.parametrize("n,k,precision,per,lds", [
-    (5000, 33, 0, 1, (2 * 36 + 264) * 8), (5000, 156, 0, 1, (2 * 156 + 264) * 8), (5000, 160, 0, 2, (2 * 160 + 264) * 8),
-    (130000, 257, 0, 2, (2 * 260 + 264) * 8), (140000, 257, 0, 1, (2 * 260 + 264) * 8),
-    (140000, 2047, 0, 1, (2 * 1024 + 264) * 8), (5000, 5, 1, 2, (2 * 8 + 528) * 4), (300000, 5, 1, 1, (2 * 8 + 528) * 4),
-    (300000, 2047, 1, 1, (2 * 2048 + 528) * 4)])
-def test_form_of_the_direct_convolution(fake, n, k, precision, per, lds):
-    """Narrow form (two workgroups per tile) up to 512 tiles and from the kernel lengths where
-    it is the faster one; the wide form's chunks of taps leave the LDS for eight waves."""
+@pytest.mark.parametrize("n,k,precision,ids,per,lds", [
+    (5000, 33, 0, 4, 1, (2 * 36 + 264) * 8), (5000, 33, 0, 5, 2, (2 * 36 + 264) * 8),
+    (5000, 124, 0, 0, 1, (2 * 124 + 264) * 8), (5000, 125, 0, 0, 2, (2 * 128 + 264) * 8),
+    (130000, 257, 0, 0, 2, (2 * 260 + 264) * 8), (140000, 257, 0, 9, 1, (2 * 260 + 264) * 8),
+    (140000, 2047, 0, 0, 1, (2 * 1024 + 264) * 8), (5000, 5, 1, 0, 2, (2 * 8 + 528) * 4),
+    (300000, 5, 1, 0, 1, (2 * 8 + 528) * 4), (300000, 2047, 1, 9, 1, (2 * 2048 + 528) * 4)])
+def test_form_of_the_direct_convolution(fake, n, k, precision, ids, per, lds):
+    """Narrow form (two workgroups per tile) up to 512 tiles and from the kernel lengths or
+    numbers of identity blocks where it is the faster one; the wide form's chunks of taps leave the LDS for eight waves."""
     tile = 256 if precision == 0 else 512
-    assert fake(direct_convolution, n, k, precision) == [[per * -(-(n + k - 1) // tile), lds]]
+    assert fake(direct_convolution, n, k, precision, ids) == [[per * -(-(n + k - 1) // tile), lds]]
 
 
 @pytest.mark.parametrize("precision", [0, 1, 2])
