@@ -88,7 +88,8 @@ DEVI int tw_index(int e) {   // entry -> m
 // operator's upload runs on its device ahead of every product, computes and stores those
 // that are not there yet (still zero: once there, no entry is written again).  A workgroup of
 // a product copies them to LDS beside its window loads; computing them there (eight
-// sincospi per thread) took about 0.6 us of every launch.
+// sincospi per thread) takes 0.7 us of a small launch (n = 20011, k = 201: 7.8 us, with the
+// table 7.1) and up to 1.2 at n = 2^20 (A 11.3 and 10.1, A^T 9.8 and 9.3).
 __device__ float2 g_twiddles[TW_N];
 constexpr int TW_PER = (TW_N + FT - 1) / FT;
 struct TwRegs {
